@@ -98,6 +98,7 @@ struct Tab {
     const double* fr;  // per frame: SS (trapezoid sum of the running integral Q),
                        // PP (trapezoid sum of C), R (sum of C over the frame's steps), omega
     const int* nf;     // steps per frame
+    const double* qa;  // per frame: trapezoid sum of the running integral of |C| (bounds SS and every response)
 };
 
 struct InferArgs {
@@ -123,6 +124,11 @@ struct InferArgs {
     double prop_logscale;  // log of the sd scale of every mixture component
     double prop_logvol;    // sum_j log(phi_j - plo_j): minus the log prior density
     const float* below;    // [V] given ABC thresholds (kept draws above them do not count), or nullptr
+    // screened draws (vpet_infer_screen_kernel)
+    const float* scr;      // [F][8][nseg] segment polynomials of the responses
+    int nseg;
+    unsigned seg0;         // first segment (float bits of beta + b0, shifted)
+    float b0;
 };
 
 // ---------------------------------------------------------------------------
@@ -801,19 +807,15 @@ struct TacSink {
 // ---------------------------------------------------------------------------
 // Kernels.
 // ---------------------------------------------------------------------------
+// fp32 distances (NaN as +inf) of the draws idx of list position m.
 template <int KIND, int U, bool L1>
-__device__ __forceinline__ void tile_keys(const InferArgs& P, int m, uint32_t v, uint32_t i0,
-                                          const double2* yw, uint64_t (&key)[U]) {
+__device__ __forceinline__ void draw_distances(const InferArgs& P, int m, uint32_t v, const uint32_t (&idx)[U],
+                                               const double2* yw, float (&fd)[U]) {
     const ModelDev& md = P.md[m];
     constexpr int NE = ModelTraits<KIND>::NE;
     DrawState<NE, U> s;
-    uint32_t idx[U];
-    bool ok[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint32_t i = i0 + (uint32_t)(u * kWave + lane_id());
-        ok[u] = i < P.n_draws;
-        idx[u] = ok[u] ? i : P.n_draws - 1;
         float th[kMaxParams];
         draw_params(md, P.key0, P.key1, v, idx[u], (uint32_t)m, th);
         setup<KIND, NE, U>(th, P.h, P.C0, s, u);
@@ -825,10 +827,28 @@ __device__ __forceinline__ void tile_keys(const InferArgs& P, int m, uint32_t v,
     simulate_draws<KIND, U>(P.tab, P.F, P.k0, s, sink);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        float fd = (float)sink.d[u];
-        if (!(fd == fd)) fd = __builtin_inff();
+        const float f = (float)sink.d[u];
+        fd[u] = f == f ? f : __builtin_inff();
+    }
+}
+
+template <int KIND, int U, bool L1>
+__device__ __forceinline__ void tile_keys(const InferArgs& P, int m, uint32_t v, uint32_t i0,
+                                          const double2* yw, uint64_t (&key)[U]) {
+    uint32_t idx[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t i = i0 + (uint32_t)(u * kWave + lane_id());
+        ok[u] = i < P.n_draws;
+        idx[u] = ok[u] ? i : P.n_draws - 1;
+    }
+    float fd[U];
+    draw_distances<KIND, U, L1>(P, m, v, idx, yw, fd);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
         const uint32_t g = (uint32_t)m * P.n_draws + idx[u];
-        key[u] = ok[u] ? (((uint64_t)__float_as_uint(fd) << 32) | g) : kNoKey;
+        key[u] = ok[u] ? (((uint64_t)__float_as_uint(fd[u]) << 32) | g) : kNoKey;
     }
 }
 
@@ -854,80 +874,148 @@ __device__ __forceinline__ bool slot_used(int kind, int q) {
     return true;
 }
 
-// KINDS: the one model kind of a single-model call (a smaller kernel with
-// fewer live registers), or 0 for any mix of models.
-template <int KINDS, bool L1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_kernel(InferArgs P) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long row = blockIdx.x;
-    if (row >= P.V) return;
-    const int F = P.F;
-    const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
-    double2* yw = reinterpret_cast<double2*>(lds);
-    const int yw_bytes = (16 * F + 15) & ~15;
-    uint64_t* keys_all = reinterpret_cast<uint64_t*>(lds + yw_bytes);
-    double* red = reinterpret_cast<double*>(keys_all + (size_t)P.wpv * P.cap);
-    int* flag = reinterpret_cast<int*>(red + kRedStride * kMaxWpv);
-    const int n = (int)P.n_acc;
+// Outputs of an invalid voxel (one wavefront).
+__device__ __forceinline__ void infer_invalid(const InferArgs& P, long long row) {
+    const int lane = lane_id(), n = (int)P.n_acc;
+    const float qnan = __builtin_nanf("");
+    for (int j = lane; j < P.M * 16; j += kWave) P.out_mom[(size_t)row * P.M * 16 + j] = qnan;
+    for (int j = lane; j < P.M; j += kWave) P.out_prob[(size_t)row * P.M + j] = qnan;
+    if (P.out_idx)
+        for (int j = lane; j < n; j += kWave) P.out_idx[(size_t)row * n + j] = -1;
+    if (P.out_dist)
+        for (int j = lane; j < n; j += kWave) P.out_dist[(size_t)row * n + j] = qnan;
+    if (P.out_thr && lane == 0) P.out_thr[row] = qnan;
+}
 
-    // Observed curve, validity and scaled weights (wave 0).
-    if (wave == 0) {
-        const float* y = P.tacs + (size_t)row * F;
-        const cdp FR = (cdp)P.tab.fr;
-        const cip NF = (cip)P.tab.nf;
-        float ymax = -__builtin_inff();
-        int bad = 0;
-        for (int f = lane; f < F; f += kWave) {
-            const float yy = y[f];
-            bad |= !isfinite(yy);
-            ymax = fmaxf(ymax, yy);
-            if (P.weights) {  // caller weights must be finite and >= 0
-                const float wv = P.weights[(size_t)row * F + f];
-                bad |= !(wv >= 0.0f) || !isfinite(wv);
-            }
-        }
+// Outputs of one voxel from its n accepted keys (ascending, in LDS).
+__device__ __forceinline__ void infer_outputs(const InferArgs& P, long long row, uint32_t vg, const uint64_t* acc,
+                                              double* red) {
+    const int tid = threadIdx.x, n = (int)P.n_acc;
+    if (P.out_idx)
+        for (int j = tid; j < n; j += blockDim.x) P.out_idx[(size_t)row * n + j] = (int)(uint32_t)acc[j];
+    if (P.out_dist)
+        for (int j = tid; j < n; j += blockDim.x) P.out_dist[(size_t)row * n + j] = __uint_as_float((uint32_t)(acc[j] >> 32));
+    if (P.out_thr && tid == 0) P.out_thr[row] = __uint_as_float((uint32_t)(acc[n - 1] >> 32));
+
+    // Survivor reduction per model: count, mean, variance (two passes, FP64).
+    // A thread's first key keeps its values between the passes.
+    const uint32_t g0 = tid < n ? (uint32_t)acc[tid] : 0u;
+    for (int m = 0; m < P.M; ++m) {
+        const ModelDev& md = P.md[m];
+        auto values = [&](uint32_t g, double (&val)[6]) {
+            float th[kMaxParams];
+            draw_params(md, P.key0, P.key1, vg, g - (uint32_t)m * P.n_draws, (uint32_t)m, th);
+            slot_values(md.kind, th, val);
+        };
+        double s1[7], v0[6];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            ymax = fmaxf(ymax, __shfl_xor(ymax, off, kWave));
-            bad |= __shfl_xor(bad, off, kWave);
+        for (int q = 0; q < 7; ++q) s1[q] = 0.0;
+        const bool mine0 = tid < n && g0 / P.n_draws == (uint32_t)m;
+        if (mine0) {
+            values(g0, v0);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) s1[q] += v0[q];
+            s1[6] += 1.0;
         }
-        const bool valid = !bad && ymax > 0.0f;
-        const double den_floor = P.floor_frac * (double)ymax;
-        for (int f = lane; f < F; f += kWave) {
-            const double nfd = (double)NF[f];
-            const double yy = (double)y[f];
-            double w;
-            if (P.weights) {
-                w = (double)P.weights[(size_t)row * F + f];
-            } else {
-                const double den = yy > den_floor ? yy : den_floor;
-                w = FR[4 * f + 3] / den;
+        for (int j = tid + blockDim.x; j < n; j += blockDim.x) {
+            const uint32_t g = (uint32_t)acc[j];
+            if (g / P.n_draws != (uint32_t)m) continue;
+            double val[6];
+            values(g, val);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) s1[q] += val[q];
+            s1[6] += 1.0;
+        }
+        block_sum<7>(s1, red, P.wpv);
+        const double cnt = s1[6];
+        double mean[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) mean[q] = s1[q] / cnt;
+        double s2[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) s2[q] = 0.0;
+        if (mine0) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const double dv = v0[q] - mean[q];
+                s2[q] = fma(dv, dv, s2[q]);
             }
-            const double sw = sqrt(w);
-            yw[f] = P.l1 ? make_double2(nfd * yy, sw / nfd) : make_double2(sw * yy, sw / nfd);
         }
-        if (lane == 0) *flag = valid ? 1 : 0;
-    }
-    __syncthreads();
-    if (*flag == 0) {
-        if (wave == 0) {
-            const float qnan = __builtin_nanf("");
-            for (int j = lane; j < P.M * 16; j += kWave) P.out_mom[(size_t)row * P.M * 16 + j] = qnan;
-            for (int j = lane; j < P.M; j += kWave) P.out_prob[(size_t)row * P.M + j] = qnan;
-            if (P.out_idx)
-                for (int j = lane; j < n; j += kWave) P.out_idx[(size_t)row * n + j] = -1;
-            if (P.out_dist)
-                for (int j = lane; j < n; j += kWave) P.out_dist[(size_t)row * n + j] = qnan;
-            if (P.out_thr && lane == 0) P.out_thr[row] = qnan;
+        for (int j = tid + blockDim.x; j < n; j += blockDim.x) {
+            const uint32_t g = (uint32_t)acc[j];
+            if (g / P.n_draws != (uint32_t)m) continue;
+            double val[6];
+            values(g, val);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const double dv = val[q] - mean[q];
+                s2[q] = fma(dv, dv, s2[q]);
+            }
         }
-        return;
+        block_sum<6>(s2, red, P.wpv);
+        if (tid < 16) {
+            const int q = tid >> 1;
+            float outv = __builtin_nanf("");
+            if (q < 6 && slot_used(md.kind, q) && cnt > 0.0) {
+                if ((tid & 1) == 0)
+                    outv = (float)mean[q];
+                else
+                    outv = (cnt > 1.0) ? (float)(s2[q] / (cnt - 1.0)) : 0.0f;
+            }
+            P.out_mom[((size_t)row * P.M + m) * 16 + tid] = outv;
+        }
+        if (tid == 0) P.out_prob[(size_t)row * P.M + m] = (float)(cnt / (double)n);
     }
+}
 
-    // Stream every draw of every model through the wave's running top-n.
+// Observed curve, validity and scaled weights of a voxel (one wavefront).
+__device__ __forceinline__ void voxel_curve(const InferArgs& P, long long row, double2* yw, int* flag) {
+    const int lane = lane_id(), F = P.F;
+    const float* y = P.tacs + (size_t)row * F;
+    const cdp FR = (cdp)P.tab.fr;
+    const cip NF = (cip)P.tab.nf;
+    float ymax = -__builtin_inff();
+    int bad = 0;
+    for (int f = lane; f < F; f += kWave) {
+        const float yy = y[f];
+        bad |= !isfinite(yy);
+        ymax = fmaxf(ymax, yy);
+        if (P.weights) {  // caller weights must be finite and >= 0
+            const float wv = P.weights[(size_t)row * F + f];
+            bad |= !(wv >= 0.0f) || !isfinite(wv);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        ymax = fmaxf(ymax, __shfl_xor(ymax, off, kWave));
+        bad |= __shfl_xor(bad, off, kWave);
+    }
+    const bool valid = !bad && ymax > 0.0f;
+    const double den_floor = P.floor_frac * (double)ymax;
+    for (int f = lane; f < F; f += kWave) {
+        const double nfd = (double)NF[f];
+        const double yy = (double)y[f];
+        double w;
+        if (P.weights) {
+            w = (double)P.weights[(size_t)row * F + f];
+        } else {
+            const double den = yy > den_floor ? yy : den_floor;
+            w = FR[4 * f + 3] / den;
+        }
+        const double sw = sqrt(w);
+        yw[f] = P.l1 ? make_double2(nfd * yy, sw / nfd) : make_double2(sw * yy, sw / nfd);
+    }
+    if (lane == 0) *flag = valid ? 1 : 0;
+}
+
+// Every draw of every model through this wavefront's running top-n: the wave's
+// n smallest keys end sorted at keys_all[wave cap ..].
+template <int KINDS, bool L1>
+__device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, const double2* yw, uint64_t* keys_all) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
     TopN top;
     top.keys = keys_all + (size_t)wave * P.cap;
-    top.n = n;
+    top.n = (int)P.n_acc;
     top.cap = P.cap;
     top.nbuf = 0;
     top.tau = kNoKey;
@@ -952,68 +1040,616 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         }
     }
     top.merge();
+}
+
+// KINDS: the one model kind of a single-model call (a smaller kernel with
+// fewer live registers), or 0 for any mix of models.
+template <int KINDS, bool L1>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_kernel(InferArgs P) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int wave = threadIdx.x >> 6;
+    const long long row = blockIdx.x;
+    if (row >= P.V) return;
+    const int F = P.F;
+    const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
+    double2* yw = reinterpret_cast<double2*>(lds);
+    const int yw_bytes = (16 * F + 15) & ~15;
+    uint64_t* keys_all = reinterpret_cast<uint64_t*>(lds + yw_bytes);
+    double* red = reinterpret_cast<double*>(keys_all + (size_t)P.wpv * P.cap);
+    int* flag = reinterpret_cast<int*>(red + kRedStride * kMaxWpv);
+    const int n = (int)P.n_acc;
+
+    if (wave == 0) voxel_curve(P, row, yw, flag);
+    __syncthreads();
+    if (*flag == 0) {
+        if (wave == 0) infer_invalid(P, row);
+        return;
+    }
+
+    stream_draws<KINDS, L1>(P, vg, yw, keys_all);
     __syncthreads();
     if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
     const uint64_t* acc = keys_all;  // the n accepted keys, ascending
 
-    if (P.out_idx)
-        for (int j = tid; j < n; j += blockDim.x) P.out_idx[(size_t)row * n + j] = (int)(uint32_t)acc[j];
-    if (P.out_dist)
-        for (int j = tid; j < n; j += blockDim.x) P.out_dist[(size_t)row * n + j] = __uint_as_float((uint32_t)(acc[j] >> 32));
-    if (P.out_thr && tid == 0) P.out_thr[row] = __uint_as_float((uint32_t)(acc[n - 1] >> 32));
+    infer_outputs(P, row, vg, acc, red);
+}
 
-    // Survivor reduction per model: count, mean, variance (two passes, FP64).
-    for (int m = 0; m < P.M; ++m) {
-        const ModelDev& md = P.md[m];
-        double s1[7];
-#pragma unroll
-        for (int q = 0; q < 7; ++q) s1[q] = 0.0;
-        for (int j = tid; j < n; j += blockDim.x) {
-            const uint32_t g = (uint32_t)acc[j];
-            if (g / P.n_draws != (uint32_t)m) continue;
-            float th[kMaxParams];
-            draw_params(md, P.key0, P.key1, vg, g - (uint32_t)m * P.n_draws, (uint32_t)m, th);
-            double val[6];
-            slot_values(md.kind, th, val);
-#pragma unroll
-            for (int q = 0; q < 6; ++q) s1[q] += val[q];
-            s1[6] += 1.0;
-        }
-        block_sum<7>(s1, red, P.wpv);
-        const double cnt = s1[6];
-        double mean[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) mean[q] = s1[q] / cnt;
-        double s2[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) s2[q] = 0.0;
-        for (int j = tid; j < n; j += blockDim.x) {
-            const uint32_t g = (uint32_t)acc[j];
-            if (g / P.n_draws != (uint32_t)m) continue;
-            float th[kMaxParams];
-            draw_params(md, P.key0, P.key1, vg, g - (uint32_t)m * P.n_draws, (uint32_t)m, th);
-            double val[6];
-            slot_values(md.kind, th, val);
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const double dv = val[q] - mean[q];
-                s2[q] = fma(dv, dv, s2[q]);
-            }
-        }
-        block_sum<6>(s2, red, P.wpv);
-        if (tid < 16) {
-            const int q = tid >> 1;
-            float outv = __builtin_nanf("");
-            if (q < 6 && slot_used(md.kind, q) && cnt > 0.0) {
-                if ((tid & 1) == 0)
-                    outv = (float)mean[q];
-                else
-                    outv = (cnt > 1.0) ? (float)(s2[q] / (cnt - 1.0)) : 0.0f;
-            }
-            P.out_mom[((size_t)row * P.M + m) * 16 + tid] = outv;
-        }
-        if (tid == 0) P.out_prob[(size_t)row * P.M + m] = (float)(cnt / (double)n);
+// ===========================================================================
+// Screened draws (L2).  A one-exponential model's curve is
+//     x_f = A e_f(beta) + B q_f + v p_f
+// with three fixed families over the grid: e_f(beta), the frame averages of
+// exp(-beta t) convolved with the input, q_f those of its running integral and
+// p_f those of the input itself (1TCM: A = (1 - vB) K1, beta = k2, B = 0;
+// irreversible 2TCM: beta = k2 + k3, A = (1 - vB) K1 k2 / beta, B = (1 - vB)
+// K1 k3 / beta; v = vB).  The weighted distance is therefore
+//     d = yy + A (A ee + ye + B eq + v ep) + B (B qq + yq + v qp) + v (v pp + yp)
+// with ee = sum w e^2, ye = -2 sum w y e, eq = 2 sum w q e, ep = 2 sum w p e:
+// four functions of the one variable beta and six constants per voxel.  The
+// functions are tabulated per voxel as cubics on the segments of u = beta + b0
+// (16 per octave), after which a draw costs about 100 fp32 instructions
+// instead of the 600 of its FP64 recursion over every grid step.
+//
+// The screen only rules draws out.  With err bounding |d~ - d| (below), every
+// draw whose lower bound d~ - err exceeds the n-th smallest upper bound
+// d~ + err seen so far cannot be among the n closest; the others (about 1.1 n
+// at the end) get the FP64 recursion of the streaming kernel, so the accepted
+// set, its keys and the outputs are that kernel's.  A voxel whose candidates
+// do not fit (ties everywhere, a curve outside the fp32 range) takes that
+// kernel's path.  Bound by the vector ALU's issue rate, as that kernel is:
+// 16,384 voxels x 100k draws (30 frames, 250 steps) 31.0 -> 4.5 ms, 1024 voxels
+// x 2000 draws 83 -> 70 us.
+//
+// Error bound.  Let Y, Q, Qa, P be the vectors s y, s q, s qa, s p (s =
+// sqrt(w), qa the frame averages of the running integral of |C|) and |e_f^(k)
+// u^k| <= max_t (u t)^k e^{-u t} e^{b0 t} qa_f.  b0 <= 1/(2 T) (T = end of the
+// grid) and k = 4: 4.69 e^0.5 qa_f, and 4.69 e qa_f^2 for e_f^2.  A segment has
+// half-width <= u/32 and the cubic interpolates at its Chebyshev nodes, so its
+// error is at most (1/32)^4/192 = 5.0e-9 times that: 3.9e-8 qa_f and 6.4e-8
+// qa_f^2, which moves d by at most 7.7e-8 A |Qa| m with m = |Y| + (A + B) |Qa| +
+// v |P|.  Forming u in fp32 (two roundings, 2^-23 u) moves e_f by at most 2^-23
+// e^-1 e^0.5 qa_f = 7.3e-8 qa_f, d by 14.6e-8 A |Qa| m.  Together 2.3e-7 A |Qa| m;
+// kScrEta = 2.6e-7 covers the fp32 rounding of the polynomials' higher
+// coefficients.  The rest are fp32 roundings relative to the sum of the
+// magnitudes of the terms of d, which Cauchy-Schwarz bounds by 4 T, T = yy +
+// A^2 ee + B^2 qq + v^2 pp: 16 roundings of a term (2^-24 each) and the relative
+// error of A and B (5 roundings and the hardware reciprocal, 4.2e-7, acting as
+// 2 sqrt(d) |dx| <= 2 sqrt(4 T) 4.2e-7 sqrt(3 T)) add up to 3.8e-6 T + 2.9e-6 T;
+// kScrEps = 9e-6.
+// ===========================================================================
+constexpr int kScrShift = 23 - 4;        // float bits below a segment: 16 segments per octave of u = beta + b0
+constexpr int kScrMaxSeg = 256;
+constexpr float kScrEta = 2.6e-7f, kScrEps = 9e-6f;
+constexpr long long kScrMaxDraws = 1LL << 24;  // a key holds 24 bits of draw index
+
+// Segment polynomials of e_f and e_f^2 (frame averages), coefficients of
+// t^0..t^3 with t in [-1/2, 1/2) across the segment: out[f][0..3][seg] and
+// out[f][4..7][seg].  Four consecutive lanes share a segment, one per
+// Chebyshev node; each runs the FP64 recursion at its node, then forms one
+// coefficient from the quad's four values.  The kernel is one serial chain
+// per lane, bound by its latency: the input nodes and frame sums are staged
+// in LDS in chunks (through the scalar cache the chain took 23 us for 300
+// steps).
+constexpr int kScrChunk = 2048;
+__global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0, double h, int F, int k0, int nseg,
+                                                               unsigned seg0, float b0, float* out) {
+    __shared__ double sC[kScrChunk], sP[VPET_MAX_FRAMES];
+    __shared__ int sN[VPET_MAX_FRAMES];
+    const int lane = threadIdx.x, j = lane & 3;
+    const int seg = blockIdx.x * 16 + (lane >> 2);
+    const int sg = min(seg, nseg - 1);
+    int kend = k0;
+    for (int f = lane; f < F; f += kWave) {
+        sP[f] = T.fr[4 * f + 1];
+        sN[f] = T.nf[f];
+        kend += T.nf[f];
     }
+    kend = wave_sum(kend - k0) + k0;
+    const double ulo = (double)__uint_as_float((seg0 + (unsigned)sg) << kScrShift);
+    const double wid = (double)__uint_as_float((seg0 + (unsigned)sg + 1u) << kScrShift) - ulo;
+    // Chebyshev nodes x_j = cos((2 j + 1) pi / 8) / 2, the rows of the inverse
+    // Vandermonde matrix from the product form of the Lagrange basis
+    const double ca = 0.46193976625564337, cb = 0.19134171618254492;
+    const double x[4] = {ca, cb, -cb, -ca};
+    double M[4];  // row j of the inverse: coefficient j from the four values
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        // prod_{i != q} (t - x_i) = t^3 - s1 t^2 + s2 t - s3
+        const double a = x[(q + 1) & 3], b = x[(q + 2) & 3], c = x[(q + 3) & 3];
+        const double rden = 1.0 / ((x[q] - a) * (x[q] - b) * (x[q] - c));
+        const double co[4] = {-a * b * c, a * b + a * c + b * c, -(a + b + c), 1.0};
+        M[q] = (j == 0 ? co[0] : (j == 1 ? co[1] : (j == 2 ? co[2] : co[3]))) * rden;
+    }
+    const double xj = j == 0 ? x[0] : (j == 1 ? x[1] : (j == 2 ? x[2] : x[3]));
+    double bA;
+    const Exp1 e = exp_setup(ulo + wid * (0.5 + xj) - (double)b0, 1.0, h, C0, &bA);
+    double H = e.H0, acc = 0.0;
+    int k = 0, kc = 0;  // kc: nodes [kc - kScrChunk, kc) are staged
+    auto steps = [&](int n) {  // n recursion steps from node k, adding H before each to acc
+        const int end = k + n;
+        while (k < end) {
+            if (k == kc) {
+                __syncthreads();
+                for (int q = lane; q < kScrChunk && kc + q < kend; q += kWave) sC[q] = T.C[kc + q];
+                __syncthreads();
+                kc += kScrChunk;
+            }
+            const int stop = min(end, kc);
+            const double* c = sC + (k - (kc - kScrChunk));
+            const int m = stop - k;
+#pragma unroll 8
+            for (int q = 0; q < m; ++q) {
+                acc += H;
+                H = fma(e.z, H, c[q]);
+            }
+            k = stop;
+        }
+    };
+    steps(k0);
+    for (int f = 0; f < F; ++f) {
+        const int n = sN[f];
+        const double Hs = H;
+        acc = 0.0;
+        steps(n);
+        // frame average of the response's trapezoid sum, (acc - (Hs - H) / 2) g + b PP
+        const double v = fma(e.eT, fma(-0.5, Hs - H, acc), bA * sP[f]) / (double)n;
+        const double y[4] = {dpp_f64<0x00>(v), dpp_f64<0x55>(v), dpp_f64<0xAA>(v), dpp_f64<0xFF>(v)};
+        double c = 0.0, c2 = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c = fma(M[q], y[q], c);
+            c2 = fma(M[q], y[q] * y[q], c2);
+        }
+        if (seg < nseg) {
+            out[((size_t)f * 8 + j) * nseg + seg] = (float)c;
+            out[((size_t)f * 8 + 4 + j) * nseg + seg] = (float)c2;
+        }
+    }
+}
+
+// A voxel's constants of the screen.
+struct ScreenVox {
+    float yy, yq, yp, qq, qp, pp, ny, nq, np, kap;
+};
+
+__device__ __forceinline__ float wave_uniform(float x) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+}
+
+// Screen constants of a voxel (wave 0, after voxel_curve): fs[f] = (w, -2 w y,
+// 2 w q, 2 w p) for the table, the sums, and whether fp32 can hold them.
+__device__ __forceinline__ bool screen_voxel(const InferArgs& P, const double2* yw, double4* fs, ScreenVox* sv) {
+    const int lane = lane_id();
+    const cdp FR = (cdp)P.tab.fr;
+    const cip NF = (cip)P.tab.nf;
+    double yy = 0.0, yq = 0.0, yp = 0.0, qq = 0.0, qp = 0.0, pp = 0.0, aa = 0.0;
+    for (int f = lane; f < P.F; f += kWave) {
+        const double nf = (double)NF[f], sn = yw[f].y, Y = yw[f].x;  // s / n_f, s y
+        const double s = sn * nf, q = sn * FR[4 * f], p = sn * FR[4 * f + 1], a = sn * P.tab.qa[f];
+        fs[f] = make_double4(s * s, -2.0 * s * Y, 2.0 * s * q, 2.0 * s * p);
+        yy = fma(Y, Y, yy);
+        yq = fma(Y, q, yq);
+        yp = fma(Y, p, yp);
+        qq = fma(q, q, qq);
+        qp = fma(q, p, qp);
+        pp = fma(p, p, pp);
+        aa = fma(a, a, aa);
+    }
+    yy = wave_sum(yy);
+    yq = wave_sum(yq);
+    yp = wave_sum(yp);
+    qq = wave_sum(qq);
+    qp = wave_sum(qp);
+    pp = wave_sum(pp);
+    aa = wave_sum(aa);
+    const double ny = sqrt(yy), nq = sqrt(aa), np = sqrt(pp);
+    double K1 = 0.0, vB = 0.0;
+    for (int m = 0; m < P.M; ++m) {
+        K1 = fmax(K1, (double)P.md[m].lo[0] + (double)P.md[m].wid[0]);
+        vB = fmax(vB, (double)P.md[m].lo[P.md[m].np - 1] + (double)P.md[m].wid[P.md[m].np - 1]);
+    }
+    const double mm = ny + K1 * nq + vB * np;
+    if (lane == 0) {
+        sv->yy = (float)yy;
+        sv->yq = (float)(-2.0 * yq);
+        sv->yp = (float)(-2.0 * yp);
+        sv->qq = (float)qq;
+        sv->qp = (float)(2.0 * qp);
+        sv->pp = (float)pp;
+        sv->ny = (float)(ny * 1.000001);
+        sv->nq = (float)(nq * 1.000001);
+        sv->np = (float)(np * 1.000001);
+        sv->kap = kScrEta * (float)(nq * 1.000001);
+    }
+    return mm * mm < 1e12 && aa < 1e12 && yy > 1e-10;
+}
+
+// The voxel's table: per segment the cubics of ee, ye, eq and ep (FP64 sums),
+// a thread per segment, four frames' loads in flight.
+__device__ __forceinline__ void screen_table(const InferArgs& P, const double4* fs, float4* tab) {
+    for (int s = threadIdx.x; s < P.nseg; s += blockDim.x) {
+        double a[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) a[k] = 0.0;
+        const float* c = P.scr + s;
+        const size_t st = (size_t)P.nseg;
+#pragma unroll 4
+        for (int f = 0; f < P.F; ++f, c += 8 * st) {
+            const double4 q = fs[f];
+            float e[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) e[r] = c[r * st];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                a[r] = fma(q.x, (double)e[4 + r], a[r]);
+                a[4 + r] = fma(q.y, (double)e[r], a[4 + r]);
+                a[8 + r] = fma(q.z, (double)e[r], a[8 + r]);
+                a[12 + r] = fma(q.w, (double)e[r], a[12 + r]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            tab[4 * s + k] = make_float4((float)a[4 * k], (float)a[4 * k + 1], (float)a[4 * k + 2], (float)a[4 * k + 3]);
+    }
+}
+
+__device__ __forceinline__ float cubic(const float4& c, float t) {
+    return fmaf(t, fmaf(t, fmaf(t, c.w, c.z), c.y), c.x);
+}
+
+// Lower bound and error bound of the distance for given coefficients.
+__device__ __forceinline__ void screen_bounds(const ScreenVox& S, const float4* tab, unsigned seg0, float b0, float beta,
+                                              float A, float B, float W, float v, float& lower, float& err) {
+    const uint32_t ub = __float_as_uint(beta + b0);
+    const float4* row = tab + 4 * ((ub >> kScrShift) - seg0);
+    const float t = __uint_as_float(((ub << (23 - kScrShift)) & 0x7FFFFFu) | 0x3F800000u) - 1.5f;
+    const float ee = cubic(row[0], t), ye = cubic(row[1], t), eq = cubic(row[2], t), ep = cubic(row[3], t);
+    const float a = A * ee, b = B * S.qq, c = v * S.pp;
+    const float ia = fmaf(v, ep, fmaf(B, eq, a + ye)), ib = fmaf(v, S.qp, b + S.yq), ic = c + S.yp;
+    const float d = fmaf(A, ia, fmaf(B, ib, fmaf(v, ic, S.yy)));
+    const float T = fmaf(A, a, fmaf(B, b, fmaf(v, c, S.yy)));
+    const float m = fmaf(W, S.nq, fmaf(v, S.np, S.ny));
+    err = fmaf(A * S.kap, m, kScrEps * T);
+    lower = d - err;
+}
+
+// Draw i of list position m: prior draw in fp32 (the exact fp32 parameters),
+// then the screen.
+template <int KIND>
+__device__ __forceinline__ void screen_draw(const InferArgs& P, const ScreenVox& S, const float4* tab, int m, uint32_t vg,
+                                            uint32_t i, float& lower, float& err) {
+    const ModelDev& md = P.md[m];
+    uint32_t w[4];
+    philox10(i, vg, 0u, (uint32_t)m << 16, P.key0, P.key1, w);
+    const float K1 = fmaf(md.wid[0], unit24(w[0]), md.lo[0]), k2 = fmaf(md.wid[1], unit24(w[1]), md.lo[1]);
+    const float p2 = fmaf(md.wid[2], unit24(w[2]), md.lo[2]);
+    if constexpr (KIND == KIND_1TCM) {
+        const float W = (1.0f - p2) * K1;
+        screen_bounds(S, tab, P.seg0, P.b0, k2, W, 0.0f, W, p2, lower, err);
+    } else {
+        const float vB = fmaf(md.wid[3], unit24(w[3]), md.lo[3]);
+        const float beta = k2 + p2, W = (1.0f - vB) * K1, r = W * __builtin_amdgcn_rcpf(beta);
+        screen_bounds(S, tab, P.seg0, P.b0, beta, r * k2, r * p2, W, vB, lower, err);
+    }
+}
+
+// Candidates of one wavefront: keys (lower bound, error class, draw), the
+// first `have` of them sorted and certified at or below tau, an upper bound of
+// the wave's n-th smallest distance.  The error class is the error rounded up
+// to the next float with two mantissa bits.
+constexpr uint32_t kErrBase = (127u - 40u) << 2;
+__device__ __forceinline__ uint64_t screen_key(float lower, float err, uint32_t g) {
+    const uint32_t cls = min(max((__float_as_uint(err) >> 21) + 1u, kErrBase) - kErrBase, 255u);
+    return ((uint64_t)__float_as_uint(fmaxf(lower, 0.0f)) << 32) | (cls << 24) | g;
+}
+// The draw's upper bound, a little up so that fp32 ties at it stay candidates.
+__device__ __forceinline__ float screen_upper(uint64_t key) {
+    const float l = __uint_as_float((uint32_t)(key >> 32));
+    const float e = __uint_as_float((((uint32_t)key >> 24) + kErrBase) << 21);
+    return fmaf(2.0f, e, l) * 1.0000005f;
+}
+
+struct ScreenList {
+    uint64_t* keys;
+    int n, cap, have, nbuf;
+    float tau;
+    bool full;  // the candidates do not fit
+
+    // tau = the largest upper bound of the first n keys; the keys whose lower
+    // bound is at or below it (a prefix of the sorted keys) stay.
+    __device__ static float prefix(const uint64_t* keys, int used, int n, int& have) {
+        float u = 0.0f;
+        for (int j = lane_id(); j < n; j += kWave) u = fmaxf(u, screen_upper(keys[j]));
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) u = fmaxf(u, __shfl_xor(u, off, kWave));
+        u = wave_uniform(u);
+        int c = 0;
+        for (int j0 = 0; j0 < used; j0 += kWave) {
+            const int j = j0 + lane_id();
+            c += __popcll(__ballot(j < used && __uint_as_float((uint32_t)(keys[j < used ? j : 0] >> 32)) <= u));
+        }
+        have = c;
+        return u;
+    }
+
+    __device__ void merge() {
+        const int used = have + nbuf;
+        const int len = used <= 2 ? 2 : min(cap, 1 << (32 - __builtin_clz((unsigned)(used - 1))));
+        for (int j = used + lane_id(); j < len; j += kWave) keys[j] = kNoKey;
+        wave_lds_sync();
+        wave_bitonic_sort(keys, len);
+        nbuf = 0;
+        have = used;
+        if (used >= n) tau = prefix(keys, used, n, have);
+        full = full || have > cap - kWave;
+    }
+
+    // First tile, n <= 64: the n-th smallest of the lanes' smallest upper bounds
+    // is one of the n-th smallest distance, so that a short stream does not
+    // sort a buffer full of draws that it can rule out.
+    template <int U>
+    __device__ __forceinline__ void start(const float (&lower)[U], const float (&err)[U], const bool (&ok)[U]) {
+        float x = __builtin_inff();
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) x = fminf(x, fmaf(2.0f, err[u], lower[u]));
+        x = fmaxf(x, 0.0f);
+        const int lane = lane_id();
+#pragma unroll
+        for (int k = 2; k <= kWave; k <<= 1) {
+#pragma unroll
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                const float y = __shfl_xor(x, j, kWave);
+                x = ((lane & j) == 0) == ((lane & k) == 0) ? fminf(x, y) : fmaxf(x, y);
+            }
+        }
+        tau = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), n - 1)) * 1.0000005f;
+    }
+
+    template <int U>
+    __device__ __forceinline__ void insert(const float (&lower)[U], const float (&err)[U], const uint32_t (&g)[U],
+                                           const bool (&ok)[U]) {
+        if (n <= kWave && have + nbuf == 0 && tau == __builtin_inff()) start(lower, err, ok);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint64_t b = __ballot(ok[u] && lower[u] <= tau);
+            if (b == 0ull || full) continue;
+            if (nbuf + __popcll(b) > cap - have) {
+                merge();
+                if (full) continue;
+                b = __ballot(ok[u] && lower[u] <= tau);
+            }
+            if (ok[u] && lower[u] <= tau) keys[have + nbuf + (int)mbcnt(b)] = screen_key(lower[u], err[u], g[u]);
+            nbuf += __popcll(b);
+            wave_lds_sync();
+        }
+    }
+};
+
+// Keys of list position m's draws of the wave's tiles into the candidates.
+template <int KIND>
+__device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVox& S, const float4* tab, int m,
+                                              uint32_t vg, const double2* yw, ScreenList& list) {
+    constexpr int U = KIND == KIND_REV ? 2 : kUmax, kTile = kWave * U;
+    const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
+    for (uint32_t t = threadIdx.x >> 6; t < ntiles && !list.full; t += (uint32_t)P.wpv) {
+        float lower[U], err[U];
+        uint32_t g[U];
+        bool ok[U];
+        if constexpr (KIND == KIND_REV) {  // two exponentials: the exact distance
+            uint32_t idx[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = t * kTile + (uint32_t)(u * kWave + lane_id());
+                ok[u] = i < P.n_draws;
+                idx[u] = ok[u] ? i : P.n_draws - 1;
+                g[u] = (uint32_t)m * P.n_draws + idx[u];
+            }
+            draw_distances<KIND_REV, U, false>(P, m, vg, idx, yw, lower);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                err[u] = 0.0f;
+                lower[u] *= 0.9999998f;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = t * kTile + (uint32_t)(u * kWave + lane_id());
+                ok[u] = i < P.n_draws;
+                g[u] = (uint32_t)m * P.n_draws + i;
+                screen_draw<KIND>(P, S, tab, m, vg, i, lower[u], err[u]);
+            }
+        }
+        list.insert(lower, err, g, ok);
+    }
+}
+
+// Exact keys of the candidates keys[j0 + lane ...], j < count, in place: U per
+// lane, kWave apart (every lane of the wavefront calls this).
+template <int KINDS, int U>
+__device__ __forceinline__ void screen_exact(const InferArgs& P, uint32_t vg, const double2* yw, uint64_t* keys, int j0,
+                                             int count) {
+    uint32_t g[U];
+    float fd[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int j = j0 + u * kWave + lane_id();
+        g[u] = j < count ? (uint32_t)keys[j] & 0xFFFFFFu : 0u;
+        fd[u] = 0.0f;
+    }
+    auto run = [&](auto kind, int m) {
+        uint32_t idx[U];
+        float d[U];
+        bool mine[U], any = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            mine[u] = KINDS != 0 || g[u] / P.n_draws == (uint32_t)m;
+            idx[u] = mine[u] ? g[u] - (uint32_t)m * P.n_draws : 0u;
+            any = any || mine[u];
+        }
+        if (KINDS == 0 && __ballot(any) == 0ull) return;
+        draw_distances<decltype(kind)::value, U, false>(P, m, vg, idx, yw, d);
+#pragma unroll
+        for (int u = 0; u < U; ++u) fd[u] = mine[u] ? d[u] : fd[u];
+    };
+    if constexpr (KINDS != 0) {
+        run(std::integral_constant<int, KINDS>{}, 0);
+    } else {
+        for (int m = 0; m < P.M; ++m) {
+            if (P.md[m].kind == KIND_IRR)
+                run(std::integral_constant<int, KIND_IRR>{}, m);
+            else if (P.md[m].kind == KIND_REV)
+                run(std::integral_constant<int, KIND_REV>{}, m);
+            else
+                run(std::integral_constant<int, KIND_1TCM>{}, m);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int j = j0 + u * kWave + lane_id();
+        if (j < count) keys[j] = ((uint64_t)__float_as_uint(fd[u]) << 32) | g[u];
+    }
+}
+
+// The n smallest of the wavefronts' distinct keys (have[w] at keys_all[w cap ..])
+// in ascending order at keys_all[0, n): every key's place is the number of
+// smaller keys.  Lists that together exceed the block are sorted instead.
+__device__ __forceinline__ void block_rank(uint64_t* keys_all, int wpv, int cap, int n, const int* have) {
+    const int tid = threadIdx.x;
+    int total = 0, w = 0, off = 0;
+    for (int q = 0; q < wpv; ++q) {
+        if (tid >= total) {
+            w = q;
+            off = total;
+        }
+        total += have[q];
+    }
+    if (total > (int)blockDim.x) {
+        for (int q = 0; q < wpv; ++q)
+            for (int j = have[q] + tid; j < cap; j += blockDim.x) keys_all[(size_t)q * cap + j] = kNoKey;
+        __syncthreads();
+        block_bitonic_sort(keys_all, wpv * cap);
+        return;
+    }
+    const uint64_t k = tid < total ? keys_all[(size_t)w * cap + (tid - off)] : kNoKey;
+    __syncthreads();
+    keys_all[tid] = k;
+    __syncthreads();
+    int rank = 0;
+    const ulonglong2* k2 = reinterpret_cast<const ulonglong2*>(keys_all);  // (padding counts for no key)
+#pragma unroll 4
+    for (int j = 0; j < ((total + 1) >> 1); ++j) {
+        const ulonglong2 o = k2[j];
+        rank += (o.x < k ? 1 : 0) + (o.y < k ? 1 : 0);
+    }
+    __syncthreads();
+    if (tid < total && rank < n) keys_all[rank] = k;
+    __syncthreads();
+}
+
+// vpet_infer_kernel (L2) with screened draws: the same outputs.
+template <int KINDS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_screen_kernel(InferArgs P) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long long row = blockIdx.x;
+    if (row >= P.V) return;
+    const int F = P.F, n = (int)P.n_acc;
+    const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
+    double2* yw = reinterpret_cast<double2*>(lds);
+    double4* fs = reinterpret_cast<double4*>(yw + F);
+    float4* tab = reinterpret_cast<float4*>(fs + F);
+    uint64_t* keys_all = reinterpret_cast<uint64_t*>(tab + 4 * P.nseg);
+    double* red = reinterpret_cast<double*>(keys_all + (size_t)P.wpv * P.cap);
+    int* flag = reinterpret_cast<int*>(red + kRedStride * P.wpv);
+    ScreenVox* sv = reinterpret_cast<ScreenVox*>(flag + 4 + P.wpv);  // flag[4 + w]: wave w's candidates
+    if (wave == 0) {
+        voxel_curve(P, row, yw, flag);
+        wave_lds_sync();
+        const bool fits = screen_voxel(P, yw, fs, sv);
+        if (lane == 0) flag[1] = fits ? 0 : 1;
+    }
+    __syncthreads();
+    if (*flag == 0) {
+        if (wave == 0) infer_invalid(P, row);
+        return;
+    }
+    bool screened = flag[1] == 0;
+    if (screened) {
+        screen_table(P, fs, tab);
+        ScreenVox S;
+        S.yy = wave_uniform(sv->yy);
+        S.yq = wave_uniform(sv->yq);
+        S.yp = wave_uniform(sv->yp);
+        S.qq = wave_uniform(sv->qq);
+        S.qp = wave_uniform(sv->qp);
+        S.pp = wave_uniform(sv->pp);
+        S.ny = wave_uniform(sv->ny);
+        S.nq = wave_uniform(sv->nq);
+        S.np = wave_uniform(sv->np);
+        S.kap = wave_uniform(sv->kap);
+        __syncthreads();
+        ScreenList list;
+        list.keys = keys_all + (size_t)wave * P.cap;
+        list.n = n;
+        list.cap = P.cap;
+        list.have = list.nbuf = 0;
+        list.tau = __builtin_inff();
+        list.full = false;
+        for (int m = 0; m < P.M; ++m) {
+            const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
+            if constexpr (KINDS != 0)
+                screen_stream<KINDS>(P, S, tab, m, vg, yw, list);
+            else if (kind == KIND_IRR)
+                screen_stream<KIND_IRR>(P, S, tab, m, vg, yw, list);
+            else if (kind == KIND_REV)
+                screen_stream<KIND_REV>(P, S, tab, m, vg, yw, list);
+            else
+                screen_stream<KIND_1TCM>(P, S, tab, m, vg, yw, list);
+        }
+        if (!list.full) list.merge();
+        if (list.full && lane == 0) flag[1] = 1;
+        if (P.wpv > 1) {
+            __syncthreads();
+            screened = flag[1] == 0;
+            if (screened && n > kWave) {
+                // one list for the block before the exact pass
+                for (int j = list.have + lane; j < P.cap; j += kWave) list.keys[j] = kNoKey;
+                __syncthreads();
+                block_bitonic_sort(keys_all, P.wpv * P.cap);
+                int have;
+                ScreenList::prefix(keys_all, P.wpv * P.cap, n, have);
+                const int rounds = (have + (int)blockDim.x - 1) / (int)blockDim.x;
+                for (int q = 0; q < rounds; ++q)
+                    if (q * (int)blockDim.x + wave * kWave < have)
+                        screen_exact<KINDS, 1>(P, vg, yw, keys_all, q * (int)blockDim.x + wave * kWave, have);
+                const int len = 1 << (32 - __builtin_clz((unsigned)(have - 1)));
+                for (int j = have + tid; j < len; j += blockDim.x) keys_all[j] = kNoKey;
+                __syncthreads();
+                block_bitonic_sort(keys_all, len);
+            } else if (screened) {
+                for (int j0 = 0; j0 < list.have; j0 += kWave) screen_exact<KINDS, 1>(P, vg, yw, list.keys, j0, list.have);
+                if (lane == 0) flag[4 + wave] = list.have;
+                __syncthreads();
+                block_rank(keys_all, P.wpv, P.cap, n, flag + 4);
+            }
+        } else if (!list.full) {
+            for (int j0 = 0; j0 < list.have; j0 += 2 * kWave) screen_exact<KINDS, 2>(P, vg, yw, list.keys, j0, list.have);
+            const int len = list.have <= 2 ? 2 : 1 << (32 - __builtin_clz((unsigned)(list.have - 1)));
+            for (int j = list.have + lane; j < len; j += kWave) list.keys[j] = kNoKey;
+            wave_lds_sync();
+            wave_bitonic_sort(list.keys, len);
+            __syncthreads();
+        } else {
+            screened = false;
+        }
+    }
+    if (!screened) {
+        __syncthreads();
+        stream_draws<KINDS, false>(P, vg, yw, keys_all);
+        __syncthreads();
+        if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
+    }
+    infer_outputs(P, row, vg, keys_all, red);
 }
 
 template <int KIND>
@@ -3029,45 +3665,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     MixTab* mix = reinterpret_cast<MixTab*>(reinterpret_cast<unsigned char*>(flag) + 16);
     const int n = (int)P.n_acc;
     if (wave == 0) {
-        const float* y = P.tacs + (size_t)row * F;
-        const cdp FR = (cdp)P.tab.fr;
-        const cip NF = (cip)P.tab.nf;
-        float ymax = -__builtin_inff();
-        int bad = 0;
-        for (int f = lane; f < F; f += kWave) {
-            const float yy = y[f];
-            bad |= !isfinite(yy);
-            ymax = fmaxf(ymax, yy);
-            if (P.weights) {  // caller weights must be finite and >= 0
-                const float wv = P.weights[(size_t)row * F + f];
-                bad |= !(wv >= 0.0f) || !isfinite(wv);
-            }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            ymax = fmaxf(ymax, __shfl_xor(ymax, off, kWave));
-            bad |= __shfl_xor(bad, off, kWave);
-        }
-        const bool valid = !bad && ymax > 0.0f;
-        const double den_floor = P.floor_frac * (double)ymax;
-        for (int f = lane; f < F; f += kWave) {
-            const double nfd = (double)NF[f];
-            const double yy = (double)y[f];
-            double w;
-            if (P.weights) {
-                w = (double)P.weights[(size_t)row * F + f];
-            } else {
-                const double den = yy > den_floor ? yy : den_floor;
-                w = FR[4 * f + 3] / den;
-            }
-            const double sw = sqrt(w);
-            yw[f] = P.l1 ? make_double2(nfd * yy, sw / nfd) : make_double2(sw * yy, sw / nfd);
-        }
-        if (lane == 0) {
-            *flag = valid ? 1 : 0;
+        voxel_curve(P, row, yw, flag);
+        if (lane == 0)
             mix_table(P.prop + (size_t)row * kNetOut, *mix, P.prop_share, P.prop_logscale, P.prop_logvol, P.plo,
                       P.phi);
-        }
     }
     __syncthreads();
     if (*flag == 0) {
@@ -3755,7 +4356,7 @@ int hip_fail(hipError_t e, const char* what) {
 struct HostTab {
     int K = 0, F = 0, k0 = 0, kend = 0;
     double h = 0.0, C0 = 0.0;
-    std::vector<double> C, fr;
+    std::vector<double> C, fr, qa;
     std::vector<int> nf;
 };
 
@@ -3788,19 +4389,24 @@ int make_tables(const float* input_fn, const float* frame_times, vpet_grid g, do
     T.k0 = kf[0];
     T.kend = kf[T.F];
     T.C0 = (double)input_fn[0];
-    std::vector<double> Cn(T.kend + 1), Q(T.kend + 1);
+    std::vector<double> Cn(T.kend + 1), Q(T.kend + 1), Qa(T.kend + 1);
     for (int k = 0; k <= T.kend; ++k) Cn[k] = (double)input_fn[k];
-    Q[0] = 0.0;
-    for (int k = 0; k < T.kend; ++k) Q[k + 1] = Q[k] + 0.5 * T.h * (Cn[k] + Cn[k + 1]);
+    Q[0] = Qa[0] = 0.0;
+    for (int k = 0; k < T.kend; ++k) {
+        Q[k + 1] = Q[k] + 0.5 * T.h * (Cn[k] + Cn[k + 1]);
+        Qa[k + 1] = Qa[k] + 0.5 * T.h * (std::fabs(Cn[k]) + std::fabs(Cn[k + 1]));
+    }
     T.C.assign(Cn.begin(), Cn.begin() + T.kend + 1);
     T.fr.assign(4 * (size_t)T.F, 0.0);
+    T.qa.assign(T.F, 0.0);
     T.nf.assign(T.F, 0);
     for (int f = 0; f < T.F; ++f) {
         const int a = kf[f], b = kf[f + 1];
-        double ss = 0.5 * (Q[a] + Q[b]), pp = 0.5 * (Cn[a] + Cn[b]), rr = 0.0;
+        double ss = 0.5 * (Q[a] + Q[b]), pp = 0.5 * (Cn[a] + Cn[b]), rr = 0.0, qa = 0.5 * (Qa[a] + Qa[b]);
         for (int k = a + 1; k < b; ++k) {
             ss += Q[k];
             pp += Cn[k];
+            qa += Qa[k];
         }
         for (int k = a; k < b; ++k) rr += Cn[k];
         const double dt = (double)(b - a) * T.h;
@@ -3809,6 +4415,7 @@ int make_tables(const float* input_fn, const float* frame_times, vpet_grid g, do
         T.fr[4 * f + 1] = pp;
         T.fr[4 * f + 2] = rr;
         T.fr[4 * f + 3] = dt * std::exp(-lambda * tmid);
+        T.qa[f] = qa;
         T.nf[f] = b - a;
     }
     return VPET_OK;
@@ -3905,16 +4512,18 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Uploads T into a slot and returns device pointers; the caller holds ctx.mu
 // until it has recorded ctx.ev[slot] after its launch.
 // Byte layout of the tables in device memory: C (FP64), the per-frame sums
-// (FP64) and the frame lengths in nodes (int32), each 256-byte aligned.
+// (FP64), the frame lengths in nodes (int32) and the per-frame sums of the
+// running integral of |C| (FP64), each 256-byte aligned.
 struct TabLayout {
-    size_t offC, offF, offN, bytes;
+    size_t offC, offF, offN, offA, bytes;
 };
 TabLayout tab_layout(const HostTab& T) {
     TabLayout L;
     L.offC = 0;
     L.offF = align256(L.offC + sizeof(double) * T.C.size());
     L.offN = align256(L.offF + sizeof(double) * T.fr.size());
-    L.bytes = align256(L.offN + sizeof(int) * T.nf.size());
+    L.offA = align256(L.offN + sizeof(int) * T.nf.size());
+    L.bytes = align256(L.offA + sizeof(double) * T.qa.size());
     return L;
 }
 
@@ -3942,11 +4551,13 @@ int upload_tables(DevCtx& ctx, const HostTab& T, hipStream_t st, Tab& tab, int& 
     if (!T.C.empty()) std::memcpy(hs + offC, T.C.data(), sizeof(double) * T.C.size());
     std::memcpy(hs + offF, T.fr.data(), sizeof(double) * T.fr.size());
     std::memcpy(hs + offN, T.nf.data(), sizeof(int) * T.nf.size());
+    if (!T.qa.empty()) std::memcpy(hs + L.offA, T.qa.data(), sizeof(double) * T.qa.size());
     e = hipMemcpyAsync(ds, hs, bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(tables)");
     tab.C = reinterpret_cast<const double*>(ds + offC);
     tab.fr = reinterpret_cast<const double*>(ds + offF);
     tab.nf = reinterpret_cast<const int*>(ds + offN);
+    tab.qa = reinterpret_cast<const double*>(ds + L.offA);
     return VPET_OK;
 }
 
@@ -4061,9 +4672,11 @@ int stage_tables_noalloc(const HostTab& T, hipStream_t st, Tab& tab) {
         return rc;
     if ((rc = stage_bytes(T.fr.data(), sizeof(double) * T.fr.size(), base + L.offF, st)) != VPET_OK) return rc;
     if ((rc = stage_bytes(T.nf.data(), sizeof(int) * T.nf.size(), base + L.offN, st)) != VPET_OK) return rc;
+    if ((rc = stage_bytes(T.qa.data(), sizeof(double) * T.qa.size(), base + L.offA, st)) != VPET_OK) return rc;
     tab.C = reinterpret_cast<const double*>(base + L.offC);
     tab.fr = reinterpret_cast<const double*>(base + L.offF);
     tab.nf = reinterpret_cast<const int*>(base + L.offN);
+    tab.qa = reinterpret_cast<const double*>(base + L.offA);
     return VPET_OK;
 }
 
@@ -4112,6 +4725,65 @@ int pow2_at_least(int x) {
 int select_key_buffer(int cap, int n, bool weighted) {
     const int want = pow2_at_least(8 * n) <= 1024 ? 8 * n : (weighted ? 6 * n : 5 * n + 1);
     return std::min(cap, std::max(512, pow2_at_least(want)));
+}
+
+// Whether a call screens its draws (vpet_infer_screen_kernel), and its shapes:
+// an L2 call with a one-exponential model whose draws per voxel repay the
+// voxel's table and the segment table's launch, whose draw indices fit a key,
+// and whose segments and candidates fit the table buffer and the LDS.
+// Measured (n = 20, 30 frames / 50 min, unscreened -> screened): 16,384 voxels
+// x 1024 draws 423 -> 262 us, x 6000 draws 2090 -> 518 us; 1024 voxels x 1024
+// draws 61 -> 68 us, x 2000 draws 83 -> 72 us; 64 voxels x 2000 draws 64.4 ->
+// 64.6 us, x 6000 draws 113 -> 77 us; one voxel x 2000 draws 57 -> 60 us, x
+// 6000 draws 106 -> 72 us.
+int64_t screen_min_draws(int64_t n_voxels) { return n_voxels >= 2048 ? 1024 : (n_voxels >= 512 ? 2000 : 2600); }
+struct ScreenPlan {
+    bool use = false;
+    int nseg = 0, cap = 0;
+    unsigned seg0 = 0;
+    float b0 = 0.0f;
+    size_t lds = 0;
+};
+ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, int M, int64_t n_draws, int n_acc,
+                       const vpet_abc_opts& o, int64_t n_voxels, int wpv) {
+    ScreenPlan S;
+    const int64_t total = (int64_t)M * n_draws;
+    if (o.distance != 0 || o.proposal || total < screen_min_draws(n_voxels) || total > kScrMaxDraws) return S;
+    float lo = INFINITY, hi = 0.0f;  // the range of beta as the kernel forms it (fp32, monotonic roundings)
+    bool any = false;
+    for (int m = 0; m < M; ++m) {
+        const ModelDev& md = P.md[m];
+        if (kinds[m] != KIND_1TCM && kinds[m] != KIND_IRR) continue;
+        any = true;
+        if (kinds[m] == KIND_IRR && !(md.lo[1] + md.lo[2] > 1e-20f)) return S;  // 1 / beta
+        float l = md.lo[1], h = std::fmaf(md.wid[1], 1.0f, md.lo[1]);
+        if (kinds[m] == KIND_IRR) {
+            l += md.lo[2];
+            h += std::fmaf(md.wid[2], 1.0f, md.lo[2]);
+        }
+        lo = std::fmin(lo, l);
+        hi = std::fmax(hi, h);
+    }
+    if (!any || !(hi < 1e6f)) return S;
+    int ex;
+    const double t_end = (double)T.kend * T.h;
+    (void)std::frexp(0.5 / t_end, &ex);
+    S.b0 = std::ldexp(1.0f, ex - 1);  // the power of two at or below 1 / (2 T)
+    auto seg_of = [&](float beta) {
+        const float u = beta + S.b0;
+        uint32_t b;
+        std::memcpy(&b, &u, sizeof b);
+        return b >> kScrShift;
+    };
+    S.seg0 = seg_of(lo);
+    S.nseg = (int)(seg_of(hi) - S.seg0) + 1;
+    if (S.nseg > kScrMaxSeg || !(S.b0 > 1e-20f)) return S;
+    if (tab_layout(T).bytes + sizeof(float) * 8 * (size_t)S.nseg * T.F > kSlotBytes) return S;
+    S.cap = pow2_at_least(n_acc + n_acc / 4 + 2 * kWave);
+    S.lds = 48 * (size_t)T.F + 64 * (size_t)S.nseg + sizeof(uint64_t) * (size_t)wpv * S.cap +
+            sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv + sizeof(ScreenVox);
+    S.use = S.lds <= (size_t)kLdsLimit;
+    return S;
 }
 
 }  // namespace
@@ -4309,7 +4981,7 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
     if (!tacs || !out_moments || !out_model_prob)
         return fail(VPET_E_ARG, "tacs, out_moments and out_model_prob must not be NULL");
 
-    const int cap = pow2_at_least((int)n_acc + 2 * kWave);
+    int cap = pow2_at_least((int)n_acc + 2 * kWave);
     int wpv = o.waves_per_voxel;
     if (wpv == 0) {
         wpv = 1;
@@ -4321,6 +4993,15 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
     };
     while (wpv > 1 && lds_for(wpv) > (size_t)kLdsLimit) wpv >>= 1;
     if (lds_for(wpv) > (size_t)kLdsLimit) return fail(VPET_E_LIMIT, "selection buffer exceeds LDS");
+    size_t lds = lds_for(wpv);
+    const ScreenPlan scr = screen_plan(T, P, kinds, M, n_draws, (int)n_acc, o, n_voxels, wpv);
+    if (scr.use) {
+        cap = scr.cap;
+        lds = scr.lds;
+        P.nseg = scr.nseg;
+        P.seg0 = scr.seg0;
+        P.b0 = scr.b0;
+    }
 
     P.weights = o.weights;
     P.C0 = T.C0;
@@ -4353,7 +5034,13 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         lock = std::unique_lock<std::mutex>(ctx->mu);
         if ((rc = upload_tables(*ctx, T, st, P.tab, slot)) != VPET_OK) return rc;
     }
-    const size_t lds = lds_for(wpv);
+    if (scr.use) {
+        // the segment polynomials follow the call's tables in the same device buffer
+        float* out = reinterpret_cast<float*>(const_cast<char*>(reinterpret_cast<const char*>(P.tab.C)) + tab_layout(T).bytes);
+        hipLaunchKernelGGL(vpet_screen_table_kernel, dim3((unsigned)((scr.nseg + 15) / 16)), dim3(64), 0, st, P.tab,
+                           T.C0, T.h, T.F, T.k0, scr.nseg, scr.seg0, scr.b0, out);
+        P.scr = out;
+    }
     const long long chunk = 1LL << 30;
     for (long long base = 0; base < n_voxels; base += chunk) {
         InferArgs Q = P;
@@ -4370,8 +5057,12 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         Q.out_ess = o.out_ess ? o.out_ess + base : nullptr;
         Q.below = o.accept_below ? o.accept_below + base : nullptr;
         const dim3 grid((unsigned)Q.V), block(kWave * wpv);
-        const int sel = o.proposal ? -1 - o.distance : (M == 1 ? kinds[0] : 0) * 2 + (o.distance == 1 ? 1 : 0);
+        const int one = M == 1 ? kinds[0] : 0;
+        const int sel = o.proposal ? -1 - o.distance : (scr.use ? -8 - one : one * 2 + (o.distance == 1 ? 1 : 0));
         switch (sel) {
+            case -8 - KIND_IRR: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_IRR>), grid, block, lds, st, Q); break;
+            case -8 - KIND_1TCM: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_1TCM>), grid, block, lds, st, Q); break;
+            case -8: hipLaunchKernelGGL((vpet_infer_screen_kernel<0>), grid, block, lds, st, Q); break;
             case -1: hipLaunchKernelGGL((vpet_infer_is_kernel<false>), grid, block, lds, st, Q); break;
             case -2: hipLaunchKernelGGL((vpet_infer_is_kernel<true>), grid, block, lds, st, Q); break;
             case 2 * KIND_IRR: hipLaunchKernelGGL((vpet_infer_kernel<KIND_IRR, false>), grid, block, lds, st, Q); break;

@@ -1,0 +1,81 @@
+"""Screened draws of the per-voxel path against the FP64 oracle, at the sizes
+and inputs where the screen can go wrong: the ends of its range of draw counts,
+tile and list edges, one and several wavefronts per voxel, rates at zero and
+beyond the short series, signed input functions, ties everywhere and curves
+outside the fp32 range (both take the unscreened path).  Tolerances are those
+of test_gpu_parity: accepted sets equal up to draws within 1e-5 of the
+threshold, means within 1e-5.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - CPU-only hosts
+    pytest.skip("no HIP device", allow_module_level=True)
+
+from test_gpu_parity import _check_infer, _inputs  # noqa: E402
+
+T1, IRR, REV = W.M_1TCM, W.M_2TCM_IRR, W.M_2TCM_REV
+
+
+@pytest.mark.parametrize("models,n_draws,n,wpv", [
+    ((IRR,), 2599, 20, 0), ((IRR,), 2600, 20, 1), ((IRR,), 2601, 1, 4), ((IRR,), 5000, 64, 2), ((IRR,), 5000, 65, 4),
+    ((IRR,), 5003, 500, 1), ((IRR,), 3000, 3000, 1), ((T1,), 4097, 100, 1), ((T1,), 3072, 63, 4),
+    ((T1, IRR), 2500, 100, 2), ((T1, IRR, REV), 3001, 200, 4), ((IRR, REV), 1500, 30, 1), ((REV,), 3001, 129, 2),
+    ((REV,), 2600, 40, 4)])
+def test_counts(models, n_draws, n, wpv):
+    import oracle as ora
+    ft, cp, y = _inputs(n_vox=9, model=models[-1], sched=W.SCHED_30x50)
+    total = n_draws * len(models)
+    _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, (n + 0.5) / total if n < total else 1.0,
+                 11, wpv=wpv, voxel_offset=5)
+
+
+@pytest.mark.parametrize("case", ["zero_rate", "fast", "signed", "offset", "ties", "tiny_weights", "huge_weights",
+                                  "low_counts", "one_frame", "fixed_rate", "rev_fast", "rev_close", "rev_no_k4"])
+def test_inputs(case):
+    import oracle as ora
+    model = T1 if case in ("zero_rate", "one_frame") else (REV if case.startswith("rev") else IRR)
+    sched = W.SCHED_30x50
+    ft, cp, y = _inputs(n_vox=12, model=model, sched=sched)
+    boxes = W.box_array([model])
+    weights, n_draws, p = None, 4000, 0.02
+    if case == "zero_rate":
+        boxes[0, 1] = (0.0, 0.2)
+    elif case == "fast":  # beta h up to 1: beyond the short series
+        boxes[0, 1] = (0.5, 4.0)
+        boxes[0, 2] = (0.2, 1.0)
+    elif case == "signed":
+        cp = (cp * np.cos(0.7 * np.arange(cp.size))).astype(np.float32)
+    elif case == "offset":
+        ft = (ft + np.float32(1.4)).astype(np.float32)[:20]
+        y = np.ascontiguousarray(y[:, :19])
+        cp = np.concatenate([cp, cp[-1:] * np.ones(10, np.float32)])
+    elif case == "ties":
+        boxes[0, :, 1] = boxes[0, :, 0]
+        boxes[0, 0] = boxes[0, 1] = (0.3, 0.3)
+        boxes[0, 2] = (0.1, 0.1)
+    elif case in ("tiny_weights", "huge_weights"):
+        weights = np.full(y.shape, 1e-18 if case == "tiny_weights" else 1e18, np.float32)
+        weights[::2] *= np.float32(1e-9 if case == "tiny_weights" else 1e9)
+    elif case == "low_counts":
+        y = (y * 1e-4).astype(np.float32)
+    elif case == "one_frame":
+        ft, y = ft[[0, 24]], np.ascontiguousarray(y[:, 20:21])
+    elif case == "fixed_rate":
+        boxes[0, 1] = (0.2, 0.2)
+        boxes[0, 2] = (0.05, 0.05)
+    elif case == "rev_fast":
+        boxes[0, 1] = (0.5, 4.0)
+        boxes[0, 3] = (0.0, 2.0)
+    elif case == "rev_close":  # nearly equal eigenvalues
+        boxes[0, 1] = (0.05, 0.06)
+        boxes[0, 2] = (0.0005, 0.001)
+        boxes[0, 3] = (0.05, 0.06)
+    elif case == "rev_no_k4":
+        boxes[0, 3] = (0.0, 0.0)
+    _check_infer(ora, y, ft, cp, [model], boxes, n_draws, p, 3, weights=weights)
