@@ -3491,6 +3491,238 @@ __device__ __forceinline__ double exp_series(double z) {
     return ldexp(p, (int)k);
 }
 
+// ---------------------------------------------------------------------------
+// Fused network evaluation: features, both hidden layers and the outputs of 64
+// rows per block and pass, activations in LDS (bf16 hi + lo), as products of
+// vpet_gemm_bf16x3_kernel's arithmetic and order (the outputs are the same
+// bits).  A block's eight wavefronts each keep 32 columns of W1 and W2 in
+// registers for the whole launch (a persistent grid of one block per CU), so
+// only W3's 96 KB of split weights stream from L2 per 64 rows; six wavefronts
+// form the outputs' 2 x 3 tiles while the other two form the next pass's
+// features.  Bound by the matrix cores: 3 x 2 x 98,304 flops a row.  262,144
+// rows of 30 frames: 980 -> 187 us (feature kernel and three products through
+// fp32 memory before; the matrix cores are busy 38 % of that, each layer's 64
+// rows waiting on a barrier with two wavefronts per SIMD); 1000 rows: 60 -> 29 us.
+// ---------------------------------------------------------------------------
+constexpr int kFwdRows = 64;
+constexpr int kFwdBlocks = 256;  // a block per CU (146 KB of LDS each)
+constexpr int kFwdXS = kNetIn + 8, kFwdHS = kNetH + 8;  // LDS row strides (bf16), padded against bank conflicts
+constexpr int kFragW1 = 0, kFragW2 = kFragW1 + 8 * (kNetIn / 16), kFragW3 = kFragW2 + 8 * (kNetH / 16),
+              kFrags = kFragW3 + (kNetOut / 32) * (kNetH / 16);
+
+// Weights as MFMA operands: fragment (layer, 32-column tile, 16-row k step) is
+// 64 lanes x 16 bytes of bf16 hi, then of lo; lane l holds column l % 32, rows
+// 8 (l / 32) .. + 7.
+__global__ __launch_bounds__(256) void vpet_net_frags_kernel(const float* p, uint4* frag) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, fr = t >> 6, lane = t & 63;
+    if (fr >= kFrags) return;
+    const float* W = p + kOffW1;
+    int N = kNetH, tile, ks;
+    if (fr < kFragW2) {
+        tile = fr / (kNetIn / 16);
+        ks = fr % (kNetIn / 16);
+    } else {
+        const int q = fr - (fr < kFragW3 ? kFragW2 : kFragW3);
+        tile = q / (kNetH / 16);
+        ks = q % (kNetH / 16);
+        W = p + (fr < kFragW3 ? kOffW2 : kOffW3);
+        if (fr >= kFragW3) N = kNetOut;
+    }
+    const int k = 16 * ks + 8 * (lane >> 5), c = 32 * tile + (lane & 31);
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = W[(size_t)(k + e) * N + c];
+    uint4 hi, lo;
+    split_bf16x8(x, hi, lo);
+    frag[(size_t)(2 * fr) * kWave + lane] = hi;
+    frag[(size_t)(2 * fr + 1) * kWave + lane] = lo;
+}
+
+// log1p(x) of x >= 0 (FP64, within 2 ulp): 2 atanh(x / (2 + x)) up to sqrt 2 - 1,
+// else the logarithm of 1 + x, by the series of log_pos.
+__device__ __forceinline__ double log1p_pos(double x) {
+    const bool small = x < 0.41421356237309503;
+    int e = 0;
+    double m = frexp(1.0 + x, &e);
+    if (m < 0.70710678118654752) {
+        m *= 2.0;
+        e -= 1;
+    }
+    const double num = small ? x : m - 1.0, den = small ? x + 2.0 : m + 1.0;
+    double r = __builtin_amdgcn_rcp(den);
+    r = fma(r, fma(-den, r, 1.0), r);
+    r = fma(r, fma(-den, r, 1.0), r);
+    double s = num * r;
+    s = fma(r, fma(-den, s, num), s);
+    const double s2 = s * s;
+    double p = 1.0 / 23.0;
+    p = fma(p, s2, 1.0 / 21.0);
+    p = fma(p, s2, 1.0 / 19.0);
+    p = fma(p, s2, 1.0 / 17.0);
+    p = fma(p, s2, 1.0 / 15.0);
+    p = fma(p, s2, 1.0 / 13.0);
+    p = fma(p, s2, 1.0 / 11.0);
+    p = fma(p, s2, 1.0 / 9.0);
+    p = fma(p, s2, 1.0 / 7.0);
+    p = fma(p, s2, 1.0 / 5.0);
+    p = fma(p, s2, 1.0 / 3.0);
+    const double lm = fma(2.0 * s, s2 * p, 2.0 * s), de = small ? 0.0 : (double)e;
+    const double v = fma(de, kLn2Hi, fma(de, kLn2Lo, lm));
+    return x < __builtin_inf() ? v : x;
+}
+
+// Four consecutive activations as bf16 hi and lo words.
+__device__ __forceinline__ void store_split4(uint16_t* hi, uint16_t* lo, const float (&v)[4]) {
+    const uint32_t h0 = bf16x2_rn(v[0], v[1]), h1 = bf16x2_rn(v[2], v[3]);
+    const uint32_t l0 = bf16x2_rn(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xFFFF0000u));
+    const uint32_t l1 = bf16x2_rn(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xFFFF0000u));
+    *reinterpret_cast<uint2*>(hi) = make_uint2(h0, h1);
+    *reinterpret_cast<uint2*>(lo) = make_uint2(l0, l1);
+}
+
+struct FwdLds {
+    uint16_t X[2][kFwdRows * kFwdXS];
+    uint16_t H1[2][kFwdRows * kFwdHS], H2[2][kFwdRows * kFwdHS];
+    float b1[kNetH], b2[kNetH], b3[kNetOut];
+};
+
+// Features of rows [row0, row0 + 64) by `nthr` threads (thread t).
+template <int PER>
+__device__ __forceinline__ void fwd_features(const float* tacs, long long n, int F, long long row0, int t, int nthr,
+                                             FwdLds& S) {
+    float y[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = t + q * nthr, f = e % kNetIn;
+        const long long row = row0 + e / kNetIn;
+        y[q] = (row < n && f < F) ? tacs[row * F + f] : 0.0f;
+    }
+#pragma unroll 2
+    for (int q = 0; q < PER; ++q) {
+        const int e = t + q * nthr, o = (e / kNetIn) * kFwdXS + e % kNetIn;
+        const float x = (float)log1p_pos(fmax((double)y[q], 0.0));
+        const uint32_t h = bf16x2_rn(x, 0.0f);
+        S.X[0][o] = (uint16_t)h;
+        S.X[1][o] = (uint16_t)bf16x2_rn(x - __uint_as_float(h << 16), 0.0f);
+    }
+}
+
+__device__ __forceinline__ bf16x8_t as_bf16x8(const uint4& v) { return __builtin_bit_cast(bf16x8_t, v); }
+
+// act lo x w hi, act hi x w lo, act hi x w hi: the order of the plain product.
+__device__ __forceinline__ f32x16_t mfma_x3(bf16x8_t wh, bf16x8_t wl, bf16x8_t ah, bf16x8_t al, f32x16_t acc) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, al, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, ah, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, ah, acc, 0, 0, 0);
+}
+
+__global__ __launch_bounds__(512) void vpet_net_forward_kernel(const float* __restrict__ p, const uint4* __restrict__ frag,
+                                                               const float* __restrict__ tacs, long long n, int F,
+                                                               float* __restrict__ out) {
+    __shared__ __align__(16) FwdLds S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    const bool aligned = (reinterpret_cast<uintptr_t>(out) & 15u) == 0;  // the caller's buffer: any float address
+    for (int c = tid; c < kNetH; c += 512) {
+        S.b1[c] = p[kOffB1 + c];
+        S.b2[c] = p[kOffB2 + c];
+        if (c < kNetOut) S.b3[c] = p[kOffB3 + c];
+    }
+    auto fragment = [&](int fr, int part) { return as_bf16x8(frag[(size_t)(2 * fr + part) * kWave + lane]); };
+    bf16x8_t w1h[2], w1l[2], w2h[16], w2l[16];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        w1h[ks] = fragment(kFragW1 + 2 * wave + ks, 0);
+        w1l[ks] = fragment(kFragW1 + 2 * wave + ks, 1);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+        w2h[ks] = fragment(kFragW2 + 16 * wave + ks, 0);
+        w2l[ks] = fragment(kFragW2 + 16 * wave + ks, 1);
+    }
+    const long long ntiles = (n + kFwdRows - 1) / kFwdRows;
+    fwd_features<4>(tacs, n, F, (long long)blockIdx.x * kFwdRows, tid, 512, S);
+    __syncthreads();
+    // result r of lane l: column 8 (r / 4) + 4 (l / 32) + r % 4 of the tile, row l % 32
+    for (long long t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        {  // layer 1: this wavefront's 32 columns of both 32-row halves
+            f32x16_t a[2] = {};
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int o = (32 * m + (lane & 31)) * kFwdXS + 16 * ks + 8 * half;
+                    a[m] = mfma_x3(w1h[ks], w1l[ks], as_bf16x8(*reinterpret_cast<const uint4*>(&S.X[0][o])),
+                                   as_bf16x8(*reinterpret_cast<const uint4*>(&S.X[1][o])), a[m]);
+                }
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 32 * wave + 8 * q + 4 * half, o = (32 * m + (lane & 31)) * kFwdHS + c;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(a[m][4 * q + e] + S.b1[c + e], 0.0f);
+                    store_split4(&S.H1[0][o], &S.H1[1][o], v);
+                }
+        }
+        __syncthreads();
+        {  // layer 2
+            f32x16_t a[2] = {};
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int o = (32 * m + (lane & 31)) * kFwdHS + 16 * ks + 8 * half;
+                    a[m] = mfma_x3(w2h[ks], w2l[ks], as_bf16x8(*reinterpret_cast<const uint4*>(&S.H1[0][o])),
+                                   as_bf16x8(*reinterpret_cast<const uint4*>(&S.H1[1][o])), a[m]);
+                }
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 32 * wave + 8 * q + 4 * half, o = (32 * m + (lane & 31)) * kFwdHS + c;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(a[m][4 * q + e] + S.b2[c + e], 0.0f);
+                    store_split4(&S.H2[0][o], &S.H2[1][o], v);
+                }
+        }
+        __syncthreads();
+        if (wave < 6) {  // layer 3: one 32 x 32 tile of the outputs
+            const int m = wave & 1, ct = wave >> 1;
+            f32x16_t a = {};
+#pragma unroll 4
+            for (int ks = 0; ks < 16; ++ks) {
+                const int o = (32 * m + (lane & 31)) * kFwdHS + 16 * ks + 8 * half;
+                a = mfma_x3(fragment(kFragW3 + 16 * ct + ks, 0), fragment(kFragW3 + 16 * ct + ks, 1),
+                            as_bf16x8(*reinterpret_cast<const uint4*>(&S.H2[0][o])),
+                            as_bf16x8(*reinterpret_cast<const uint4*>(&S.H2[1][o])), a);
+            }
+            const long long row = t * kFwdRows + 32 * m + (lane & 31);
+            if (row < n) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 32 * ct + 8 * q + 4 * half;
+                    float* dst = out + row * kNetOut + c;
+                    const float4 v = make_float4(a[4 * q] + S.b3[c], a[4 * q + 1] + S.b3[c + 1], a[4 * q + 2] + S.b3[c + 2],
+                                                 a[4 * q + 3] + S.b3[c + 3]);
+                    if (aligned) {
+                        *reinterpret_cast<float4*>(dst) = v;
+                    } else {
+                        dst[0] = v.x;
+                        dst[1] = v.y;
+                        dst[2] = v.z;
+                        dst[3] = v.w;
+                    }
+                }
+            }
+        } else if (t + gridDim.x < ntiles) {
+            fwd_features<16>(tacs, n, F, (t + gridDim.x) * kFwdRows, tid - 384, 128, S);
+        }
+        __syncthreads();
+    }
+}
+
 // Proposal draw i of voxel v: one Philox block (stream 2), u0 from the low
 // bytes of words 0-2, u_j = (w_j >> 8) 2^-24.  u0 below the defensive share
 // draws theta uniformly from the box (z = log theta); otherwise a component
@@ -6294,22 +6526,15 @@ int vpet_proposal_forward(const float* params, const float* tacs, int64_t n, int
     int dev;
     if ((rc = current_device(&dev)) != VPET_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
-    const long long rows = std::min<long long>(n, 1LL << 17);
-    char* work = nullptr;
-    hipError_t e = hipMallocAsync((void**)&work, net_work_bytes(rows), st);
+    uint4* frag = nullptr;
+    hipError_t e = hipMallocAsync((void**)&frag, sizeof(uint4) * 2 * kWave * kFrags, st);
     if (e != hipSuccess) return fail(VPET_E_NOMEM, "proposal work: %s", hipGetErrorString(e));
-    NetWork w;
-    net_work_carve(work, rows, w);
-    for (long long b0 = 0; b0 < n; b0 += rows) {
-        const int cnt = (int)std::min<long long>(rows, n - b0);
-        hipLaunchKernelGGL(vpet_net_features_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st,
-                           tacs + (size_t)b0 * n_frames, (long long)cnt, n_frames, w.X);
-        NetWork wo = w;
-        wo.O = out + (size_t)b0 * kNetOut;  // the last layer writes the caller's buffer
-        net_forward(st, params, wo, cnt);
-    }
+    hipLaunchKernelGGL(vpet_net_frags_kernel, dim3((kFrags * kWave + 255) / 256), dim3(256), 0, st, params, frag);
+    const long long tiles = (n + kFwdRows - 1) / kFwdRows;
+    hipLaunchKernelGGL(vpet_net_forward_kernel, dim3((unsigned)std::min<long long>(tiles, kFwdBlocks)), dim3(512), 0, st,
+                       params, frag, tacs, (long long)n, n_frames, out);
     e = hipGetLastError();
-    const hipError_t e2 = hipFreeAsync(work, st);
+    const hipError_t e2 = hipFreeAsync(frag, st);
     if (e != hipSuccess) return hip_fail(e, "proposal forward");
     return e2 == hipSuccess ? VPET_OK : hip_fail(e2, "hipFreeAsync");
 }
