@@ -129,6 +129,11 @@ struct InferArgs {
     int nseg;
     unsigned seg0;         // first segment (float bits of beta + b0, shifted)
     float b0;
+    // two exponentials: polynomials [F][kScrDeg] of the responses in s = a1 a1scale - 1
+    const double* poly;
+    float a1scale, a1hi, a2hi;
+    int nseg2;             // segments of a2, from seg2
+    unsigned seg2;
 };
 
 // ---------------------------------------------------------------------------
@@ -624,6 +629,26 @@ __device__ void block_bitonic_sort(uint64_t* a, int len) {
     }
 }
 
+// The same for a whose consecutive runs of `run` keys are each sorted (len / run
+// and run powers of two): the runs are merged pairwise, the first stage of a
+// merge comparing with the mirrored position.
+__device__ void block_merge_runs(uint64_t* a, int run, int len) {
+    for (int kk = 2 * run; kk <= len; kk <<= 1) {
+        for (int j = kk >> 1; j > 0; j >>= 1) {
+            for (int p = threadIdx.x; p < (len >> 1); p += blockDim.x) {
+                int i = ((p & ~(j - 1)) << 1) | (p & (j - 1)), l = i | j;
+                if (j == (kk >> 1)) l = (i & ~(kk - 1)) + kk - 1 - (i & (kk - 1));
+                const uint64_t x = a[i], y = a[l];
+                if (x > y) {
+                    a[i] = y;
+                    a[l] = x;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // The block's n smallest keys after every wavefront has merged its own list
 // (wave w's n best, sorted, at keys_all[w cap ..]): they are among the waves'
 // first n keys, so for a small n those are gathered into wpv pow2(n)
@@ -1089,36 +1114,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // (16 per octave), after which a draw costs about 100 fp32 instructions
 // instead of the 600 of its FP64 recursion over every grid step.
 //
-// The screen only rules draws out.  With err bounding |d~ - d| (below), every
-// draw whose lower bound d~ - err exceeds the n-th smallest upper bound
-// d~ + err seen so far cannot be among the n closest; the others (about 1.1 n
-// at the end) get the FP64 recursion of the streaming kernel, so the accepted
-// set, its keys and the outputs are that kernel's.  A voxel whose candidates
-// do not fit (ties everywhere, a curve outside the fp32 range) takes that
-// kernel's path.  Bound by the vector ALU's issue rate, as that kernel is:
-// 16,384 voxels x 100k draws (30 frames, 250 steps) 31.0 -> 4.5 ms, 1024 voxels
-// x 2000 draws 83 -> 70 us.
+// The reversible 2TCM has two exponentials, x = A1 e(a1) + A2 e(a2) + v p with
+// A1 + A2 = (1 - vB) K1 and rates a1 <= min(k2, k4) <= max(k2, k3 + k4) <= a2.
+// Its one function of two variables, 2 sum w e(a1) e(a2), is a polynomial of
+// degree 11 in a1 (e_f interpolated at 12 Chebyshev nodes of a1's range, the
+// same for every voxel) whose coefficients are functions of a2, tabulated as
+// cubics like the others.
 //
-// Error bound.  Let Y, Q, Qa, P be the vectors s y, s q, s qa, s p (s =
-// sqrt(w), qa the frame averages of the running integral of |C|) and |e_f^(k)
-// u^k| <= max_t (u t)^k e^{-u t} e^{b0 t} qa_f.  b0 <= 1/(2 T) (T = end of the
-// grid) and k = 4: 4.69 e^0.5 qa_f, and 4.69 e qa_f^2 for e_f^2.  A segment has
-// half-width <= u/32 and the cubic interpolates at its Chebyshev nodes, so its
-// error is at most (1/32)^4/192 = 5.0e-9 times that: 3.9e-8 qa_f and 6.4e-8
-// qa_f^2, which moves d by at most 7.7e-8 A |Qa| m with m = |Y| + (A + B) |Qa| +
-// v |P|.  Forming u in fp32 (two roundings, 2^-23 u) moves e_f by at most 2^-23
-// e^-1 e^0.5 qa_f = 7.3e-8 qa_f, d by 14.6e-8 A |Qa| m.  Together 2.3e-7 A |Qa| m;
-// kScrEta = 2.6e-7 covers the fp32 rounding of the polynomials' higher
-// coefficients.  The rest are fp32 roundings relative to the sum of the
-// magnitudes of the terms of d, which Cauchy-Schwarz bounds by 4 T, T = yy +
-// A^2 ee + B^2 qq + v^2 pp: 16 roundings of a term (2^-24 each) and the relative
-// error of A and B (5 roundings and the hardware reciprocal, 4.2e-7, acting as
-// 2 sqrt(d) |dx| <= 2 sqrt(4 T) 4.2e-7 sqrt(3 T)) add up to 3.8e-6 T + 2.9e-6 T;
-// kScrEps = 9e-6.
+// The screen only rules draws out.  With d~ the quadratic form at the fp32
+// coefficients, |d~ - d'| <= err for d' the distance of the curve x' at those
+// coefficients and |s (x' - x)| <= rho (below), so (sqrt(d~ - err) - rho)^2 <= d
+// <= (sqrt(d~ + err) + rho)^2.  A draw whose lower bound exceeds the n-th
+// smallest upper bound seen so far cannot be among the n closest; the others
+// (about 1.05 n at the end) get the FP64 recursion of the streaming kernel, so
+// the accepted set, its keys and the outputs are that kernel's.  A voxel whose
+// candidates do not fit (ties everywhere, a curve outside the fp32 range)
+// takes that kernel's path.  Bound by the vector ALU's issue rate, as that
+// kernel is (111 vector instructions a one-exponential draw, 235 a two-exponential
+// one, whose 19 LDS reads a draw weigh as much): 16,384 voxels x 100k draws (30
+// frames, 250 steps) 31.0 -> 4.6 ms, 1024 voxels x 2000 draws 83 -> 72 us, 5003
+// voxels x 20k draws of each 2TCM 6.55 -> 1.99 ms.
+//
+// Error bounds.  Let Y, Q, Qa, P be the vectors s y, s q, s qa, s p (s =
+// sqrt(w), qa the frame averages of the running integral of |C|), W = (1 - vB)
+// K1 (= A + B, A1 + A2), m = |Y| + W |Qa| + v |P|, eps = 2^-24.
+// Tables: |e_f^(k) u^k| <= max_t (u t)^k e^{-u t} e^{b0 t} qa_f, b0 <= 1/(2 T) (T
+// = end of the grid); k = 4: 4.69 e^0.5 qa_f, and 4.69 e qa_f^2 for e_f^2.  A
+// segment has half-width <= u/32 and its cubic interpolates at the Chebyshev
+// nodes: error <= (1/32)^4/192 = 5.0e-9 times that, 3.9e-8 qa_f and 6.4e-8
+// qa_f^2, which moves d' by at most 7.7e-8 A |Qa| m (A = W for two
+// exponentials).  The polynomial in a1 has error <= 7.5e-8 qa_f (4 times the tail of
+// the Bessel series I_k(3) e^-3, k >= 12, for (a1's range) T <= 6): at most 3.8e-8
+// W^2 |Qa|^2 since 2 A1 A2 <= W^2 / 2, and its fp32 evaluation 20 eps 2 A1 |Qa| A2
+// |E2| <= 1.2e-7 A1^2 |Qa|^2 + 1.2e-5 A2^2 ee.
+// Roundings: the terms of d~ sum to at most 4 T, T = yy + sum A^2 ee + v^2 pp (+
+// B^2 qq); 16 roundings of a term, 3.8e-6 T.
+// So err = kScrEta W |Qa| m + kScrEps T, with A for W and a one-exponential eta.
+// Coefficients: u = beta + b0 in fp32 moves e_f by at most 2 eps e^-1 e^0.5 qa_f
+// per rounding of relative size eps, A and B have relative errors of 5 eps and
+// the reciprocal's: rho = 10 eps W |Qa|.  Two exponentials: a2 = (sum + r)/2 >=
+// sum/2 with r^2 = (k2 + k3 - k4)^2 + 4 k3 k4 is off by 6 eps a2, a1 = 2 k2 k4 /
+// (sum + r) by 5 eps a1; A1 = W (k3 + k4 - a1)/r, A2 = W - A1: where a1 <= (k3 +
+// k4)/2, r >= (k3 + k4)/2 and A1 is off by 9 eps W (x by 18 eps W |Qa|), else x moves
+// by the error of A1 times |E(a1) - E(a2)| <= r 0.61 |Qa|/a1, 6 eps W |Qa|; with the
+// divisions and W, rho = 40 eps W |Qa|.
 // ===========================================================================
 constexpr int kScrShift = 23 - 4;        // float bits below a segment: 16 segments per octave of u = beta + b0
 constexpr int kScrMaxSeg = 256;
-constexpr float kScrEta = 2.6e-7f, kScrEps = 9e-6f;
+constexpr float kScrEta1 = 9e-8f, kScrEps1 = 5e-6f, kScrRho1 = 6e-7f;    // one exponential
+constexpr float kScrEta2 = 2.8e-7f, kScrEps2 = 1.8e-5f, kScrRho2 = 2.4e-6f;  // two
+constexpr int kScrDeg = 12;              // coefficients of the polynomial in a1
+// LDS rows of a segment (float4).  Odd ones spread lanes that read the same
+// function of different segments over all banks (two exponentials: 19 reads a
+// draw); one exponential reads 4, hidden behind the vector ALU, and keeps the
+// smaller table so that 16 one-wavefront blocks fit a CU.
+constexpr int kScrRow1 = 4, kScrRow2 = 5, kScrCross = kScrDeg + 1;
+template <int KINDS>
+constexpr int screen_row() { return (KINDS == KIND_1TCM || KINDS == KIND_IRR) ? kScrRow1 : kScrRow2; }
+constexpr double kScrMaxA1T = 6.5;       // the range of a1 times T that it covers
 constexpr long long kScrMaxDraws = 1LL << 24;  // a key holds 24 bits of draw index
 
 // Segment polynomials of e_f and e_f^2 (frame averages), coefficients of
@@ -1131,11 +1184,14 @@ constexpr long long kScrMaxDraws = 1LL << 24;  // a key holds 24 bits of draw in
 // steps).
 constexpr int kScrChunk = 2048;
 __global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0, double h, int F, int k0, int nseg,
-                                                               unsigned seg0, float b0, float* out) {
+                                                               unsigned seg0, float b0, float* out, double a1hi,
+                                                               const double* cheb, double* poly) {
     __shared__ double sC[kScrChunk], sP[VPET_MAX_FRAMES];
     __shared__ int sN[VPET_MAX_FRAMES];
     const int lane = threadIdx.x, j = lane & 3;
-    const int seg = blockIdx.x * 16 + (lane >> 2);
+    // the block past the segments: e_f at the Chebyshev nodes of [0, a1hi]
+    const bool pol = (int)blockIdx.x * 16 >= nseg;
+    const int seg = pol ? nseg : blockIdx.x * 16 + (lane >> 2);
     const int sg = min(seg, nseg - 1);
     int kend = k0;
     for (int f = lane; f < F; f += kWave) {
@@ -1161,7 +1217,8 @@ __global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0,
     }
     const double xj = j == 0 ? x[0] : (j == 1 ? x[1] : (j == 2 ? x[2] : x[3]));
     double bA;
-    const Exp1 e = exp_setup(ulo + wid * (0.5 + xj) - (double)b0, 1.0, h, C0, &bA);
+    const double pr = pol ? 0.5 * a1hi * (1.0 + cospi((2 * min(lane, kScrDeg - 1) + 1) / (2.0 * kScrDeg))) : 0.0;
+    const Exp1 e = exp_setup(pol ? pr : ulo + wid * (0.5 + xj) - (double)b0, 1.0, h, C0, &bA);
     double H = e.H0, acc = 0.0;
     int k = 0, kc = 0;  // kc: nodes [kc - kScrChunk, kc) are staged
     auto steps = [&](int n) {  // n recursion steps from node k, adding H before each to acc
@@ -1192,6 +1249,13 @@ __global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0,
         steps(n);
         // frame average of the response's trapezoid sum, (acc - (Hs - H) / 2) g + b PP
         const double v = fma(e.eT, fma(-0.5, Hs - H, acc), bA * sP[f]) / (double)n;
+        if (pol) {  // coefficient `lane` of e_f in s = 2 a1 / a1hi - 1
+            double c = 0.0;
+#pragma unroll
+            for (int q = 0; q < kScrDeg; ++q) c = fma(cheb[min(lane, kScrDeg - 1) * kScrDeg + q], lane_f64(v, q), c);
+            if (lane < kScrDeg) poly[(size_t)f * kScrDeg + lane] = c;
+            continue;
+        }
         const double y[4] = {dpp_f64<0x00>(v), dpp_f64<0x55>(v), dpp_f64<0xAA>(v), dpp_f64<0xFF>(v)};
         double c = 0.0, c2 = 0.0;
 #pragma unroll
@@ -1208,7 +1272,7 @@ __global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0,
 
 // A voxel's constants of the screen.
 struct ScreenVox {
-    float yy, yq, yp, qq, qp, pp, ny, nq, np, kap;
+    float yy, yq, yp, qq, qp, pp, ny, nq, np;
 };
 
 __device__ __forceinline__ float wave_uniform(float x) {
@@ -1258,13 +1322,13 @@ __device__ __forceinline__ bool screen_voxel(const InferArgs& P, const double2* 
         sv->ny = (float)(ny * 1.000001);
         sv->nq = (float)(nq * 1.000001);
         sv->np = (float)(np * 1.000001);
-        sv->kap = kScrEta * (float)(nq * 1.000001);
     }
     return mm * mm < 1e12 && aa < 1e12 && yy > 1e-10;
 }
 
 // The voxel's table: per segment the cubics of ee, ye, eq and ep (FP64 sums),
 // a thread per segment, four frames' loads in flight.
+template <int ROW>
 __device__ __forceinline__ void screen_table(const InferArgs& P, const double4* fs, float4* tab) {
     for (int s = threadIdx.x; s < P.nseg; s += blockDim.x) {
         double a[16];
@@ -1288,7 +1352,7 @@ __device__ __forceinline__ void screen_table(const InferArgs& P, const double4* 
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            tab[4 * s + k] = make_float4((float)a[4 * k], (float)a[4 * k + 1], (float)a[4 * k + 2], (float)a[4 * k + 3]);
+            tab[ROW * s + k] = make_float4((float)a[4 * k], (float)a[4 * k + 1], (float)a[4 * k + 2], (float)a[4 * k + 3]);
     }
 }
 
@@ -1296,63 +1360,164 @@ __device__ __forceinline__ float cubic(const float4& c, float t) {
     return fmaf(t, fmaf(t, fmaf(t, c.w, c.z), c.y), c.x);
 }
 
-// Lower bound and error bound of the distance for given coefficients.
-__device__ __forceinline__ void screen_bounds(const ScreenVox& S, const float4* tab, unsigned seg0, float b0, float beta,
-                                              float A, float B, float W, float v, float& lower, float& err) {
+// Two exponentials: the cubics in a2 of the coefficients of 2 sum w e(a1)
+// e(a2) in s, [segment - seg2][kScrDeg]; a thread per segment and three
+// coefficients.
+__device__ __forceinline__ void screen_cross_table(const InferArgs& P, const double4* fs, float4* cross) {
+    constexpr int G = 3, NG = kScrDeg / G;
+    for (int q0 = (threadIdx.x >> 6) * kWave; q0 < P.nseg2 * NG; q0 += blockDim.x) {
+        const int q = min(q0 + lane_id(), P.nseg2 * NG - 1);
+        const int s = q / NG, r0 = (q - s * NG) * G;
+        double a[4 * G];
+#pragma unroll
+        for (int k = 0; k < 4 * G; ++k) a[k] = 0.0;
+        const size_t st = (size_t)P.nseg;
+        const float* c = P.scr + (P.seg2 - P.seg0) + s;
+        const double* po = P.poly + r0;
+#pragma unroll 2
+        for (int f = 0; f < P.F; ++f, c += 8 * st, po += kScrDeg) {
+            const double w2 = 2.0 * fs[f].x;
+            double e[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[r] = (double)c[r * st];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const double wp = w2 * po[g];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) a[4 * g + r] = fma(wp, e[r], a[4 * g + r]);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            cross[s * kScrCross + r0 + g] =
+                make_float4((float)a[4 * g], (float)a[4 * g + 1], (float)a[4 * g + 2], (float)a[4 * g + 3]);
+    }
+}
+
+// Row of a table of `stride` float4 per segment.
+__device__ __forceinline__ const float4* table_row(const float4* tab, uint32_t seg, uint32_t stride) {
+    return reinterpret_cast<const float4*>(reinterpret_cast<const char*>(tab) + __umul24(seg, 16u * stride));
+}
+
+// Segment of a rate and the position t in [-1/2, 1/2) across it.
+__device__ __forceinline__ uint32_t segment_of(float beta, float b0, float& t) {
     const uint32_t ub = __float_as_uint(beta + b0);
-    const float4* row = tab + 4 * ((ub >> kScrShift) - seg0);
-    const float t = __uint_as_float(((ub << (23 - kScrShift)) & 0x7FFFFFu) | 0x3F800000u) - 1.5f;
+    t = __uint_as_float(((ub << (23 - kScrShift)) & 0x7FFFFFu) | 0x3F800000u) - 1.5f;
+    return ub >> kScrShift;
+}
+
+// A draw's d~, err and rho (see above).
+struct Screened {
+    float d, err, rho;
+};
+
+template <int ROW>
+__device__ __forceinline__ Screened screen_one(const ScreenVox& S, const float4* tab, unsigned seg0, float b0, float beta,
+                                               float A, float B, float W, float v) {
+    float t;
+    const float4* row = table_row(tab, segment_of(beta, b0, t) - seg0, ROW);
     const float ee = cubic(row[0], t), ye = cubic(row[1], t), eq = cubic(row[2], t), ep = cubic(row[3], t);
     const float a = A * ee, b = B * S.qq, c = v * S.pp;
     const float ia = fmaf(v, ep, fmaf(B, eq, a + ye)), ib = fmaf(v, S.qp, b + S.yq), ic = c + S.yp;
-    const float d = fmaf(A, ia, fmaf(B, ib, fmaf(v, ic, S.yy)));
     const float T = fmaf(A, a, fmaf(B, b, fmaf(v, c, S.yy)));
-    const float m = fmaf(W, S.nq, fmaf(v, S.np, S.ny));
-    err = fmaf(A * S.kap, m, kScrEps * T);
-    lower = d - err;
+    const float wq = W * S.nq, m = fmaf(v, S.np, S.ny) + wq;
+    Screened r;
+    r.d = fmaf(A, ia, fmaf(B, ib, fmaf(v, ic, S.yy)));
+    r.err = fmaf(kScrEta1 * S.nq * A, m, kScrEps1 * T);
+    r.rho = kScrRho1 * wq;
+    return r;
 }
 
-// Draw i of list position m: prior draw in fp32 (the exact fp32 parameters),
-// then the screen.
-template <int KIND>
-__device__ __forceinline__ void screen_draw(const InferArgs& P, const ScreenVox& S, const float4* tab, int m, uint32_t vg,
-                                            uint32_t i, float& lower, float& err) {
+__device__ __forceinline__ Screened screen_two(const InferArgs& P, const ScreenVox& S, const float4* tab,
+                                               const float4* cross, float a1, float a2, float A1, float A2, float W,
+                                               float v) {
+    float t1, t2;
+    const float4* r1 = table_row(tab, segment_of(a1, P.b0, t1) - P.seg0, kScrRow2);
+    const uint32_t s2 = segment_of(a2, P.b0, t2);
+    const float4* r2 = table_row(tab, s2 - P.seg0, kScrRow2);
+    const float4* cr = table_row(cross, s2 - P.seg2, kScrCross);
+    const float e1 = cubic(r1[0], t1), y1 = cubic(r1[1], t1), p1 = cubic(r1[3], t1);
+    const float e2 = cubic(r2[0], t2), y2 = cubic(r2[1], t2), p2 = cubic(r2[3], t2);
+    const float z = fmaf(a1, P.a1scale, -1.0f);
+    float g = cubic(cr[kScrDeg - 1], t2);
+#pragma unroll
+    for (int k = kScrDeg - 2; k >= 0; --k) g = fmaf(g, z, cubic(cr[k], t2));
+    const float a = A1 * e1, b = A2 * e2, c = v * S.pp;
+    const float i1 = fmaf(v, p1, fmaf(A2, g, a + y1)), i2 = fmaf(v, p2, b + y2), ic = c + S.yp;
+    const float T = fmaf(A1, a, fmaf(A2, b, fmaf(v, c, S.yy)));
+    const float wq = W * S.nq, m = fmaf(v, S.np, S.ny) + wq;
+    Screened r;
+    r.d = fmaf(A1, i1, fmaf(A2, i2, fmaf(v, ic, S.yy)));
+    r.err = fmaf(kScrEta2 * wq, m, kScrEps2 * T);
+    r.rho = kScrRho2 * wq;
+    return r;
+}
+
+// Draw i of list position m: the exact fp32 parameters of its prior draw, then
+// the screen.
+template <int KIND, int ROW>
+__device__ __forceinline__ Screened screen_draw(const InferArgs& P, const ScreenVox& S, const float4* tab,
+                                                const float4* cross, int m, uint32_t vg, uint32_t i) {
     const ModelDev& md = P.md[m];
+    // the width times 2^-24 is exact (a power of two), and so is the integer
+    auto param = [&](int j, uint32_t u) { return fmaf(md.wid[j] * 0x1p-24f, (float)(u >> 8), md.lo[j]); };
     uint32_t w[4];
     philox10(i, vg, 0u, (uint32_t)m << 16, P.key0, P.key1, w);
-    const float K1 = fmaf(md.wid[0], unit24(w[0]), md.lo[0]), k2 = fmaf(md.wid[1], unit24(w[1]), md.lo[1]);
-    const float p2 = fmaf(md.wid[2], unit24(w[2]), md.lo[2]);
+    const float K1 = param(0, w[0]), k2 = param(1, w[1]);
+    const float p2 = param(2, w[2]);
     if constexpr (KIND == KIND_1TCM) {
         const float W = (1.0f - p2) * K1;
-        screen_bounds(S, tab, P.seg0, P.b0, k2, W, 0.0f, W, p2, lower, err);
-    } else {
-        const float vB = fmaf(md.wid[3], unit24(w[3]), md.lo[3]);
+        return screen_one<ROW>(S, tab, P.seg0, P.b0, k2, W, 0.0f, W, p2);
+    } else if constexpr (KIND == KIND_IRR) {
+        const float vB = param(3, w[3]);
         const float beta = k2 + p2, W = (1.0f - vB) * K1, r = W * __builtin_amdgcn_rcpf(beta);
-        screen_bounds(S, tab, P.seg0, P.b0, beta, r * k2, r * p2, W, vB, lower, err);
+        return screen_one<ROW>(S, tab, P.seg0, P.b0, beta, r * k2, r * p2, W, vB);
+    } else {
+        const float k4 = param(3, w[3]);
+        uint32_t w2[4];
+        philox10(i, vg, 0u, ((uint32_t)m << 16) | 1u, P.key0, P.key1, w2);
+        const float vB = param(4, w2[0]);
+        const float W = (1.0f - vB) * K1, dk = (k2 + p2) - k4, sum = (k2 + p2) + k4;
+        const float r = __builtin_amdgcn_sqrtf(fmaf(dk, dk, 4.0f * p2 * k4)), sr = sum + r;
+        const float a2 = 0.5f * sr, a1 = 2.0f * k2 * k4 * __builtin_amdgcn_rcpf(sr);
+        const float A1 = fminf(fmaxf(W * ((p2 + k4) - a1) * __builtin_amdgcn_rcpf(r), 0.0f), W);
+        return screen_two(P, S, tab, cross, fminf(a1, P.a1hi), fminf(a2, P.a2hi), A1, W - A1, W, vB);
     }
 }
 
 // Candidates of one wavefront: keys (lower bound, error class, draw), the
 // first `have` of them sorted and certified at or below tau, an upper bound of
-// the wave's n-th smallest distance.  The error class is the error rounded up
-// to the next float with two mantissa bits.
+// the wave's n-th smallest distance.  The error class is the width of the
+// draw's interval rounded up to the next float with two mantissa bits.
 constexpr uint32_t kErrBase = (127u - 40u) << 2;
-__device__ __forceinline__ uint64_t screen_key(float lower, float err, uint32_t g) {
-    const uint32_t cls = min(max((__float_as_uint(err) >> 21) + 1u, kErrBase) - kErrBase, 255u);
-    return ((uint64_t)__float_as_uint(fmaxf(lower, 0.0f)) << 32) | (cls << 24) | g;
+__device__ __forceinline__ float screen_upper(const Screened& s) {
+    const float q = __builtin_amdgcn_sqrtf(fmaxf(s.d + s.err, 0.0f)) * 1.0000003f + s.rho;
+    return q * q * 1.0000005f;
+}
+__device__ __forceinline__ uint64_t screen_key(const Screened& s, uint32_t g) {
+    const float q = fmaxf(__builtin_amdgcn_sqrtf(fmaxf(s.d - s.err, 0.0f)) * 0.9999997f - s.rho, 0.0f);
+    const float lower = q * q * 0.9999995f, width = screen_upper(s) - lower;
+    const uint32_t cls = min(max((__float_as_uint(width) >> 21) + 1u, kErrBase) - kErrBase, 255u);
+    return ((uint64_t)__float_as_uint(lower) << 32) | (cls << 24) | g;
 }
 // The draw's upper bound, a little up so that fp32 ties at it stay candidates.
 __device__ __forceinline__ float screen_upper(uint64_t key) {
     const float l = __uint_as_float((uint32_t)(key >> 32));
     const float e = __uint_as_float((((uint32_t)key >> 24) + kErrBase) << 21);
-    return fmaf(2.0f, e, l) * 1.0000005f;
+    return (l + e) * 1.0000005f;
+}
+
+// Keys of a block's lists in LDS, which first hold 4 doubles per frame.
+__host__ __device__ inline size_t screen_keys(int wpv, int cap, int F) {
+    const size_t k = (size_t)wpv * cap, f = 4 * (size_t)F;
+    return k > f ? k : f;
 }
 
 struct ScreenList {
     uint64_t* keys;
     int n, cap, have, nbuf;
-    float tau;
-    bool full;  // the candidates do not fit
+    float tau, root;  // root: sqrt(tau), rounded up
+    bool full;        // the candidates do not fit
 
     // tau = the largest upper bound of the first n keys; the keys whose lower
     // bound is at or below it (a prefix of the sorted keys) stay.
@@ -1379,7 +1544,7 @@ struct ScreenList {
         wave_bitonic_sort(keys, len);
         nbuf = 0;
         have = used;
-        if (used >= n) tau = prefix(keys, used, n, have);
+        if (used >= n) set_tau(prefix(keys, used, n, have));
         full = full || have > cap - kWave;
     }
 
@@ -1387,12 +1552,11 @@ struct ScreenList {
     // is one of the n-th smallest distance, so that a short stream does not
     // sort a buffer full of draws that it can rule out.
     template <int U>
-    __device__ __forceinline__ void start(const float (&lower)[U], const float (&err)[U], const bool (&ok)[U]) {
+    __device__ __forceinline__ void start(const Screened (&s)[U], const bool (&ok)[U]) {
         float x = __builtin_inff();
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (ok[u]) x = fminf(x, fmaf(2.0f, err[u], lower[u]));
-        x = fmaxf(x, 0.0f);
+            if (ok[u]) x = fminf(x, screen_upper(s[u]));
         const int lane = lane_id();
 #pragma unroll
         for (int k = 2; k <= kWave; k <<= 1) {
@@ -1402,23 +1566,33 @@ struct ScreenList {
                 x = ((lane & j) == 0) == ((lane & k) == 0) ? fminf(x, y) : fmaxf(x, y);
             }
         }
-        tau = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), n - 1)) * 1.0000005f;
+        set_tau(__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), n - 1)) * 1.0000005f);
+    }
+
+    __device__ __forceinline__ void set_tau(float t) {
+        tau = t;
+        root = wave_uniform(__builtin_amdgcn_sqrtf(t) * 1.0000003f);
+    }
+
+    // The lower bound is at or below tau unless d - err > (sqrt(tau) + rho)^2.
+    __device__ __forceinline__ bool passes(const Screened& s) const {
+        const float q = root + s.rho;
+        return s.d - s.err <= q * q;
     }
 
     template <int U>
-    __device__ __forceinline__ void insert(const float (&lower)[U], const float (&err)[U], const uint32_t (&g)[U],
-                                           const bool (&ok)[U]) {
-        if (n <= kWave && have + nbuf == 0 && tau == __builtin_inff()) start(lower, err, ok);
+    __device__ __forceinline__ void insert(const Screened (&s)[U], const uint32_t (&g)[U], const bool (&ok)[U]) {
+        if (n <= kWave && have + nbuf == 0 && tau == __builtin_inff()) start(s, ok);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            uint64_t b = __ballot(ok[u] && lower[u] <= tau);
+            uint64_t b = __ballot(ok[u] && passes(s[u]));
             if (b == 0ull || full) continue;
             if (nbuf + __popcll(b) > cap - have) {
                 merge();
                 if (full) continue;
-                b = __ballot(ok[u] && lower[u] <= tau);
+                b = __ballot(ok[u] && passes(s[u]));
             }
-            if (ok[u] && lower[u] <= tau) keys[have + nbuf + (int)mbcnt(b)] = screen_key(lower[u], err[u], g[u]);
+            if (ok[u] && passes(s[u])) keys[have + nbuf + (int)mbcnt(b)] = screen_key(s[u], g[u]);
             nbuf += __popcll(b);
             wave_lds_sync();
         }
@@ -1426,40 +1600,23 @@ struct ScreenList {
 };
 
 // Keys of list position m's draws of the wave's tiles into the candidates.
-template <int KIND>
-__device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVox& S, const float4* tab, int m,
-                                              uint32_t vg, const double2* yw, ScreenList& list) {
+template <int KIND, int ROW>
+__device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVox& S, const float4* tab,
+                                              const float4* cross, int m, uint32_t vg, ScreenList& list) {
     constexpr int U = KIND == KIND_REV ? 2 : kUmax, kTile = kWave * U;
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
     for (uint32_t t = threadIdx.x >> 6; t < ntiles && !list.full; t += (uint32_t)P.wpv) {
-        float lower[U], err[U];
+        Screened s[U];
         uint32_t g[U];
         bool ok[U];
-        if constexpr (KIND == KIND_REV) {  // two exponentials: the exact distance
-            uint32_t idx[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t i = t * kTile + (uint32_t)(u * kWave + lane_id());
-                ok[u] = i < P.n_draws;
-                idx[u] = ok[u] ? i : P.n_draws - 1;
-                g[u] = (uint32_t)m * P.n_draws + idx[u];
-            }
-            draw_distances<KIND_REV, U, false>(P, m, vg, idx, yw, lower);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                err[u] = 0.0f;
-                lower[u] *= 0.9999998f;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t i = t * kTile + (uint32_t)(u * kWave + lane_id());
-                ok[u] = i < P.n_draws;
-                g[u] = (uint32_t)m * P.n_draws + i;
-                screen_draw<KIND>(P, S, tab, m, vg, i, lower[u], err[u]);
-            }
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = t * kTile + (uint32_t)(u * kWave + lane_id());
+            ok[u] = i < P.n_draws;
+            g[u] = (uint32_t)m * P.n_draws + i;
+            s[u] = screen_draw<KIND, ROW>(P, S, tab, cross, m, vg, i);
         }
-        list.insert(lower, err, g, ok);
+        list.insert(s, g, ok);
     }
 }
 
@@ -1556,10 +1713,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     const int F = P.F, n = (int)P.n_acc;
     const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
     double2* yw = reinterpret_cast<double2*>(lds);
-    double4* fs = reinterpret_cast<double4*>(yw + F);
-    float4* tab = reinterpret_cast<float4*>(fs + F);
-    uint64_t* keys_all = reinterpret_cast<uint64_t*>(tab + 4 * P.nseg);
-    double* red = reinterpret_cast<double*>(keys_all + (size_t)P.wpv * P.cap);
+    constexpr int kRow = screen_row<KINDS>();
+    float4* tab = reinterpret_cast<float4*>(yw + F);
+    float4* cross = tab + kRow * P.nseg;
+    uint64_t* keys_all = reinterpret_cast<uint64_t*>(cross + kScrCross * P.nseg2);
+    double4* fs = reinterpret_cast<double4*>(keys_all);  // (until the table is built)
+    double* red = reinterpret_cast<double*>(keys_all + screen_keys(P.wpv, P.cap, F));
     int* flag = reinterpret_cast<int*>(red + kRedStride * P.wpv);
     ScreenVox* sv = reinterpret_cast<ScreenVox*>(flag + 4 + P.wpv);  // flag[4 + w]: wave w's candidates
     if (wave == 0) {
@@ -1575,7 +1734,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     }
     bool screened = flag[1] == 0;
     if (screened) {
-        screen_table(P, fs, tab);
+        screen_table<kRow>(P, fs, tab);
+        if (KINDS == 0 || KINDS == KIND_REV) screen_cross_table(P, fs, cross);
         ScreenVox S;
         S.yy = wave_uniform(sv->yy);
         S.yq = wave_uniform(sv->yq);
@@ -1586,25 +1746,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         S.ny = wave_uniform(sv->ny);
         S.nq = wave_uniform(sv->nq);
         S.np = wave_uniform(sv->np);
-        S.kap = wave_uniform(sv->kap);
         __syncthreads();
         ScreenList list;
         list.keys = keys_all + (size_t)wave * P.cap;
         list.n = n;
         list.cap = P.cap;
         list.have = list.nbuf = 0;
-        list.tau = __builtin_inff();
+        list.tau = list.root = __builtin_inff();
         list.full = false;
         for (int m = 0; m < P.M; ++m) {
             const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
             if constexpr (KINDS != 0)
-                screen_stream<KINDS>(P, S, tab, m, vg, yw, list);
+                screen_stream<KINDS, kRow>(P, S, tab, cross, m, vg, list);
             else if (kind == KIND_IRR)
-                screen_stream<KIND_IRR>(P, S, tab, m, vg, yw, list);
+                screen_stream<KIND_IRR, kRow>(P, S, tab, cross, m, vg, list);
             else if (kind == KIND_REV)
-                screen_stream<KIND_REV>(P, S, tab, m, vg, yw, list);
+                screen_stream<KIND_REV, kRow>(P, S, tab, cross, m, vg, list);
             else
-                screen_stream<KIND_1TCM>(P, S, tab, m, vg, yw, list);
+                screen_stream<KIND_1TCM, kRow>(P, S, tab, cross, m, vg, list);
         }
         if (!list.full) list.merge();
         if (list.full && lane == 0) flag[1] = 1;
@@ -1615,7 +1774,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
                 // one list for the block before the exact pass
                 for (int j = list.have + lane; j < P.cap; j += kWave) list.keys[j] = kNoKey;
                 __syncthreads();
-                block_bitonic_sort(keys_all, P.wpv * P.cap);
+                block_merge_runs(keys_all, P.cap, P.wpv * P.cap);
                 int have;
                 ScreenList::prefix(keys_all, P.wpv * P.cap, n, have);
                 const int rounds = (have + (int)blockDim.x - 1) / (int)blockDim.x;
@@ -4589,6 +4748,7 @@ struct HostTab {
     int K = 0, F = 0, k0 = 0, kend = 0;
     double h = 0.0, C0 = 0.0;
     std::vector<double> C, fr, qa;
+    std::vector<double> cheb;  // screened reversible draws: chebyshev_to_powers(), after the other tables
     std::vector<int> nf;
 };
 
@@ -4747,7 +4907,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // (FP64), the frame lengths in nodes (int32) and the per-frame sums of the
 // running integral of |C| (FP64), each 256-byte aligned.
 struct TabLayout {
-    size_t offC, offF, offN, offA, bytes;
+    size_t offC, offF, offN, offA, bytes;  // (bytes: without T.cheb, which starts there)
 };
 TabLayout tab_layout(const HostTab& T) {
     TabLayout L;
@@ -4774,6 +4934,7 @@ int upload_tables(DevCtx& ctx, const HostTab& T, hipStream_t st, Tab& tab, int& 
     const TabLayout L = tab_layout(T);
     const size_t offC = L.offC, offF = L.offF, offN = L.offN, bytes = L.bytes;
     if (bytes > kSlotBytes) return fail(VPET_E_LIMIT, "tables need %zu bytes (> %zu)", bytes, kSlotBytes);
+    const size_t copy = bytes + sizeof(double) * T.cheb.size();
     slot = ctx.next;
     ctx.next = (ctx.next + 1) % kSlots;
     hipError_t e = hipEventSynchronize(ctx.ev[slot]);
@@ -4784,7 +4945,8 @@ int upload_tables(DevCtx& ctx, const HostTab& T, hipStream_t st, Tab& tab, int& 
     std::memcpy(hs + offF, T.fr.data(), sizeof(double) * T.fr.size());
     std::memcpy(hs + offN, T.nf.data(), sizeof(int) * T.nf.size());
     if (!T.qa.empty()) std::memcpy(hs + L.offA, T.qa.data(), sizeof(double) * T.qa.size());
-    e = hipMemcpyAsync(ds, hs, bytes, hipMemcpyHostToDevice, st);
+    if (!T.cheb.empty()) std::memcpy(hs + bytes, T.cheb.data(), sizeof(double) * T.cheb.size());
+    e = hipMemcpyAsync(ds, hs, copy, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(tables)");
     tab.C = reinterpret_cast<const double*>(ds + offC);
     tab.fr = reinterpret_cast<const double*>(ds + offF);
@@ -4905,6 +5067,9 @@ int stage_tables_noalloc(const HostTab& T, hipStream_t st, Tab& tab) {
     if ((rc = stage_bytes(T.fr.data(), sizeof(double) * T.fr.size(), base + L.offF, st)) != VPET_OK) return rc;
     if ((rc = stage_bytes(T.nf.data(), sizeof(int) * T.nf.size(), base + L.offN, st)) != VPET_OK) return rc;
     if ((rc = stage_bytes(T.qa.data(), sizeof(double) * T.qa.size(), base + L.offA, st)) != VPET_OK) return rc;
+    if (!T.cheb.empty() &&
+        (rc = stage_bytes(T.cheb.data(), sizeof(double) * T.cheb.size(), base + L.bytes, st)) != VPET_OK)
+        return rc;
     tab.C = reinterpret_cast<const double*>(base + L.offC);
     tab.fr = reinterpret_cast<const double*>(base + L.offF);
     tab.nf = reinterpret_cast<const int*>(base + L.offN);
@@ -4971,34 +5136,48 @@ int select_key_buffer(int cap, int n, bool weighted) {
 int64_t screen_min_draws(int64_t n_voxels) { return n_voxels >= 2048 ? 1024 : (n_voxels >= 512 ? 2000 : 2600); }
 struct ScreenPlan {
     bool use = false;
-    int nseg = 0, cap = 0;
-    unsigned seg0 = 0;
-    float b0 = 0.0f;
-    size_t lds = 0;
+    int nseg = 0, nseg2 = 0, cap = 0, wpv = 1;
+    unsigned seg0 = 0, seg2 = 0;
+    float b0 = 0.0f, a1hi = 0.0f, a2hi = 0.0f;
+    size_t lds = 0, off_cheb = 0, off_poly = 0, off_scr = 0;  // bytes from the tables' start
 };
 ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, int M, int64_t n_draws, int n_acc,
                        const vpet_abc_opts& o, int64_t n_voxels, int wpv) {
     ScreenPlan S;
     const int64_t total = (int64_t)M * n_draws;
     if (o.distance != 0 || o.proposal || total < screen_min_draws(n_voxels) || total > kScrMaxDraws) return S;
-    float lo = INFINITY, hi = 0.0f;  // the range of beta as the kernel forms it (fp32, monotonic roundings)
-    bool any = false;
+    // the range of the rates as the kernel forms them (fp32, monotonic roundings)
+    float lo = INFINITY, hi = 0.0f, lo2 = INFINITY, hi2 = 0.0f, a1hi = 0.0f;
     for (int m = 0; m < M; ++m) {
         const ModelDev& md = P.md[m];
-        if (kinds[m] != KIND_1TCM && kinds[m] != KIND_IRR) continue;
-        any = true;
-        if (kinds[m] == KIND_IRR && !(md.lo[1] + md.lo[2] > 1e-20f)) return S;  // 1 / beta
-        float l = md.lo[1], h = std::fmaf(md.wid[1], 1.0f, md.lo[1]);
-        if (kinds[m] == KIND_IRR) {
-            l += md.lo[2];
-            h += std::fmaf(md.wid[2], 1.0f, md.lo[2]);
+        float up[kMaxParams];
+        for (int j = 0; j < md.np; ++j) up[j] = std::fmaf(md.wid[j], 1.0f, md.lo[j]);
+        float l, h;
+        if (kinds[m] == KIND_1TCM) {
+            l = md.lo[1];
+            h = up[1];
+        } else if (kinds[m] == KIND_IRR) {
+            l = md.lo[1] + md.lo[2];
+            h = up[1] + up[2];
+            if (!(l > 1e-20f)) return S;  // 1 / beta
+        } else {
+            // a1 in [0, min(k2, k4)], a2 in [max(k2, k3 + k4), k2 + k3 + k4] and a
+            // little beyond in fp32 (the kernel clamps the upper ends)
+            l = 0.0f;
+            h = up[1] + up[2] + up[3];
+            a1hi = std::fmax(a1hi, std::fmin(up[1], up[3]) * 1.00001f);
+            lo2 = std::fmin(lo2, std::fmax(md.lo[1], md.lo[2] + md.lo[3]) * 0.9999f);
+            hi2 = std::fmax(hi2, h * 1.00001f);
+            if (!(md.lo[2] > 1e-12f) || !(md.lo[1] + md.lo[2] > 1e-12f)) return S;  // 1 / r, 1 / (sum + r)
+            h = hi2;
         }
         lo = std::fmin(lo, l);
         hi = std::fmax(hi, h);
     }
-    if (!any || !(hi < 1e6f)) return S;
-    int ex;
     const double t_end = (double)T.kend * T.h;
+    const bool rev = hi2 > 0.0f;
+    if (!(hi < 1e6f) || (rev && (double)a1hi * t_end > kScrMaxA1T)) return S;
+    int ex;
     (void)std::frexp(0.5 / t_end, &ex);
     S.b0 = std::ldexp(1.0f, ex - 1);  // the power of two at or below 1 / (2 T)
     auto seg_of = [&](float beta) {
@@ -5010,12 +5189,44 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
     S.seg0 = seg_of(lo);
     S.nseg = (int)(seg_of(hi) - S.seg0) + 1;
     if (S.nseg > kScrMaxSeg || !(S.b0 > 1e-20f)) return S;
-    if (tab_layout(T).bytes + sizeof(float) * 8 * (size_t)S.nseg * T.F > kSlotBytes) return S;
+    if (rev) {
+        S.seg2 = seg_of(lo2);
+        S.nseg2 = (int)(seg_of(hi2) - S.seg2) + 1;
+        S.a1hi = std::fmax(a1hi, 1e-6f);
+        S.a2hi = hi2;
+    }
+    S.off_cheb = tab_layout(T).bytes;
+    S.off_poly = S.off_cheb + (rev ? align256(sizeof(double) * kScrDeg * kScrDeg) : 0);
+    S.off_scr = S.off_poly + (rev ? align256(sizeof(double) * kScrDeg * (size_t)T.F) : 0);
+    if (S.off_scr + sizeof(float) * 8 * (size_t)S.nseg * T.F > kSlotBytes) return S;
     S.cap = pow2_at_least(n_acc + n_acc / 4 + 2 * kWave);
-    S.lds = 48 * (size_t)T.F + 64 * (size_t)S.nseg + sizeof(uint64_t) * (size_t)wpv * S.cap +
-            sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv + sizeof(ScreenVox);
+    // the large table of a voxel's two-exponential screen is shared by four wavefronts
+    if (rev && o.waves_per_voxel == 0) wpv = std::max(wpv, 4);
+    const int row = M == 1 && !rev ? kScrRow1 : kScrRow2;
+    S.wpv = wpv;
+    S.lds = 16 * ((size_t)T.F + (size_t)row * S.nseg + (size_t)kScrCross * S.nseg2) +
+            sizeof(uint64_t) * screen_keys(wpv, S.cap, T.F) + sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv +
+            sizeof(ScreenVox);
     S.use = S.lds <= (size_t)kLdsLimit;
     return S;
+}
+
+// Row r of the matrix that takes a function's values at the kScrDeg Chebyshev
+// nodes s_j = cos((2 j + 1) pi / (2 kScrDeg)) to its interpolant's coefficient of
+// s^r: sum_k (2 - [k = 0]) / kScrDeg T_k(s_j) t_kr, T_k = sum_r t_kr s^r.
+std::vector<double> chebyshev_to_powers() {
+    constexpr int D = kScrDeg;
+    std::vector<double> m(D * D, 0.0);
+    double t[D][D] = {};
+    t[0][0] = t[1][1] = 1.0;
+    for (int k = 2; k < D; ++k)
+        for (int r = 0; r < D; ++r) t[k][r] = (r > 0 ? 2.0 * t[k - 1][r - 1] : 0.0) - t[k - 2][r];
+    for (int j = 0; j < D; ++j)
+        for (int k = 0; k < D; ++k) {
+            const double c = (k == 0 ? 1.0 : 2.0) / D * std::cos(M_PI * k * (2 * j + 1) / (2.0 * D));
+            for (int r = 0; r < D; ++r) m[r * D + j] += c * t[k][r];
+        }
+    return m;
 }
 
 }  // namespace
@@ -5233,6 +5444,13 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         P.nseg = scr.nseg;
         P.seg0 = scr.seg0;
         P.b0 = scr.b0;
+        P.nseg2 = scr.nseg2;
+        P.seg2 = scr.seg2;
+        P.a1hi = scr.a1hi;
+        P.a2hi = scr.a2hi;
+        P.a1scale = scr.nseg2 ? 2.0f / scr.a1hi : 0.0f;
+        wpv = scr.wpv;
+        if (scr.nseg2) T.cheb = chebyshev_to_powers();
     }
 
     P.weights = o.weights;
@@ -5267,11 +5485,16 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         if ((rc = upload_tables(*ctx, T, st, P.tab, slot)) != VPET_OK) return rc;
     }
     if (scr.use) {
-        // the segment polynomials follow the call's tables in the same device buffer
-        float* out = reinterpret_cast<float*>(const_cast<char*>(reinterpret_cast<const char*>(P.tab.C)) + tab_layout(T).bytes);
-        hipLaunchKernelGGL(vpet_screen_table_kernel, dim3((unsigned)((scr.nseg + 15) / 16)), dim3(64), 0, st, P.tab,
-                           T.C0, T.h, T.F, T.k0, scr.nseg, scr.seg0, scr.b0, out);
+        // the screen's tables follow the call's in the same device buffer
+        char* base = const_cast<char*>(reinterpret_cast<const char*>(P.tab.C));
+        float* out = reinterpret_cast<float*>(base + scr.off_scr);
+        double* poly = reinterpret_cast<double*>(base + scr.off_poly);
+        const unsigned blocks = (unsigned)((scr.nseg + 15) / 16) + (scr.nseg2 ? 1u : 0u);
+        hipLaunchKernelGGL(vpet_screen_table_kernel, dim3(blocks), dim3(64), 0, st, P.tab, T.C0, T.h, T.F, T.k0, scr.nseg,
+                           scr.seg0, scr.b0, out, (double)scr.a1hi, reinterpret_cast<const double*>(base + scr.off_cheb),
+                           poly);
         P.scr = out;
+        P.poly = poly;
     }
     const long long chunk = 1LL << 30;
     for (long long base = 0; base < n_voxels; base += chunk) {
@@ -5293,6 +5516,7 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         const int sel = o.proposal ? -1 - o.distance : (scr.use ? -8 - one : one * 2 + (o.distance == 1 ? 1 : 0));
         switch (sel) {
             case -8 - KIND_IRR: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_IRR>), grid, block, lds, st, Q); break;
+            case -8 - KIND_REV: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_REV>), grid, block, lds, st, Q); break;
             case -8 - KIND_1TCM: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_1TCM>), grid, block, lds, st, Q); break;
             case -8: hipLaunchKernelGGL((vpet_infer_screen_kernel<0>), grid, block, lds, st, Q); break;
             case -1: hipLaunchKernelGGL((vpet_infer_is_kernel<false>), grid, block, lds, st, Q); break;
