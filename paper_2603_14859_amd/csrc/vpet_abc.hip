@@ -1327,13 +1327,17 @@ __device__ __forceinline__ bool screen_voxel(const InferArgs& P, const double2* 
 }
 
 // The voxel's table: per segment the cubics of ee, ye, eq and ep (FP64 sums),
-// a thread per segment, four frames' loads in flight.
+// a thread per segment, four frames' loads in flight; with `slope` also the
+// norm of u e'(beta) at the segment's middle (u is 16.5 + (segment mod 16) of its
+// widths there).
 template <int ROW>
-__device__ __forceinline__ void screen_table(const InferArgs& P, const double4* fs, float4* tab) {
+__device__ __forceinline__ void screen_table(const InferArgs& P, const double4* fs, float4* tab,
+                                             float* slope = nullptr) {
     for (int s = threadIdx.x; s < P.nseg; s += blockDim.x) {
         double a[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) a[k] = 0.0;
+        double sl = 0.0;
         const float* c = P.scr + s;
         const size_t st = (size_t)P.nseg;
 #pragma unroll 4
@@ -1349,10 +1353,12 @@ __device__ __forceinline__ void screen_table(const InferArgs& P, const double4* 
                 a[8 + r] = fma(q.z, (double)e[r], a[8 + r]);
                 a[12 + r] = fma(q.w, (double)e[r], a[12 + r]);
             }
+            sl = fma(q.x * (double)e[1], (double)e[1], sl);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             tab[ROW * s + k] = make_float4((float)a[4 * k], (float)a[4 * k + 1], (float)a[4 * k + 2], (float)a[4 * k + 3]);
+        if (slope) slope[s] = (16.5f + (float)((P.seg0 + (unsigned)s) & 15u)) * sqrtf((float)sl) * 1.00001f;
     }
 }
 
@@ -1410,12 +1416,18 @@ __device__ __forceinline__ uint32_t segment_of(float beta, float b0, float& t) {
 struct Screened {
     float d, err, rho;
 };
+// T of the draw (see above) and its segment's number, for callers with larger coefficient errors.
+struct ScreenTerms {
+    float T;
+    uint32_t seg;
+};
 
 template <int ROW>
 __device__ __forceinline__ Screened screen_one(const ScreenVox& S, const float4* tab, unsigned seg0, float b0, float beta,
-                                               float A, float B, float W, float v) {
+                                               float A, float B, float W, float v, ScreenTerms* terms = nullptr) {
     float t;
-    const float4* row = table_row(tab, segment_of(beta, b0, t) - seg0, ROW);
+    const uint32_t seg = segment_of(beta, b0, t) - seg0;
+    const float4* row = table_row(tab, seg, ROW);
     const float ee = cubic(row[0], t), ye = cubic(row[1], t), eq = cubic(row[2], t), ep = cubic(row[3], t);
     const float a = A * ee, b = B * S.qq, c = v * S.pp;
     const float ia = fmaf(v, ep, fmaf(B, eq, a + ye)), ib = fmaf(v, S.qp, b + S.yq), ic = c + S.yp;
@@ -1425,6 +1437,7 @@ __device__ __forceinline__ Screened screen_one(const ScreenVox& S, const float4*
     r.d = fmaf(A, ia, fmaf(B, ib, fmaf(v, ic, S.yy)));
     r.err = fmaf(kScrEta1 * S.nq * A, m, kScrEps1 * T);
     r.rho = kScrRho1 * wq;
+    if (terms) *terms = {T, seg};
     return r;
 }
 
@@ -3562,37 +3575,44 @@ struct MixTab {
     float lo[kMixD], hi[kMixD];  // fp32 prior box of the drawn parameters
 };
 
-// Mixture of one voxel's outputs o[72]: weights softmax(logits), log sd =
-// LS0 + (LS1 - LS0) sigmoid(raw) + logscale; cum[c] = a + (1 - a) (pi_0 + ...
-// + pi_c), the component thresholds of u0 above the defensive share a.
-__device__ void mix_table(const float* o, MixTab& t, double share, double logscale, double logvol, const float* lo,
-                          const float* hi) {
+// Mixture of one voxel's outputs o[72], by one wavefront (a lane per component
+// and parameter): weights softmax(logits), log sd = LS0 + (LS1 - LS0)
+// sigmoid(raw) + logscale; cum[c] = a + (1 - a) (pi_0 + ... + pi_c), the
+// component thresholds of u0 above the defensive share a.  (One lane's 70
+// exponentials were 15 % of a voxel with 20k screened draws.)
+__device__ __forceinline__ void mix_table(const float* o, MixTab& t, double share, double logscale, double logvol,
+                                          const float* lo, const float* hi) {
+    const int lane = lane_id();
     double mx = -1e300;
     for (int c = 0; c < kMixC; ++c) mx = fmax(mx, (double)o[c]);
+    const double ex = lane < kMixC ? exp((double)o[lane] - mx) : 0.0;
     double se = 0.0;
-    for (int c = 0; c < kMixC; ++c) se += exp((double)o[c] - mx);
+    for (int c = 0; c < kMixC; ++c) se += lane_f64(ex, c);
     const double lse = mx + log(se);
+    if (lane < kMixC) t.logpi[lane] = (double)o[lane] - lse;
+    const double pi = lane < kMixC ? exp((double)o[lane] - lse) : 0.0;
     double run = 0.0;
     for (int c = 0; c < kMixC; ++c) {
-        t.logpi[c] = (double)o[c] - lse;
-        run += exp(t.logpi[c]);
-        t.cum[c] = share + (1.0 - share) * run;
-        for (int j = 0; j < kMixD; ++j) {
-            const int q = c * kMixD + j;
-            t.mu[q] = (double)o[kMixC + q];
-            t.logsd[q] = kLS0 + (kLS1 - kLS0) / (1.0 + exp(-(double)o[kMixC + kMixC * kMixD + q]));
-            if (logscale != 0.0) t.logsd[q] += logscale;
-            t.sd[q] = exp(t.logsd[q]);
-        }
+        run += lane_f64(pi, c);
+        if (lane == 0) t.cum[c] = share + (1.0 - share) * run;
     }
-    for (int j = 0; j < kMixD; ++j) {
-        t.lo[j] = lo[j];
-        t.hi[j] = hi[j];
+    if (lane < kMixC * kMixD) {
+        t.mu[lane] = (double)o[kMixC + lane];
+        double ls = kLS0 + (kLS1 - kLS0) / (1.0 + exp(-(double)o[kMixC + kMixC * kMixD + lane]));
+        if (logscale != 0.0) ls += logscale;
+        t.logsd[lane] = ls;
+        t.sd[lane] = exp(ls);
     }
-    t.share = share;
-    t.log_share = log(share);
-    t.log_rest = log1p(-share);
-    t.logvol = logvol;
+    if (lane < kMixD) {
+        t.lo[lane] = lo[lane];
+        t.hi[lane] = hi[lane];
+    }
+    if (lane == 0) {
+        t.share = share;
+        t.log_share = log(share);
+        t.log_rest = log1p(-share);
+        t.logvol = logvol;
+    }
 }
 
 // FP64 log and exp for the proposal draws, from their series (within 1 ulp
@@ -3985,24 +4005,21 @@ __device__ __forceinline__ double proposal_log_weight(const MixTab& t, const dou
     return -(m + log1p(exp(-fabs(x - y))));
 }
 
-// Keys of one tile of proposal draws (invalid draws never enter the top n).
+// fp32 distances of the proposal draws idx (+inf for a draw outside the box).
 template <int U, bool L1>
-__device__ __forceinline__ void tile_keys_is(const InferArgs& P, const MixTab& mix, uint32_t v, uint32_t i0,
-                                             const double2* yw, uint64_t (&key)[U]) {
+__device__ __forceinline__ void proposal_distances(const InferArgs& P, const MixTab& mix, uint32_t v,
+                                                   const uint32_t (&idx)[U], const double2* yw, float (&fd)[U],
+                                                   bool (&ok)[U]) {
     DrawState<1, U> s;
-    uint32_t idx[U];
-    bool ok[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint32_t i = i0 + (uint32_t)(u * kWave + lane_id());
-        idx[u] = i < P.n_draws ? i : P.n_draws - 1;
         float th[kMaxParams];
         const ThetaDraw d = proposal_theta(&mix, P.key0, P.key1, v, idx[u]);
 #pragma unroll
         for (int j = 0; j < kMixD; ++j) th[j] = d.th[j];
 #pragma unroll
         for (int j = kMixD; j < kMaxParams; ++j) th[j] = 0.0f;
-        ok[u] = d.ok && i < P.n_draws;
+        ok[u] = d.ok;
         if (!ok[u]) {  // a harmless in-box stand-in keeps the lane's recursion finite
             th[0] = mix.hi[0];
             th[1] = mix.hi[1];
@@ -4018,10 +4035,28 @@ __device__ __forceinline__ void tile_keys_is(const InferArgs& P, const MixTab& m
     simulate_draws<KIND_IRR, U>(P.tab, P.F, P.k0, s, sink);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        float fd = (float)sink.d[u];
-        if (!(fd == fd)) fd = __builtin_inff();
-        key[u] = ok[u] ? (((uint64_t)__float_as_uint(fd) << 32) | idx[u]) : kNoKey;
+        const float f = (float)sink.d[u];
+        fd[u] = f == f ? f : __builtin_inff();
     }
+}
+
+// Keys of one tile of proposal draws (invalid draws never enter the top n).
+template <int U, bool L1>
+__device__ __forceinline__ void tile_keys_is(const InferArgs& P, const MixTab& mix, uint32_t v, uint32_t i0,
+                                             const double2* yw, uint64_t (&key)[U]) {
+    uint32_t idx[U];
+    bool in[U], ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t i = i0 + (uint32_t)(u * kWave + lane_id());
+        in[u] = i < P.n_draws;
+        idx[u] = in[u] ? i : P.n_draws - 1;
+    }
+    float fd[U];
+    proposal_distances<U, L1>(P, mix, v, idx, yw, fd, ok);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        key[u] = in[u] && ok[u] ? (((uint64_t)__float_as_uint(fd[u]) << 32) | idx[u]) : kNoKey;
 }
 
 __device__ double block_max(double v, double* red, int nw) {
@@ -4034,53 +4069,30 @@ __device__ double block_max(double v, double* red, int nw) {
     return m;
 }
 
-// Importance-weighted ABC of one voxel per block (irreversible 2TCM): n_draws
-// proposal draws from the voxel's mixture, the n closest valid ones accepted,
-// moments weighted by prior / proposal (FP64, max-shifted), and the effective
-// sample size (sum w)^2 / sum w^2.
-// (At most 128 VGPRs for four waves per SIMD: the few spills this costs sit
-// in the accepted-draw epilogue, not in the screening loop.)
+// Outputs of an invalid voxel (one wavefront).
+__device__ __forceinline__ void infer_is_invalid(const InferArgs& P, long long row) {
+    const int lane = lane_id(), n = (int)P.n_acc;
+    const float qnan = __builtin_nanf("");
+    for (int j = lane; j < 16; j += kWave) P.out_mom[(size_t)row * 16 + j] = qnan;
+    if (lane == 0) {
+        P.out_prob[row] = qnan;
+        if (P.out_ess) P.out_ess[row] = qnan;
+        if (P.out_thr) P.out_thr[row] = qnan;
+    }
+    if (P.out_idx)
+        for (int j = lane; j < n; j += kWave) P.out_idx[(size_t)row * n + j] = -1;
+    if (P.out_dist)
+        for (int j = lane; j < n; j += kWave) P.out_dist[(size_t)row * n + j] = qnan;
+}
+
+// Every proposal draw through this wavefront's running top-n.
 template <bool L1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_is_kernel(InferArgs P) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long row = blockIdx.x;
-    if (row >= P.V) return;
-    const int F = P.F;
-    const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
-    double2* yw = reinterpret_cast<double2*>(lds);
-    const int yw_bytes = (16 * F + 15) & ~15;
-    uint64_t* keys_all = reinterpret_cast<uint64_t*>(lds + yw_bytes);
-    double* red = reinterpret_cast<double*>(keys_all + (size_t)P.wpv * P.cap);
-    int* flag = reinterpret_cast<int*>(red + kRedStride * kMaxWpv);
-    MixTab* mix = reinterpret_cast<MixTab*>(reinterpret_cast<unsigned char*>(flag) + 16);
-    const int n = (int)P.n_acc;
-    if (wave == 0) {
-        voxel_curve(P, row, yw, flag);
-        if (lane == 0)
-            mix_table(P.prop + (size_t)row * kNetOut, *mix, P.prop_share, P.prop_logscale, P.prop_logvol, P.plo,
-                      P.phi);
-    }
-    __syncthreads();
-    if (*flag == 0) {
-        if (wave == 0) {
-            const float qnan = __builtin_nanf("");
-            for (int j = lane; j < 16; j += kWave) P.out_mom[(size_t)row * 16 + j] = qnan;
-            if (lane == 0) {
-                P.out_prob[row] = qnan;
-                if (P.out_ess) P.out_ess[row] = qnan;
-                if (P.out_thr) P.out_thr[row] = qnan;
-            }
-            if (P.out_idx)
-                for (int j = lane; j < n; j += kWave) P.out_idx[(size_t)row * n + j] = -1;
-            if (P.out_dist)
-                for (int j = lane; j < n; j += kWave) P.out_dist[(size_t)row * n + j] = qnan;
-        }
-        return;
-    }
+__device__ __forceinline__ void stream_draws_is(const InferArgs& P, const MixTab& mix, uint32_t vg, const double2* yw,
+                                                uint64_t* keys_all) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
     TopN top;
     top.keys = keys_all + (size_t)wave * P.cap;
-    top.n = n;
+    top.n = (int)P.n_acc;
     top.cap = P.cap;
     top.nbuf = 0;
     top.tau = kNoKey;
@@ -4091,52 +4103,76 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
     for (uint32_t t = (uint32_t)wave; t < ntiles; t += (uint32_t)P.wpv) {
         uint64_t key[kU];
-        tile_keys_is<kU, L1>(P, *mix, vg, t * kTile, yw, key);
+        tile_keys_is<kU, L1>(P, mix, vg, t * kTile, yw, key);
         top.insert(key);
     }
     top.merge();
-    __syncthreads();
-    if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
-    const uint64_t* acc = keys_all;
+}
+
+// Importance-weighted outputs of one voxel from its n accepted keys: the
+// weights' maximum, then the weighted sums, then the spread.  The first keys of
+// a thread keep their log weight and values between the passes (each costs an
+// FP64 draw and the log density of eight components).
+constexpr int kIsCache = 2;
+__device__ __forceinline__ void infer_is_outputs(const InferArgs& P, long long row, uint32_t vg, const MixTab* mix,
+                                                 const uint64_t* acc, double* red) {
+    const int tid = threadIdx.x, n = (int)P.n_acc, nw = blockDim.x >> 6;
     if (P.out_idx)
         for (int j = tid; j < n; j += blockDim.x)
             P.out_idx[(size_t)row * n + j] = acc[j] == kNoKey ? -1 : (int)(uint32_t)acc[j];
     if (P.out_dist)
         for (int j = tid; j < n; j += blockDim.x) P.out_dist[(size_t)row * n + j] = __uint_as_float((uint32_t)(acc[j] >> 32));
     if (P.out_thr && tid == 0) P.out_thr[row] = __uint_as_float((uint32_t)(acc[n - 1] >> 32));
-
-    // weights of the accepted draws: max, then sums, then the spread
-    const int nw = blockDim.x >> 6;
     const float h_v = P.below ? P.below[row] : __builtin_inff();
-    auto accepted = [&](int j, float th[kMaxParams], double& lw) {
+    auto accepted = [&](int j, double (&val)[6], double& lw) {
         if (acc[j] == kNoKey) return false;
         if (!(__uint_as_float((uint32_t)(acc[j] >> 32)) <= h_v)) return false;  // given threshold
+        float th[kMaxParams];
         double z[kMixD];
         proposal_draw<true>(*mix, P.key0, P.key1, vg, (uint32_t)acc[j], th, z);
         lw = proposal_log_weight(*mix, z);
+        slot_values(KIND_IRR, th, val);
         return true;
     };
-    double lmax = -__builtin_inf();
-    for (int j = tid; j < n; j += blockDim.x) {
-        float th[kMaxParams];
-        double lw;
-        if (accepted(j, th, lw)) lmax = fmax(lmax, lw);
+    double c_lw[kIsCache], c_val[kIsCache][6], lmax = -__builtin_inf();
+    bool c_ok[kIsCache];
+#pragma unroll 1
+    for (int i = 0; i < kIsCache; ++i) {
+        const int j = tid + i * (int)blockDim.x;
+        double lw = 0.0, val[6];
+        const bool ok = j < n && accepted(j, val, lw);
+#pragma unroll
+        for (int k = 0; k < kIsCache; ++k)
+            if (k == i) {
+                c_ok[k] = ok;
+                c_lw[k] = lw;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) c_val[k][q] = ok ? val[q] : 0.0;
+            }
+        if (ok) lmax = fmax(lmax, lw);
+    }
+    for (int j = tid + kIsCache * (int)blockDim.x; j < n; j += blockDim.x) {
+        double lw, val[6];
+        if (accepted(j, val, lw)) lmax = fmax(lmax, lw);
     }
     lmax = block_max(lmax, red, nw);
-    double s1[8];
+    double s1[8], c_w[kIsCache];
 #pragma unroll
     for (int q = 0; q < 8; ++q) s1[q] = 0.0;  // sum w val[0..5], sum w, sum w^2
-    for (int j = tid; j < n; j += blockDim.x) {
-        float th[kMaxParams];
-        double lw;
-        if (!accepted(j, th, lw)) continue;
-        const double w = exp(lw - lmax);
-        double val[6];
-        slot_values(KIND_IRR, th, val);
+    auto add = [&](double w, const double (&val)[6]) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) s1[q] = fma(w, val[q], s1[q]);
         s1[6] += w;
         s1[7] = fma(w, w, s1[7]);
+    };
+#pragma unroll
+    for (int i = 0; i < kIsCache; ++i) {
+        c_w[i] = c_ok[i] ? exp(c_lw[i] - lmax) : 0.0;
+        if (c_ok[i]) add(c_w[i], c_val[i]);
+    }
+    for (int j = tid + kIsCache * (int)blockDim.x; j < n; j += blockDim.x) {
+        double lw, val[6];
+        if (accepted(j, val, lw)) add(exp(lw - lmax), val);
     }
     block_sum<8>(s1, red, nw);
     const double sw = s1[6];
@@ -4146,18 +4182,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         mean[q] = s1[q] / sw;
         s2[q] = 0.0;
     }
-    for (int j = tid; j < n; j += blockDim.x) {
-        float th[kMaxParams];
-        double lw;
-        if (!accepted(j, th, lw)) continue;
-        const double w = exp(lw - lmax);
-        double val[6];
-        slot_values(KIND_IRR, th, val);
+    auto spread = [&](double w, const double (&val)[6]) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
             const double dv = val[q] - mean[q];
             s2[q] = fma(w * dv, dv, s2[q]);
         }
+    };
+#pragma unroll
+    for (int i = 0; i < kIsCache; ++i)
+        if (c_ok[i]) spread(c_w[i], c_val[i]);
+    for (int j = tid + kIsCache * (int)blockDim.x; j < n; j += blockDim.x) {
+        double lw, val[6];
+        if (accepted(j, val, lw)) spread(exp(lw - lmax), val);
     }
     block_sum<6>(s2, red, nw);
     if (tid < 16) {
@@ -4170,6 +4207,261 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         P.out_prob[row] = sw > 0.0 ? 1.0f : __builtin_nanf("");
         if (P.out_ess) P.out_ess[row] = sw > 0.0 ? (float)(sw * sw / s1[7]) : __builtin_nanf("");
     }
+}
+
+// Importance-weighted ABC of one voxel per block (irreversible 2TCM): n_draws
+// proposal draws from the voxel's mixture, the n closest valid ones accepted,
+// moments weighted by prior / proposal (FP64, max-shifted), and the effective
+// sample size (sum w)^2 / sum w^2.
+// (At most 128 VGPRs for four waves per SIMD: the few spills this costs sit
+// in the accepted-draw epilogue, not in the screening loop.)
+template <bool L1>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_is_kernel(InferArgs P) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int wave = threadIdx.x >> 6;
+    const long long row = blockIdx.x;
+    if (row >= P.V) return;
+    const int F = P.F;
+    const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
+    double2* yw = reinterpret_cast<double2*>(lds);
+    const int yw_bytes = (16 * F + 15) & ~15;
+    uint64_t* keys_all = reinterpret_cast<uint64_t*>(lds + yw_bytes);
+    double* red = reinterpret_cast<double*>(keys_all + (size_t)P.wpv * P.cap);
+    int* flag = reinterpret_cast<int*>(red + kRedStride * kMaxWpv);
+    MixTab* mix = reinterpret_cast<MixTab*>(reinterpret_cast<unsigned char*>(flag) + 16);
+    if (wave == 0) {
+        voxel_curve(P, row, yw, flag);
+        mix_table(P.prop + (size_t)row * kNetOut, *mix, P.prop_share, P.prop_logscale, P.prop_logvol, P.plo, P.phi);
+    }
+    __syncthreads();
+    if (*flag == 0) {
+        if (wave == 0) infer_is_invalid(P, row);
+        return;
+    }
+    stream_draws_is<L1>(P, *mix, vg, yw, keys_all);
+    __syncthreads();
+    if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, (int)P.n_acc);
+    infer_is_outputs(P, row, vg, mix, keys_all, red);
+}
+
+// ---------------------------------------------------------------------------
+// Screened proposal draws (L2): the screen of vpet_infer_screen_kernel with the
+// mixture draw itself in fp32 on the hardware's transcendental unit; the draws
+// it cannot rule out are drawn and scored as in vpet_infer_is_kernel.  About 200
+// instructions a draw instead of 1100: 16,384 voxels x 20k draws, n = 100, 10.1 ->
+// 2.45 ms, of which 0.6 ms do not depend on the number of draws.
+//
+// u0 and the component thresholds are compared as integers (u0 2^24 < ceil(cum
+// 2^24)), so the component is the exact one.  theta = e^mu 2^(sd log2(e) n): the
+// Box-Muller normal n is off by at most 1.6e-6 (over all 2^24 values of u the
+// radius by 4.9e-7 and the hardware's sine and cosine by 1.3e-7, measured against
+// FP64; |n| <= 5.8), sd log2(e) and the product with n by eps = 2^-24 each, the
+// hardware exp2 by 8.3e-8, e^mu and the last product by eps: theta is off by at
+// most kap = 2.3e-6 max sd + 2.1e-7, relatively.  A draw whose box test kap
+// could change is tested exactly.
+// rho: K1, k2 and beta each move A and B by kap (A's and B's parts of s x have
+// norms at most sqrt(T)), vB <= 1/2 moves W by kap and s v p by kap v |P|, and
+// beta moves e by kap |u e'|, tabulated at the middle of each segment (elsewhere
+// in it larger by at most (0.61 + 0.9)/32 |Qa|): rho = kap (6 sqrt(T) + A (slope +
+// 0.05 |Qa|) + v |P|) + the one-exponential rho.  (Bounding e and its slope by |Qa|
+// alone is 10-30 times looser and overflowed the candidate lists.)
+// ---------------------------------------------------------------------------
+struct MixScreen {
+    uint32_t thr[kMixC];       // u0 2^24 below thr[0]: a prior draw; component: the number of thr[1..7] at or below
+    float4 mul[kMixC], ex[kMixC];  // e^mu and sd log2(e) of each component's parameters
+    float kap, tol;            // relative error of theta; of the box test
+    int bad;                   // mixture beyond what the screen covers
+};
+
+// (one wavefront, after mix_table)
+__device__ __forceinline__ void mix_screen(const MixTab& t, MixScreen& m) {
+    const int lane = lane_id();
+    if (lane < kMixC) {
+        const double c = lane == 0 ? t.share : t.cum[lane - 1];
+        m.thr[lane] = (uint32_t)fmin(fmax(ceil(c * 0x1p24), 0.0), 0x1p25);
+        const int q = lane * kMixD;
+        m.mul[lane] = make_float4((float)exp_series(t.mu[q]), (float)exp_series(t.mu[q + 1]), (float)exp_series(t.mu[q + 2]),
+                                  (float)exp_series(t.mu[q + 3]));
+        m.ex[lane] = make_float4((float)(t.sd[q] * 1.4426950408889634), (float)(t.sd[q + 1] * 1.4426950408889634),
+                                 (float)(t.sd[q + 2] * 1.4426950408889634), (float)(t.sd[q + 3] * 1.4426950408889634));
+    }
+    double sd = lane < kMixC * kMixD ? t.sd[lane] : 0.0, z = lane < kMixC * kMixD ? fabs(t.mu[lane]) : 0.0;
+    const bool finite = isfinite(sd) && isfinite(z) && !(lane < kMixC && !isfinite(t.cum[lane]));
+    const bool bad = __ballot(!finite) != 0ull;
+    sd = wave_max(sd);
+    z = wave_max(z) + 5.8 * sd;
+    double w = 0.0;
+    for (int j = 0; j < kMixD; ++j) w = fmax(w, 2.0 * (double)t.hi[j] / ((double)t.hi[j] - (double)t.lo[j]));
+    if (lane == 0) {
+        const double kap = 2.3e-6 * sd + 2.1e-7;
+        m.kap = (float)kap * 1.000001f;
+        m.tol = (float)(2.0 * (kap + 4e-7) * w);
+        m.bad = (bad || !(z < 80.0) || !(m.tol < 0.1f)) ? 1 : 0;
+    }
+}
+
+// Draw i of voxel v: false outside the box, else the screen of its distance.
+struct ProposalScreen {
+    float kap, kapP, kapQ, tol;
+    float a[kMixD], b[kMixD], lo[kMixD], wid[kMixD], blo, bhi;
+};
+__device__ __forceinline__ bool screen_proposal(const InferArgs& P, const ScreenVox& S, const ProposalScreen& C,
+                                                const MixTab* mix, const MixScreen* ms, const float4* tab,
+                                                const float* slope, uint32_t v,
+                                                uint32_t i, Screened& out) {
+    uint32_t w[4];
+    philox10(i, v, 2u, 0u, P.key0, P.key1, w);
+    const uint32_t u0 = (w[0] & 255u) | (w[1] & 255u) << 8 | (w[2] & 255u) << 16;
+    const bool prior = u0 < ms->thr[0];
+    int c = 0;
+#pragma unroll
+    for (int q = 1; q < kMixC; ++q) c += u0 >= ms->thr[q] ? 1 : 0;
+    const float4 ml = ms->mul[c], ex = ms->ex[c];
+    float u[kMixD], n[kMixD], th[kMixD];
+#pragma unroll
+    for (int j = 0; j < kMixD; ++j) u[j] = (float)(w[j] >> 8);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf((u[2 * q] + 1.0f) * 0x1p-24f));
+        const float x = u[2 * q + 1] * 0x1p-24f;  // the hardware's sine and cosine take turns, not radians
+        n[2 * q] = r * __builtin_amdgcn_cosf(x);
+        n[2 * q + 1] = r * __builtin_amdgcn_sinf(x);
+    }
+    const float mj[4] = {ml.x, ml.y, ml.z, ml.w}, ej[4] = {ex.x, ex.y, ex.z, ex.w};
+    float t = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kMixD; ++j) {
+        const float q = mj[j] * __builtin_amdgcn_exp2f(ej[j] * n[j]);
+        t = fmaxf(t, fabsf(fmaf(q, C.a[j], C.b[j])));
+        th[j] = prior ? fmaf(u[j], C.wid[j], C.lo[j]) : q;
+    }
+    bool ok = prior || t <= 1.0f + C.tol;
+    if (ok && !prior && !(t < 1.0f - C.tol)) ok = proposal_theta(mix, P.key0, P.key1, v, i).ok != 0;
+    const float beta = fminf(fmaxf(th[1] + th[2], C.blo), C.bhi);
+    const float W = (1.0f - th[3]) * th[0], r = W * __builtin_amdgcn_rcpf(beta);
+    const float A = r * th[1];
+    ScreenTerms x;
+    out = screen_one<kScrRow1>(S, tab, P.seg0, P.b0, beta, A, r * th[2], W, th[3], &x);
+    out.rho += fmaf(th[3], C.kapP, fmaf(A, fmaf(C.kap, slope[x.seg], C.kapQ), 6.0f * C.kap * __builtin_amdgcn_sqrtf(x.T)));
+    return ok;
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_is_screen_kernel(InferArgs P) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long long row = blockIdx.x;
+    if (row >= P.V) return;
+    const int F = P.F, n = (int)P.n_acc;
+    const uint32_t vg = (uint32_t)(P.vbase + (unsigned long long)row);
+    double2* yw = reinterpret_cast<double2*>(lds);
+    float4* tab = reinterpret_cast<float4*>(yw + F);
+    uint64_t* keys_all = reinterpret_cast<uint64_t*>(tab + kScrRow1 * P.nseg);
+    double4* fs = reinterpret_cast<double4*>(keys_all);  // (until the table is built)
+    double* red = reinterpret_cast<double*>(keys_all + screen_keys(P.wpv, P.cap, F));
+    MixTab* mix = reinterpret_cast<MixTab*>(red + kRedStride * P.wpv);
+    MixScreen* ms = reinterpret_cast<MixScreen*>(mix + 1);
+    ScreenVox* sv = reinterpret_cast<ScreenVox*>(ms + 1);
+    int* flag = reinterpret_cast<int*>(sv + 1);  // [0] valid, [1] unscreened, [4 + w] wave w's candidates
+    float* slope = reinterpret_cast<float*>(flag + 4 + P.wpv);
+    if (wave == 0) {
+        voxel_curve(P, row, yw, flag);
+        mix_table(P.prop + (size_t)row * kNetOut, *mix, P.prop_share, P.prop_logscale, P.prop_logvol, P.plo, P.phi);
+        wave_lds_sync();
+        mix_screen(*mix, *ms);
+        const bool fits = screen_voxel(P, yw, fs, sv);
+        wave_lds_sync();
+        if (lane == 0) flag[1] = fits && ms->bad == 0 ? 0 : 1;
+    }
+    __syncthreads();
+    if (*flag == 0) {
+        if (wave == 0) infer_is_invalid(P, row);
+        return;
+    }
+    bool screened = flag[1] == 0;
+    if (screened) {
+        screen_table<kScrRow1>(P, fs, tab, slope);
+        ScreenVox S;
+        S.yy = wave_uniform(sv->yy);
+        S.yq = wave_uniform(sv->yq);
+        S.yp = wave_uniform(sv->yp);
+        S.qq = wave_uniform(sv->qq);
+        S.qp = wave_uniform(sv->qp);
+        S.pp = wave_uniform(sv->pp);
+        S.ny = wave_uniform(sv->ny);
+        S.nq = wave_uniform(sv->nq);
+        S.np = wave_uniform(sv->np);
+        ProposalScreen C;
+        const float kap = wave_uniform(ms->kap);
+        C.kap = kap;
+        C.kapP = kap * S.np;
+        C.kapQ = 0.05f * kap * S.nq;
+        C.tol = wave_uniform(ms->tol);
+#pragma unroll
+        for (int j = 0; j < kMixD; ++j) {
+            const float half = 0.5f * (P.phi[j] - P.plo[j]);
+            C.a[j] = 1.0f / half;
+            C.b[j] = -0.5f * (P.phi[j] + P.plo[j]) / half;
+            C.lo[j] = P.plo[j];
+            C.wid[j] = (P.phi[j] - P.plo[j]) * 0x1p-24f;
+        }
+        C.blo = P.plo[1] + P.plo[2];
+        C.bhi = P.phi[1] + P.phi[2];
+        __syncthreads();
+        ScreenList list;
+        list.keys = keys_all + (size_t)wave * P.cap;
+        list.n = n;
+        list.cap = P.cap;
+        list.have = list.nbuf = 0;
+        list.tau = list.root = __builtin_inff();
+        list.full = false;
+        constexpr int U = 1, kTile = kWave * U;
+        const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
+        for (uint32_t t = (uint32_t)wave; t < ntiles && !list.full; t += (uint32_t)P.wpv) {
+            Screened s[U];
+            uint32_t g[U];
+            bool ok[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                g[u] = t * kTile + (uint32_t)(u * kWave + lane);
+                ok[u] = screen_proposal(P, S, C, mix, ms, tab, slope, vg, g[u], s[u]) && g[u] < P.n_draws;
+            }
+            list.insert(s, g, ok);
+        }
+        if (!list.full) list.merge();
+        if (lane == 0) {
+            if (list.full) flag[1] = 1;
+            flag[4 + wave] = list.have;
+        }
+        // exact keys of this wavefront's candidates, then the n smallest
+        if (!list.full) {
+            for (int j0 = 0; j0 < list.have; j0 += kWave) {
+                const int j = j0 + lane;
+                const uint32_t idx[1] = {j < list.have ? (uint32_t)list.keys[j] & 0xFFFFFFu : 0u};
+                float fd[1];
+                bool ok[1];
+                proposal_distances<1, false>(P, *mix, vg, idx, yw, fd, ok);
+                if (j < list.have)
+                    list.keys[j] = ok[0] ? (((uint64_t)__float_as_uint(fd[0]) << 32) | idx[0]) : kNoKey;
+            }
+            // (fewer than n valid draws in all leave kNoKey at the end)
+            const int len = 1 << (32 - __builtin_clz((unsigned)(max(list.have, n) | 1)));
+            for (int j = list.have + lane; j < P.cap; j += kWave) list.keys[j] = kNoKey;
+            wave_lds_sync();
+            wave_bitonic_sort(list.keys, min(len, P.cap));
+        }
+        __syncthreads();
+        screened = flag[1] == 0;
+        if (screened && P.wpv > 1) {
+            block_topn_sort(keys_all, P.wpv, P.cap, n);
+        }
+    }
+    if (!screened) {
+        __syncthreads();
+        stream_draws_is<false>(P, *mix, vg, yw, keys_all);
+        __syncthreads();
+        if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
+    }
+    infer_is_outputs(P, row, vg, mix, keys_all, red);
 }
 
 // ===========================================================================
@@ -5145,7 +5437,7 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
                        const vpet_abc_opts& o, int64_t n_voxels, int wpv) {
     ScreenPlan S;
     const int64_t total = (int64_t)M * n_draws;
-    if (o.distance != 0 || o.proposal || total < screen_min_draws(n_voxels) || total > kScrMaxDraws) return S;
+    if (o.distance != 0 || total < screen_min_draws(n_voxels) || total > kScrMaxDraws) return S;
     // the range of the rates as the kernel forms them (fp32, monotonic roundings)
     float lo = INFINITY, hi = 0.0f, lo2 = INFINITY, hi2 = 0.0f, a1hi = 0.0f;
     for (int m = 0; m < M; ++m) {
@@ -5157,9 +5449,12 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
             l = md.lo[1];
             h = up[1];
         } else if (kinds[m] == KIND_IRR) {
-            l = md.lo[1] + md.lo[2];
-            h = up[1] + up[2];
+            l = o.proposal ? P.plo[1] + P.plo[2] : md.lo[1] + md.lo[2];
+            h = o.proposal ? P.phi[1] + P.phi[2] : up[1] + up[2];
             if (!(l > 1e-20f)) return S;  // 1 / beta
+            if (o.proposal && !(P.phi[3] <= 0.5f)) return S;  // (the bound on vB's part of rho)
+            for (int j = 0; o.proposal && j < 4; ++j)  // the box test divides by its width
+                if (!(P.phi[j] - P.plo[j] > 1e-6f * P.phi[j])) return S;
         } else {
             // a1 in [0, min(k2, k4)], a2 in [max(k2, k3 + k4), k2 + k3 + k4] and a
             // little beyond in fp32 (the kernel clamps the upper ends)
@@ -5206,7 +5501,7 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
     S.wpv = wpv;
     S.lds = 16 * ((size_t)T.F + (size_t)row * S.nseg + (size_t)kScrCross * S.nseg2) +
             sizeof(uint64_t) * screen_keys(wpv, S.cap, T.F) + sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv +
-            sizeof(ScreenVox);
+            sizeof(ScreenVox) + (o.proposal ? sizeof(MixTab) + sizeof(MixScreen) + sizeof(float) * S.nseg : 0);
     S.use = S.lds <= (size_t)kLdsLimit;
     return S;
 }
@@ -5513,7 +5808,8 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         Q.below = o.accept_below ? o.accept_below + base : nullptr;
         const dim3 grid((unsigned)Q.V), block(kWave * wpv);
         const int one = M == 1 ? kinds[0] : 0;
-        const int sel = o.proposal ? -1 - o.distance : (scr.use ? -8 - one : one * 2 + (o.distance == 1 ? 1 : 0));
+        const int sel = o.proposal ? (scr.use ? -3 : -1 - o.distance)
+                                   : (scr.use ? -8 - one : one * 2 + (o.distance == 1 ? 1 : 0));
         switch (sel) {
             case -8 - KIND_IRR: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_IRR>), grid, block, lds, st, Q); break;
             case -8 - KIND_REV: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_REV>), grid, block, lds, st, Q); break;
@@ -5521,6 +5817,7 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
             case -8: hipLaunchKernelGGL((vpet_infer_screen_kernel<0>), grid, block, lds, st, Q); break;
             case -1: hipLaunchKernelGGL((vpet_infer_is_kernel<false>), grid, block, lds, st, Q); break;
             case -2: hipLaunchKernelGGL((vpet_infer_is_kernel<true>), grid, block, lds, st, Q); break;
+            case -3: hipLaunchKernelGGL(vpet_infer_is_screen_kernel, grid, block, lds, st, Q); break;
             case 2 * KIND_IRR: hipLaunchKernelGGL((vpet_infer_kernel<KIND_IRR, false>), grid, block, lds, st, Q); break;
             case 2 * KIND_IRR + 1: hipLaunchKernelGGL((vpet_infer_kernel<KIND_IRR, true>), grid, block, lds, st, Q); break;
             case 2 * KIND_REV: hipLaunchKernelGGL((vpet_infer_kernel<KIND_REV, false>), grid, block, lds, st, Q); break;

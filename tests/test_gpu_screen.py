@@ -79,3 +79,21 @@ def test_inputs(case):
     elif case == "rev_no_k4":
         boxes[0, 3] = (0.0, 0.0)
     _check_infer(ora, y, ft, cp, [model], boxes, n_draws, p, 3, weights=weights)
+
+
+@pytest.mark.parametrize("n_draws,n,share,scale,spread,sd", [
+    (2599, 20, 0.1, 1.0, 0.2, 0.3), (2600, 64, 0.0, 1.0, 0.2, 0.3), (2601, 65, 0.1, 1.5, 0.2, 0.3),
+    (5003, 300, 0.5, 1.0, 0.2, 0.3), (4000, 1000, 0.1, 1.0, 0.2, 0.3),
+    (6000, 50, 0.0, 1.0, 2.0, 3.0),    # most draws outside the box
+    (6000, 50, 0.1, 1.0, 0.05, 0.01),  # a sharp mixture: every draw close
+    (3000, 2000, 0.0, 1.0, 3.0, 5.0)])  # fewer valid draws than accepted ones
+def test_proposal_draws(n_draws, n, share, scale, spread, sd):
+    from test_gpu_proposal import _check_is, _synthetic_outputs, _tacs
+    rng = np.random.default_rng(31)
+    ft, cp, th, y = _tacs(10, 9)
+    o = _synthetic_outputs(th, rng, spread=spread, sd=sd)
+    o[2, 3] = np.nan   # a mixture the screen does not take
+    o[3, 9] = 300.0
+    y[4, 2] = np.nan
+    keep = [v for v in range(10) if v not in (2, 3)]
+    _check_is(y, ft, cp, o, n_draws, (n + 0.5) / n_draws, 5, share=share, scale=scale, sample=keep, v_off=3)
