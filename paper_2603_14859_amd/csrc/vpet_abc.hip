@@ -1933,6 +1933,8 @@ struct BankArgs {
     uint64_t* cand;         // [V][cap] candidate keys
     int* fb_list;           // [V] voxels whose candidate list cannot certify the top n
     unsigned* fb_count;     // [1] entries in fb_list
+    unsigned* fb_done;      // [kFbGrid] parts of a listed voxel that are done
+    uint64_t* fb_keys;      // [kFbGrid][n_acc] the parts' smallest keys
     // BF16 contraction (L2 only): d = a_v + sum_k A_vk B_gk with
     // A_v = [-2 w y, w], B_g = [x, x^2], each split into bf16 hi + lo parts
     int K;                  // 2 * ld
@@ -2763,50 +2765,96 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void vp
     bank_outputs_m<WEIGHTED ? 1 : 0>(P, row, keys, red, keys + P.n_acc);
 }
 
-// Exact fallback: one block per listed voxel streams every bank row; each
+// Exact fallback: a listed voxel's bank rows are streamed by one block, or, when
+// the list (whose length the select kernel left in fb_count) is shorter than
+// the fixed grid, by `parts` of them, a contiguous range of rows each; each
 // wavefront keeps a running top-n of its share of the rows (the per-voxel
 // selection of the infer kernel, in fb_cap keys), and a block-wide bitonic
-// sort merges the shares.  A fixed grid walks the list, whose length the
-// select kernel left in fb_count.
+// sort merges the shares.  The parts' n smallest keys go to fb_keys, and the
+// block that finishes a voxel last merges them and writes its outputs.  Bound
+// by the latency of a wavefront's row loads (64 rows of up to 384 bytes, one
+// after the other): two voxels against 400,000 rows (n = 400) took 4.2 ms in a
+// block each, 0.64 ms in 64.
+constexpr unsigned kFbGrid = 2048, kFbParts = 64, kFbPartRows = 4096;
+__device__ __forceinline__ unsigned fallback_parts(const BankArgs& P, unsigned n_fb) {
+    const unsigned room = kFbGrid / (n_fb > 0u ? n_fb : 1u), rows = P.n_tot / kFbPartRows;
+    return max(1u, min(min(room, rows), kFbParts));
+}
+
 template <int LD, bool L1>
 __global__ __launch_bounds__(512) void vpet_bank_fallback_kernel(BankArgs P) {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6;
+    __shared__ int last;
+    const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6, n = (int)P.n_acc;
     uint64_t* keys_all = reinterpret_cast<uint64_t*>(lds);
     double* red = reinterpret_cast<double*>(keys_all + (size_t)nw * P.fb_cap);
     const unsigned n_fb = *P.fb_count;
-    for (unsigned item = blockIdx.x; item < n_fb; item += gridDim.x) {
-        const long long row = P.fb_list[item];
-        double Y[LD], Wt[LD];
-        lane_curve<LD, L1>(P, row, Y, Wt);  // every lane holds the same voxel
-        TopN top;
+    const unsigned parts = fallback_parts(P, n_fb), work = n_fb * parts;
+    TopN top;
+    auto reset = [&]() {
         top.keys = keys_all + (size_t)wave * P.fb_cap;
-        top.n = (int)P.n_acc;
+        top.n = n;
         top.cap = P.fb_cap;
         top.nbuf = 0;
         top.tau = kNoKey;
-        __syncthreads();  // the previous voxel's outputs have read the keys
+        __syncthreads();  // the previous keys have been read
         for (int j = lane_id(); j < P.fb_cap; j += kWave) top.keys[j] = kNoKey;
         wave_lds_sync();
-        const unsigned gb = bank_row_base(P, row);
-        for (unsigned g0 = (unsigned)wave * kWave; g0 < P.n_tot; g0 += (unsigned)nw * kWave) {
-            const unsigned g = g0 + (unsigned)lane_id();
-            uint64_t key[1] = {kNoKey};
-            if (g < P.n_tot) {
-                const float fd = key_dist(row_distance<LD, L1>(P.bank_x + (size_t)(gb + g) * LD, Y, Wt));
-                key[0] = ((uint64_t)__float_as_uint(fd) << 32) | (gb + g);
-            }
-            top.insert(key);
-        }
+    };
+    auto finish = [&]() {
         top.merge();
         __syncthreads();
         if (nw > 1) block_bitonic_sort(keys_all, nw * P.fb_cap);
+    };
+    for (unsigned w = blockIdx.x; w < work; w += gridDim.x) {
+        const unsigned item = w / parts, part = w - item * parts;
+        const long long row = P.fb_list[item];
+        {
+            double Y[LD], Wt[LD];
+            lane_curve<LD, L1>(P, row, Y, Wt);  // every lane holds the same voxel
+            reset();
+            const unsigned gb = bank_row_base(P, row);
+            const unsigned ra = (unsigned)(((uint64_t)P.n_tot * part) / parts);
+            const unsigned rb = (unsigned)(((uint64_t)P.n_tot * (part + 1u)) / parts);
+            for (unsigned g0 = ra + (unsigned)wave * kWave; g0 < rb; g0 += (unsigned)nw * kWave) {
+                const unsigned g = g0 + (unsigned)lane_id();
+                uint64_t key[1] = {kNoKey};
+                if (g < rb) {
+                    const float fd = key_dist(row_distance<LD, L1>(P.bank_x + (size_t)(gb + g) * LD, Y, Wt));
+                    key[0] = ((uint64_t)__float_as_uint(fd) << 32) | (gb + g);
+                }
+                top.insert(key);
+            }
+        }
+        finish();
+        if (parts > 1u) {
+            uint64_t* mine = P.fb_keys + (size_t)w * n;
+            for (int j = threadIdx.x; j < n; j += blockDim.x) mine[j] = keys_all[j];
+            __threadfence();
+            __syncthreads();
+            if (threadIdx.x == 0) last = atomicAdd(P.fb_done + item, 1u) == parts - 1u;
+            __syncthreads();
+            if (!last) continue;
+            __threadfence();
+            reset();
+            const uint64_t* all = P.fb_keys + (size_t)item * parts * n;
+            const unsigned total = parts * (unsigned)n;
+            for (unsigned j0 = (unsigned)wave * kWave; j0 < total; j0 += (unsigned)nw * kWave) {
+                const unsigned j = j0 + (unsigned)lane_id();
+                const uint64_t key[1] = {j < total ? __hip_atomic_load(all + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                                   : kNoKey};
+                top.insert(key);
+            }
+            finish();
+        }
         bank_outputs(P, row, keys_all, red);
     }
 }
 
-__global__ void vpet_bank_reset_kernel(BankArgs P) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *P.fb_count = 0u;
+__global__ __launch_bounds__(256) void vpet_bank_reset_kernel(BankArgs P) {
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0u) *P.fb_count = 0u;
+    if (i < kFbGrid) P.fb_done[i] = 0u;
 }
 
 // vpet_abc_bank_screen: every valid voxel's candidate test admits every row
@@ -5530,6 +5578,18 @@ std::vector<double> chebyshev_to_powers() {
 // C ABI.
 // ===========================================================================
 namespace {
+// Scratch of the exact fallback: count, parts done, list of up to cv voxels,
+// the parts' keys.
+size_t fallback_bytes(long long cv, int n) {
+    return 256 + sizeof(unsigned) * kFbGrid + align256(sizeof(int) * cv) + align256(sizeof(uint64_t) * kFbGrid * (size_t)n);
+}
+void fallback_carve(char* q, long long cv, BankArgs& A) {
+    A.fb_count = reinterpret_cast<unsigned*>(q);
+    A.fb_done = reinterpret_cast<unsigned*>(q + 256);
+    A.fb_list = reinterpret_cast<int*>(q + 256 + sizeof(unsigned) * kFbGrid);
+    A.fb_keys = reinterpret_cast<uint64_t*>(q + 256 + sizeof(unsigned) * kFbGrid + align256(sizeof(int) * cv));
+}
+
 // BF16 hi/lo operands B_g = [x_g, x_g^2] of the first `rows` bank rows.
 void bank_bops(BankArgs A, unsigned rows, hipStream_t st, int ld) {
     A.n_tot = rows;
@@ -5551,10 +5611,10 @@ void bank_chunk(const BankArgs& Q, hipStream_t st, int ld, bool l1, bool mfma, s
                 int fb_waves, Mark& mark) {
     const dim3 lanes((unsigned)((Q.V + 255) / 256)), b256(256), per_voxel((unsigned)Q.V), b64(64);
     const dim3 mblocks((unsigned)((Q.V + kMfmaVox - 1) / kMfmaVox));
-    const dim3 fb_grid((unsigned)std::min<long long>(Q.V, 2048)), fb_block(64 * fb_waves), one(1);
+    const dim3 fb_grid((unsigned)std::min<long long>(Q.V * kFbParts, kFbGrid)), fb_block(64 * fb_waves), resets((kFbGrid + 255) / 256);
 #define VPET_BANK_LAUNCH(LDV, L1V)                                                                        \
     do {                                                                                                  \
-        hipLaunchKernelGGL(vpet_bank_reset_kernel, one, one, 0, st, Q);                                   \
+        hipLaunchKernelGGL(vpet_bank_reset_kernel, resets, b256, 0, st, Q);                               \
         if (mfma) {                                                                                       \
             hipLaunchKernelGGL((vpet_bank_aops_kernel<LDV>), lanes, b256, 0, st, Q);                      \
             launch_mfma<2 * LDV, true>(mblocks, st, Q);                                                   \
@@ -6016,7 +6076,7 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     const int KB = 2 * ld;  // contraction length: [x, x^2] per frame
     char* work = nullptr;
     const size_t sz_tau = align256(sizeof(float) * cv), sz_cnt = align256(sizeof(int) * 2 * cv);
-    const size_t sz_fb = align256(sizeof(int) * cv) + 256, sz_cand = align256(cand_bytes * (size_t)cap * cv);
+    const size_t sz_fb = fallback_bytes(cv, (int)n_acc), sz_cand = align256(cand_bytes * (size_t)cap * cv);
     const size_t sz_b = use_mfma ? align256(sizeof(uint16_t) * (size_t)KB * n_tot) : 0;
     const size_t sz_a = use_mfma ? align256(sizeof(uint16_t) * (size_t)KB * cv) : 0;
     const size_t sz_c = use_mfma ? align256(sizeof(float) * cv) : 0;
@@ -6029,8 +6089,7 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     A.cnt = reinterpret_cast<int*>(q);
     A.cnt_hi = A.cnt + cv;
     q += sz_cnt;
-    A.fb_count = reinterpret_cast<unsigned*>(q);
-    A.fb_list = reinterpret_cast<int*>(q + 256);
+    fallback_carve(q, cv, A);
     q += sz_fb;
     A.cand = reinterpret_cast<uint64_t*>(q);
     q += sz_cand;
@@ -6216,7 +6275,7 @@ int vpet_abc_infer_bank_learned(const float* tacs, int64_t n_voxels, const float
                  sz_bw = gp.out_bank_logw ? 0 : a256(sizeof(double) * rows_c),
                  sz_b = mfma ? a256(sizeof(uint16_t) * (size_t)KB * rows_c) : 0;
     const size_t sz_tau = a256(sizeof(float) * cv), sz_cnt = a256(sizeof(int) * 2 * cv),
-                 sz_fb = a256(sizeof(int) * cv) + 256, sz_cand = a256(sizeof(uint64_t) * (size_t)cap * cv),
+                 sz_fb = fallback_bytes(cv, (int)n_acc), sz_cand = a256(sizeof(uint64_t) * (size_t)cap * cv),
                  sz_a = mfma ? a256(sizeof(uint16_t) * (size_t)KB * cv) : 0, sz_c = mfma ? a256(sizeof(float) * cv) : 0,
                  sz_av = mfma ? a256(sizeof(double) * cv) : 0;
     const size_t total = sz_key + sz_zm + sz_hist + sz_perm + sz_ys + sz_ws + sz_grp + sz_tot + sz_ref + sz_bt + sz_bx +
@@ -6317,11 +6376,7 @@ int vpet_abc_infer_bank_learned(const float* tacs, int64_t n_voxels, const float
     B.tau = reinterpret_cast<float*>(carve(sz_tau));
     B.cnt = reinterpret_cast<int*>(carve(sz_cnt));
     B.cnt_hi = B.cnt + cv;
-    {
-        char* fb = carve(sz_fb);
-        B.fb_count = reinterpret_cast<unsigned*>(fb);
-        B.fb_list = reinterpret_cast<int*>(fb + 256);
-    }
+    fallback_carve(carve(sz_fb), cv, B);
     B.cand = reinterpret_cast<uint64_t*>(carve(sz_cand));
     if (mfma) {
         B.ahi = reinterpret_cast<uint16_t*>(carve(sz_a));
