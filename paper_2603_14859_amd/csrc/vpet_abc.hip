@@ -506,6 +506,73 @@ __device__ __forceinline__ void simulate_draws(const Tab& T, int F, int k0, Draw
     }
 }
 
+// FP64 log and exp for the proposal draws and the lp-ntPET activation, from
+// their series (within 1 ulp of the library functions, at about a third of their
+// instructions):
+//   log x = e ln 2 + 2 atanh(s), x = m 2^e, m in [1/sqrt 2, sqrt 2),
+//           s = (m - 1)/(m + 1), atanh by its odd series to s^23 (|s| < 0.172);
+//   exp z = 2^k e^r, k = rint(z log2 e), r = z - k ln 2 (|r| <= 0.347), e^r by
+//           its Taylor series to r^13;
+// ln 2 is split into hi = ln 2 rounded to float (k hi exact) and lo = the rest.
+// log_pos needs a finite x > 0; with RCP its quotient is the refined hardware
+// reciprocal's (within an ulp) instead of the IEEE division's.
+constexpr double kLn2Hi = 0.693147182464599609375, kLn2Lo = -1.9046542999577693e-09;
+
+template <bool RCP = false>
+__device__ __forceinline__ double log_pos(double x) {
+    int e;
+    double m = frexp(x, &e);
+    if (m < 0.70710678118654752) {
+        m *= 2.0;
+        e -= 1;
+    }
+    double s;
+    if (RCP) {
+        double r = __builtin_amdgcn_rcp(m + 1.0);
+        r = fma(r, fma(-(m + 1.0), r, 1.0), r);
+        r = fma(r, fma(-(m + 1.0), r, 1.0), r);
+        s = (m - 1.0) * r;
+    } else {
+        s = (m - 1.0) / (m + 1.0);
+    }
+    const double s2 = s * s;
+    double p = 1.0 / 23.0;
+    p = fma(p, s2, 1.0 / 21.0);
+    p = fma(p, s2, 1.0 / 19.0);
+    p = fma(p, s2, 1.0 / 17.0);
+    p = fma(p, s2, 1.0 / 15.0);
+    p = fma(p, s2, 1.0 / 13.0);
+    p = fma(p, s2, 1.0 / 11.0);
+    p = fma(p, s2, 1.0 / 9.0);
+    p = fma(p, s2, 1.0 / 7.0);
+    p = fma(p, s2, 1.0 / 5.0);
+    p = fma(p, s2, 1.0 / 3.0);
+    const double lm = fma(2.0 * s, s2 * p, 2.0 * s);
+    const double de = (double)e;
+    return fma(de, kLn2Hi, fma(de, kLn2Lo, lm));
+}
+
+__device__ __forceinline__ double exp_series(double z) {
+    const double k = rint(z * 1.4426950408889634);
+    double r = fma(-k, kLn2Hi, z);
+    r = fma(-k, kLn2Lo, r);
+    double p = 1.0 / 6227020800.0;  // 1/13!
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)k);
+}
+
 // ---------------------------------------------------------------------------
 // lp-ntPET (Eq. (3)-(4)) as the ODE C_t' = R1 C_r' + k2 C_r - kappa(t) C_t with
 // kappa = k2a + gamma g(t): with C_t = R1 C_r + z, z' = (k2 - R1 kappa) C_r -
@@ -535,6 +602,22 @@ __device__ __forceinline__ StepW step_weights(double kappa, double h) {
     return w;
 }
 
+// The same for 0 <= x <= 0.3 from the one series of b/h: c = x (1 - x b/h), and a/h
+// = (c (1 + x) - x)/x^2 = 1 - (1 + x) b/h, neither with cancellation (no
+// exponential, no division).
+__device__ __forceinline__ StepW step_weights_small(double kappa, double h) {
+    const double x = kappa * h, bh = b_over_h_small(x);
+    StepW w;
+    w.e = fma(-x, fma(-x, bh, 1.0), 1.0);
+    w.a = h * fma(-(1.0 + x), bh, 1.0);
+    w.b = h * bh;
+    return w;
+}
+
+// Bound by the FP64 vector ALU: an active step was about 250 instructions with
+// the library's log, exp, expm1 and a division, and is about 110 with the
+// series; 200,000 lp-ntPET rows of 450 steps 671 -> 387 us (3.05 wavefronts per
+// SIMD, so the SIMDs with four set the time).
 template <class Sink>
 __device__ void simulate_lpnt(const float* th, const Tab& T, int F, int k0, double h, Sink& sink) {
     const double R1 = th[0], k2 = th[1], k2a = th[2], gam = th[3], tD = th[4], tP = th[5], alpha = th[6];
@@ -552,8 +635,9 @@ __device__ void simulate_lpnt(const float* th, const Tab& T, int F, int k0, doub
         const double tm = ((double)k + 0.5) * h;
         if (tm > tD) {
             const double sv = (tm - tD) * rspan;
-            const double kap = k2a + gam * exp(alpha * (log(sv) + 1.0 - sv));
-            const StepW w = step_weights(kap, h);
+            const double kap = k2a + gam * exp_series(alpha * (log_pos<true>(sv) + 1.0 - sv));
+            const StepW w = __ballot(!(kap * h >= 0.0 && kap * h <= 0.3)) == 0ull ? step_weights_small(kap, h)
+                                                                                  : step_weights(kap, h);
             z = fma(w.e, z, (k2 - R1 * kap) * fma(w.a, c_prev, w.b * c_next));
         } else {
             z = fma(w0.e, z, src0 * fma(w0.a, c_prev, w0.b * c_next));
@@ -3661,61 +3745,6 @@ __device__ __forceinline__ void mix_table(const float* o, MixTab& t, double shar
         t.log_rest = log1p(-share);
         t.logvol = logvol;
     }
-}
-
-// FP64 log and exp for the proposal draws, from their series (within 1 ulp
-// of the library functions, at about a third of their instructions):
-//   log x = e ln 2 + 2 atanh(s), x = m 2^e, m in [1/sqrt 2, sqrt 2),
-//           s = (m - 1)/(m + 1), atanh by its odd series to s^23 (|s| < 0.172);
-//   exp z = 2^k e^r, k = rint(z log2 e), r = z - k ln 2 (|r| <= 0.347), e^r by
-//           its Taylor series to r^13;
-// ln 2 is split into hi = ln 2 rounded to float (k hi exact) and lo = the rest.
-// log_pos needs a finite x > 0.
-constexpr double kLn2Hi = 0.693147182464599609375, kLn2Lo = -1.9046542999577693e-09;
-
-__device__ __forceinline__ double log_pos(double x) {
-    int e;
-    double m = frexp(x, &e);
-    if (m < 0.70710678118654752) {
-        m *= 2.0;
-        e -= 1;
-    }
-    const double s = (m - 1.0) / (m + 1.0), s2 = s * s;
-    double p = 1.0 / 23.0;
-    p = fma(p, s2, 1.0 / 21.0);
-    p = fma(p, s2, 1.0 / 19.0);
-    p = fma(p, s2, 1.0 / 17.0);
-    p = fma(p, s2, 1.0 / 15.0);
-    p = fma(p, s2, 1.0 / 13.0);
-    p = fma(p, s2, 1.0 / 11.0);
-    p = fma(p, s2, 1.0 / 9.0);
-    p = fma(p, s2, 1.0 / 7.0);
-    p = fma(p, s2, 1.0 / 5.0);
-    p = fma(p, s2, 1.0 / 3.0);
-    const double lm = fma(2.0 * s, s2 * p, 2.0 * s);
-    const double de = (double)e;
-    return fma(de, kLn2Hi, fma(de, kLn2Lo, lm));
-}
-
-__device__ __forceinline__ double exp_series(double z) {
-    const double k = rint(z * 1.4426950408889634);
-    double r = fma(-k, kLn2Hi, z);
-    r = fma(-k, kLn2Lo, r);
-    double p = 1.0 / 6227020800.0;  // 1/13!
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    return ldexp(p, (int)k);
 }
 
 // ---------------------------------------------------------------------------
