@@ -2012,8 +2012,9 @@ struct BankArgs {
     unsigned n_tot, n_draws, n_acc, n_pilot;
     int kinds[kMaxModels];
     float* tau;             // [V] pilot threshold (fp32 distance), NaN for an invalid voxel
-    int* cnt;               // [V] candidates found (may exceed cap)
-    int* cnt_hi;            // [V] of them, in the second half of the list (the rest are at its start)
+    int* cnt;               // [V] candidates found (may exceed cap; contraction scan: only -1 = invalid voxel)
+    int* cnt_part;          // [V][2 splits] contraction scan: candidates of each piece of the list
+    int splits;             // blocks that share the rows of 256 voxels (ordered scan), each its tiles mod splits
     uint64_t* cand;         // [V][cap] candidate keys
     int* fb_list;           // [V] voxels whose candidate list cannot certify the top n
     unsigned* fb_count;     // [1] entries in fb_list
@@ -2069,10 +2070,33 @@ __device__ __forceinline__ long long bank_voxel(const BankArgs& P, long long row
 __device__ __forceinline__ long long bank_out_row(const BankArgs& P, long long row) {
     return P.out_row ? (long long)P.out_row[P.pos0 + row] : row;
 }
-// Position in a voxel's list of its j-th candidate (c0 of them at the start,
-// the rest from the middle on).
-__device__ __forceinline__ int cand_slot(const BankArgs& P, int j, int c0) {
-    return j < c0 ? j : (P.cap >> 1) + (j - c0);
+// A voxel's list of the contraction scan: 2 splits pieces of cap / (2 splits)
+// entries.  first[k]: candidates before piece k (of at most kMaxSplits blocks).
+constexpr int kMaxSplits = 4;
+struct CandPieces {
+    int first[2 * kMaxSplits];
+    int total, len;
+    bool full;  // a piece overflowed
+    __device__ __forceinline__ int slot(int j) const {
+        int s = j;
+#pragma unroll
+        for (int k = 1; k < 2 * kMaxSplits; ++k) s = j >= first[k] ? j - first[k] + k * len : s;
+        return s;
+    }
+};
+// (a wavefront; n = this lane's piece count, 0 past the pieces)
+__device__ __forceinline__ CandPieces cand_pieces(const BankArgs& P, int n) {
+    CandPieces c;
+    c.len = (int)((unsigned)P.cap / (2u * (unsigned)P.splits));
+    c.full = __ballot(n > c.len) != 0ull;
+    int at = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * kMaxSplits; ++k) {
+        c.first[k] = k < 2 * P.splits ? at : 0x7FFFFFFF;
+        at += __builtin_amdgcn_readlane(n, k);
+    }
+    c.total = at;
+    return c;
 }
 
 // Per-lane observed curve and weights of voxel `row` (a lane per voxel).
@@ -2222,10 +2246,7 @@ __global__ __launch_bounds__(256) void vpet_bank_scan_kernel(BankArgs P) {
                 ++c;
             }
         }
-        if (live) {
-            P.cnt[row] = valid ? c : -1;
-            P.cnt_hi[row] = 0;
-        }
+        if (live) P.cnt[row] = valid ? c : -1;
     }
 }
 
@@ -2710,14 +2731,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void vp
     if (row >= P.V) return;
     // the voxel's scalars and (RECOMPUTE) its TAC value of this lane's frame,
     // loaded together: the kernel is bound by the latency of such round trips
-    const int c = P.cnt[row];
-    const int c_hi = RECOMPUTE ? P.cnt_hi[row] : 0;
+    int c = P.cnt[row];
+    const int piece = RECOMPUTE && lane_id() < 2 * P.splits ? P.cnt_part[row * (2 * P.splits) + lane_id()] : 0;
     const float tau = P.tau[row];
     const float tau1 = RECOMPUTE ? P.tau1[row] : 0.0f, cthr1 = RECOMPUTE ? P.cthr1[row] : 0.0f;
     const float y_lane = (RECOMPUTE && lane_id() < P.F) ? P.tacs[(size_t)bank_voxel(P, row) * P.F + lane_id()] : 0.0f;
     if (c < 0) {
         bank_invalid(P, row);
         return;
+    }
+    CandPieces list{};
+    if (RECOMPUTE) {
+        list = cand_pieces(P, piece);
+        c = list.full ? P.cap + 1 : list.total;
     }
     if (c < (int)P.n_acc || c > P.cap) {
         if (threadIdx.x == 0) P.fb_list[atomicAdd(P.fb_count, 1u)] = (int)row;
@@ -2736,7 +2762,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void vp
         wave_curve_lds<LD, L1>(P, row, y_lane, Ys, Ws);
         uint32_t* queue = reinterpret_cast<uint32_t*>(Ws + LD);  // 2 x 64 rows
         const uint64_t* src = P.cand + (size_t)row * P.cap;
-        const int c0 = c - c_hi;
         const int lane = lane_id(), part = lane & 3;
         constexpr int Q = LD / 4;
         double Yq[Q], Wq[Q];  // this lane's quarter of the curve and weights
@@ -2793,7 +2818,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void vp
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int j = j0 + u * kWave + lane;
-                    e[u] = j < c ? src[cand_slot(P, j, c0)] : 0ull;
+                    e[u] = j < c ? src[list.slot(j)] : 0ull;
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -2842,8 +2867,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void vp
         }
     } else {
         const uint64_t* src = P.cand + (size_t)row * P.cap;
-        const int c0 = c - P.cnt_hi[row];
-        for (int j = lane_id(); j < c; j += kWave) keys[j] = src[cand_slot(P, j, c0)];
+        for (int j = lane_id(); j < c; j += kWave) keys[j] = src[j];
         below = c;
     }
     if (below < (int)P.n_acc) {
@@ -2960,7 +2984,6 @@ __global__ __launch_bounds__(256) void vpet_bank_passall_kernel(BankArgs P) {
     const double a = P.aval[v];
     P.cthr[v] = a == a ? __builtin_inff() : -__builtin_inff();
     P.cnt[v] = a == a ? 0 : -1;
-    P.cnt_hi[v] = 0;
 }
 
 // vpet_abc_bank_screen: voxel `blockIdx.x`'s candidates (computed S, bank row)
@@ -2971,11 +2994,11 @@ __global__ __launch_bounds__(256) void vpet_bank_scatter_kernel(BankArgs P, floa
     for (unsigned j = threadIdx.x; j < P.n_tot; j += blockDim.x) dst[j] = __builtin_nanf("");
     if (threadIdx.x == 0) out_a[v] = P.aval[v];
     __syncthreads();
-    const int c = P.cnt[v];
-    const int c0 = c - P.cnt_hi[v];
+    if (P.cnt[v] < 0) return;
+    const int c0 = P.cnt_part[2 * v], c = c0 + P.cnt_part[2 * v + 1];  // (one block per voxel: two pieces)
     const uint64_t* src = P.cand + (size_t)v * P.cap;
     for (int j = threadIdx.x; j < c && j < P.cap; j += blockDim.x) {
-        const uint64_t e = src[cand_slot(P, j, c0)];
+        const uint64_t e = src[j < c0 ? j : (P.cap >> 1) + (j - c0)];
         const uint32_t g = (uint32_t)e;
         if (g < P.n_tot) dst[g] = __uint_as_float((uint32_t)(e >> 32));
     }
@@ -3152,8 +3175,8 @@ __host__ __device__ constexpr double contraction_rel_err() {
 // every row whose exact distance is <= tau_v is a candidate.  A voxel's list
 // has two halves of cap / 2 entries, one per half-wavefront: each lane appends
 // its voxel's candidates to its own half with a count in a register, so a
-// candidate costs no cross-lane work.  cnt = both halves' count (cap + 1 when
-// either half overflowed), cnt_hi = the second half's.
+// candidate costs no cross-lane work; cnt_part holds the halves' counts (beyond the
+// half's length when it overflowed).
 //
 // ORDERED (SCAN only; bank operands in an order whose tiles hold similar rows,
 // voxels likewise): a tile is visited only if some voxel of the block may have a
@@ -3164,7 +3187,9 @@ __host__ __device__ constexpr double contraction_rel_err() {
 // the error bound above at t = q^2.  sum w R^2 is one bf16 product of w's hi part
 // and R^2 rounded up, times 1.0041 (w <= w_hi (1 + 2^-8)).  Tiles are taken in
 // segments of kSegTiles: their centres are tested first, 64 at a time, then the
-// needed ones are scanned.
+// needed ones are scanned.  The number of needed tiles differs between blocks
+// (neighbouring cells are not equally dense), so with few blocks each 256 voxels'
+// tiles are dealt to `splits` of them, each with its own pieces of the lists.
 constexpr int kSegTiles = 2048;
 template <int K, bool PILOT, bool ORDERED = false>
 __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
@@ -3174,10 +3199,10 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
     constexpr int CA = TR * K / 8;        // 16-byte chunks per array (hi or lo) per tile
     constexpr int CPT = (2 * CA + 511) / 512;  // chunks per thread and tile
     static_assert(CA % 64 == 0 && CPT <= 3, "whole wavefronts per array, at most three chunks per thread");
-    static_assert(kSegTiles == 32 * kWave, "a mask word per lane");
+    static_assert(kSegTiles == 32 * kWave, "a mask word per lane, eight per thread of the block");
     __shared__ __align__(16) unsigned char tile[2][2][TR * RS];
-    __shared__ uint32_t rowid[ORDERED ? 2 : 1][ORDERED ? TR : 1];
-    __shared__ uint32_t mask[ORDERED ? kSegTiles / 32 : 1];
+    __shared__ uint32_t rowid[ORDERED ? 2 : 1][ORDERED ? TR : 1];  // bank rows of the staged tiles
+    __shared__ uint32_t mask[ORDERED ? 8 : 1][ORDERED ? kSegTiles / 32 : 1];  // tiles that each wavefront needs
     __shared__ uint16_t list[ORDERED ? kSegTiles : 1];
     __shared__ int listed;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -3208,21 +3233,23 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
     // SCAN: this lane's half of its voxel's list, as byte offsets from the
     // block's first list (256 lists of at most 8192 entries: 32 bits suffice):
     // its start, its last entry and the next free entry
-    const unsigned hcap = (unsigned)P.cap >> 1;
+    const unsigned splits = ORDERED ? (unsigned)P.splits : 1u, split = ORDERED ? blockIdx.y : 0u;
+    const unsigned hcap = (unsigned)P.cap / (2u * splits);
     unsigned char* blist = reinterpret_cast<unsigned char*>(P.cand + (size_t)vbase * (size_t)P.cap);
-    const unsigned loff = ((unsigned)(wave * 32 + (lane & 31)) * (unsigned)P.cap + half * hcap) * 8u;
+    const unsigned loff = ((unsigned)(wave * 32 + (lane & 31)) * (unsigned)P.cap + (2u * split + half) * hcap) * 8u;
     const unsigned llast = loff + (hcap - 1u) * 8u;
     unsigned lnext = loff;
 
     // PILOT: ceil(n_pilot / TR) tiles spread evenly over the bank (it is
     // ordered by model, so a prefix would see one model only)
     const unsigned n_rows = P.n_tot;
-    const unsigned all_tiles = (n_rows + TR - 1) / TR;
+    // (ORDERED: of this block's share, tile t of it is tile t splits + split)
+    const unsigned all_tiles = ((n_rows + TR - 1) / TR + splits - 1u - split) / splits;
     const unsigned pilot_tiles = (P.n_pilot + TR - 1) / TR;
     unsigned ntiles = (PILOT && pilot_tiles < all_tiles) ? pilot_tiles : all_tiles;
     unsigned seg0 = 0;  // ORDERED: first tile of the segment whose list is scanned
     auto tile_row0 = [&](unsigned t) {
-        if (ORDERED) return (seg0 + list[t]) * (unsigned)TR;
+        if (ORDERED) return ((seg0 + list[t]) * splits + split) * (unsigned)TR;
         return (PILOT ? (unsigned)(((uint64_t)t * all_tiles) / ntiles) : t) * (unsigned)TR;
     };
     // this thread's 16-byte chunks of a tile: array (hi/lo; CA is a multiple of
@@ -3301,28 +3328,34 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
                 stash(buf ^ 1);
                 if (t + 2 < ntiles) fetch(t + 2);
             }
-            f32x16_t acc0 = {}, acc1 = {};
-    #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int off = (lane & 31) * RS + (ks * 16 + half * 8) * 2;
-                const unsigned char* hi = &tile[buf][0][0];
-                const unsigned char* lo = hi + TR * RS;
-                const bf16x8_t bh0 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(hi + off));
-                const bf16x8_t bl0 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(lo + off));
-                const bf16x8_t bh1 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(hi + 32 * RS + off));
-                const bf16x8_t bl1 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(lo + 32 * RS + off));
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh0, ah[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh1, ah[ks], acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl0, ah[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl1, ah[ks], acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh0, al[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh1, al[ks], acc1, 0, 0, 0);
+            // (ORDERED: a wavefront whose own voxels do not need the tile goes on)
+            const bool wanted =
+                !ORDERED || ((__builtin_amdgcn_readfirstlane((int)mask[wave][list[t] >> 5]) >> (list[t] & 31u)) & 1) != 0;
+            if (wanted) {
+                f32x16_t acc0 = {}, acc1 = {};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int off = (lane & 31) * RS + (ks * 16 + half * 8) * 2;
+                    const unsigned char* hi = &tile[buf][0][0];
+                    const unsigned char* lo = hi + TR * RS;
+                    const bf16x8_t bh0 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(hi + off));
+                    const bf16x8_t bl0 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(lo + off));
+                    const bf16x8_t bh1 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(hi + 32 * RS + off));
+                    const bf16x8_t bl1 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(lo + 32 * RS + off));
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh0, ah[ks], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh1, ah[ks], acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl0, ah[ks], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl1, ah[ks], acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh0, al[ks], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh1, al[ks], acc1, 0, 0, 0);
+                }
+                if constexpr (K <= 64) __builtin_amdgcn_s_setprio(0);
+                const unsigned r0 = ORDERED ? 0u : tile_row0(t);
+                screen(acc0, r0, t * TR, rowid[ORDERED ? buf : 0]);
+                screen(acc1, r0 + kMfmaRows, t * TR + kMfmaRows, rowid[ORDERED ? buf : 0] + (ORDERED ? kMfmaRows : 0));
+            } else if constexpr (K <= 64) {
+                __builtin_amdgcn_s_setprio(0);
             }
-            if constexpr (K <= 64) __builtin_amdgcn_s_setprio(0);
-            const unsigned r0 = ORDERED ? 0u : tile_row0(t);
-            const uint32_t* ids = ORDERED ? rowid[buf] : nullptr;
-            screen(acc0, r0, t * TR, ids);
-            screen(acc1, r0 + kMfmaRows, t * TR + kMfmaRows, ids + (ORDERED ? kMfmaRows : 0));
             __syncthreads();
         }
     };
@@ -3337,14 +3370,14 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
         const bool all = live && !(cth < __builtin_inff() && root < 1e18f);  // no threshold: every tile
         for (seg0 = 0; seg0 < all_tiles; seg0 += kSegTiles) {
             const unsigned nseg = min((unsigned)kSegTiles, all_tiles - seg0);
-            for (int q = tid; q < kSegTiles / 32; q += 512) mask[q] = 0u;
+            mask[tid / (kSegTiles / 32)][tid % (kSegTiles / 32)] = 0u;
             for (unsigned c0 = 0; c0 < nseg; c0 += TR) {
                 __syncthreads();  // the previous centres have been read, the mask is clear
                 for (int e = tid; e < 3 * CA; e += 512) {
                     const int arr = e / CA, rem = e - arr * CA, r = rem / (K / 8), col = rem - r * (K / 8);
                     const uint16_t* src = arr == 0 ? P.chi : (arr == 1 ? P.clo : P.rad);
                     uint4 x = make_uint4(0, 0, 0, 0);
-                    if (c0 + r < nseg) x = *reinterpret_cast<const uint4*>(src + (size_t)(seg0 + c0 + r) * K + col * 8);
+                    if (c0 + r < nseg) x = *reinterpret_cast<const uint4*>(src + (size_t)((seg0 + c0 + r) * splits + split) * K + col * 8);
                     *reinterpret_cast<uint4*>(&tile[arr >> 1][arr & 1][0] + r * RS + col * 16) = x;
                 }
                 __syncthreads();
@@ -3373,12 +3406,14 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
                         const int t0 = 8 * (r >> 2) + (r & 3);
                         need |= ((uint32_t)hit != 0u ? 1u << t0 : 0u) | ((uint32_t)(hit >> 32) != 0u ? 16u << t0 : 0u);
                     }
-                    if (lane == 0 && need != 0u) atomicOr(&mask[c0 / 32 + hf], need);
+                    if (lane == 0) mask[wave][c0 / 32 + hf] = need;
                 }
             }
             __syncthreads();
             if (wave == 0) {  // the needed tiles in order
-                uint32_t w = mask[lane];
+                uint32_t w = 0u;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) w |= mask[q][lane];
                 const unsigned first = (unsigned)lane * 32u;
                 if (first + 32u > nseg) w = first >= nseg ? 0u : w & ((1u << (nseg - first)) - 1u);
                 int at = __popc(w);
@@ -3456,11 +3491,7 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
             }
         }
     } else {
-        const unsigned cnt = (lnext - loff) >> 3, other = __shfl_xor(cnt, 32, kWave);
-        if (half == 0 && v < P.V && cth > -__builtin_inff()) {
-            P.cnt[v] = (cnt > hcap || other > hcap) ? P.cap + 1 : (int)(cnt + other);
-            P.cnt_hi[v] = (int)other;
-        }
+        if (v < P.V) P.cnt_part[v * (2u * splits) + 2u * split + half] = (int)((lnext - loff) >> 3);
     }
 }
 
@@ -3471,7 +3502,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
     bank_mfma_body<K, PILOT, ORDERED>(P);
 }
 template <int K, bool PILOT, bool ORDERED>
-__global__ __launch_bounds__(512) void vpet_bank_mfma_wide_kernel(BankArgs P) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(ORDERED ? 4 : 1))) void vpet_bank_mfma_wide_kernel(BankArgs P) {
     bank_mfma_body<K, PILOT, ORDERED>(P);
 }
 
@@ -3491,7 +3522,9 @@ void launch_mfma(dim3 grid, hipStream_t st, const BankArgs& Q) {
 // deviations on the irreversible-2TCM bank) and, recursively by quantiles, 32 x
 // 8 x 4 cells; rows and voxels are then counting-sorted by cell along a
 // serpentine walk.  Of 1563 tiles a 256-voxel block needs 7 % (irreversible 2TCM,
-// 30 frames), of MRTM / lp-ntPET's 6250 25 %.
+// 30 frames), of MRTM / lp-ntPET's 6250 25 %: 262,144 voxels x 100k rows, scan 8.65
+// -> 1.33 ms and the call 11.7 -> 4.3 ms; 65,536 x 400k rows (40 frames) 12.6 -> 4.3
+// ms and 15.9 -> 9.0 ms.
 // ---------------------------------------------------------------------------
 constexpr int kOrdDirs = 3, kOrdCov = 512, kOrdSample = 2048;
 constexpr int kOrd1 = 32, kOrd2 = 8, kOrd3 = 4, kOrdCells = kOrd1 * kOrd2 * kOrd3;
@@ -5908,6 +5941,13 @@ bool order_pays(int64_t n_voxels, int64_t n_tot) {
     return n_voxels >= 8192 && n_tot >= 16384 && (double)n_voxels * (double)n_tot >= 3e9;
 }
 
+// Blocks per 256 voxels of an ordered scan: the needed tiles vary from block to
+// block, so about 2048 of them (four per resident one) even the CUs' loads out.
+int order_splits(long long voxels) {
+    const long long blocks = (voxels + kMfmaVox - 1) / kMfmaVox;
+    return blocks >= 2048 ? 1 : (blocks >= 1024 ? 2 : kMaxSplits);
+}
+
 // Scratch of the exact fallback: count, parts done, list of up to cv voxels,
 // the parts' keys.
 size_t fallback_bytes(long long cv, int n) {
@@ -5998,7 +6038,7 @@ template <class Mark>
 void bank_chunk(const BankArgs& Q, hipStream_t st, int ld, bool l1, bool mfma, size_t lds, size_t fb_lds,
                 int fb_waves, Mark& mark, const BankOrder* ord = nullptr) {
     const dim3 lanes((unsigned)((Q.V + 255) / 256)), b256(256), per_voxel((unsigned)Q.V), b64(64);
-    const dim3 mblocks((unsigned)((Q.V + kMfmaVox - 1) / kMfmaVox));
+    const dim3 mblocks((unsigned)((Q.V + kMfmaVox - 1) / kMfmaVox)), oblocks(mblocks.x, (unsigned)Q.splits);
     const dim3 fb_grid((unsigned)std::min<long long>(Q.V * kFbParts, kFbGrid)), fb_block(64 * fb_waves), resets((kFbGrid + 255) / 256);
 #define VPET_BANK_LAUNCH(LDV, L1V)                                                                        \
     do {                                                                                                  \
@@ -6009,7 +6049,7 @@ void bank_chunk(const BankArgs& Q, hipStream_t st, int ld, bool l1, bool mfma, s
             launch_mfma<2 * LDV, true>(mblocks, st, ord ? ord->pilot(Q) : Q);                             \
             mark(0);                                                                                      \
             if (ord)                                                                                      \
-                launch_mfma<2 * LDV, false, true>(mblocks, st, Q);                                        \
+                launch_mfma<2 * LDV, false, true>(oblocks, st, Q);                                        \
             else                                                                                          \
                 launch_mfma<2 * LDV, false>(mblocks, st, Q);                                              \
             mark(1);                                                                                      \
@@ -6467,13 +6507,14 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     const long long cv = std::min<long long>(n_voxels, chunk);
     const int KB = 2 * ld;  // contraction length: [x, x^2] per frame
     char* work = nullptr;
-    const size_t sz_tau = align256(sizeof(float) * cv), sz_cnt = align256(sizeof(int) * 2 * cv);
+    const bool ordered = use_mfma && order_pays(n_voxels, n_tot);
+    A.splits = ordered ? order_splits(cv) : 1;
+    const size_t sz_tau = align256(sizeof(float) * cv), sz_cnt = align256(sizeof(int) * (1 + 2 * (size_t)A.splits) * cv);
     const size_t sz_fb = fallback_bytes(cv, (int)n_acc), sz_cand = align256(cand_bytes * (size_t)cap * cv);
     const size_t sz_b = use_mfma ? align256(sizeof(uint16_t) * (size_t)KB * n_tot) : 0;
     const size_t sz_a = use_mfma ? align256(sizeof(uint16_t) * (size_t)KB * cv) : 0;
     const size_t sz_c = use_mfma ? align256(sizeof(float) * cv) : 0;
     const size_t sz_av = use_mfma ? align256(sizeof(double) * cv) : 0;
-    const bool ordered = use_mfma && order_pays(n_voxels, n_tot);
     const size_t n_tiles = ((size_t)n_tot + 63) / 64, n_keys = (size_t)std::max<long long>(n_tot, cv);
     const size_t sz_tree = align256(sizeof(OrderTree)), sz_key = align256(sizeof(unsigned) * n_keys);
     const size_t sz_hist = align256(sizeof(int) * ((n_keys + kLbBlock - 1) / kLbBlock) * (kOrdCells + 1));
@@ -6487,7 +6528,7 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     A.tau = reinterpret_cast<float*>(q);
     q += sz_tau;
     A.cnt = reinterpret_cast<int*>(q);
-    A.cnt_hi = A.cnt + cv;
+    A.cnt_part = A.cnt + cv;
     q += sz_cnt;
     fallback_carve(q, cv, A);
     q += sz_fb;
@@ -6711,7 +6752,7 @@ int vpet_abc_infer_bank_learned(const float* tacs, int64_t n_voxels, const float
                  sz_bx = a256(sizeof(double) * (size_t)ld * rows_c),
                  sz_bw = gp.out_bank_logw ? 0 : a256(sizeof(double) * rows_c),
                  sz_b = mfma ? a256(sizeof(uint16_t) * (size_t)KB * rows_c) : 0;
-    const size_t sz_tau = a256(sizeof(float) * cv), sz_cnt = a256(sizeof(int) * 2 * cv),
+    const size_t sz_tau = a256(sizeof(float) * cv), sz_cnt = a256(sizeof(int) * 3 * cv),
                  sz_fb = fallback_bytes(cv, (int)n_acc), sz_cand = a256(sizeof(uint64_t) * (size_t)cap * cv),
                  sz_a = mfma ? a256(sizeof(uint16_t) * (size_t)KB * cv) : 0, sz_c = mfma ? a256(sizeof(float) * cv) : 0,
                  sz_av = mfma ? a256(sizeof(double) * cv) : 0;
@@ -6812,7 +6853,8 @@ int vpet_abc_infer_bank_learned(const float* tacs, int64_t n_voxels, const float
     }
     B.tau = reinterpret_cast<float*>(carve(sz_tau));
     B.cnt = reinterpret_cast<int*>(carve(sz_cnt));
-    B.cnt_hi = B.cnt + cv;
+    B.cnt_part = B.cnt + cv;
+    B.splits = 1;
     fallback_carve(carve(sz_fb), cv, B);
     B.cand = reinterpret_cast<uint64_t*>(carve(sz_cand));
     if (mfma) {
@@ -7000,7 +7042,7 @@ int vpet_abc_bank_screen(const float* tacs, int64_t n_voxels, const float* frame
     if ((rc = upload_blob(*ctx, omega.data(), sizeof(double) * F, st, &dom, slot)) != VPET_OK) return rc;
     A.omega = static_cast<const double*>(dom);
     const size_t V = (size_t)n_voxels;
-    const size_t sz_cnt = align256(sizeof(int) * 2 * V), sz_cand = align256(sizeof(uint64_t) * (size_t)cap * V);
+    const size_t sz_cnt = align256(sizeof(int) * 3 * V), sz_cand = align256(sizeof(uint64_t) * (size_t)cap * V);
     const size_t sz_b = align256(sizeof(uint16_t) * (size_t)KB * (size_t)n_rows);
     const size_t sz_a = align256(sizeof(uint16_t) * (size_t)KB * V);
     const size_t sz_c = align256(sizeof(float) * V), sz_av = align256(sizeof(double) * V);
@@ -7009,7 +7051,8 @@ int vpet_abc_bank_screen(const float* tacs, int64_t n_voxels, const float* frame
     if (e != hipSuccess) return fail(VPET_E_NOMEM, "screen work: %s", hipGetErrorString(e));
     char* q = work;
     A.cnt = reinterpret_cast<int*>(q);
-    A.cnt_hi = A.cnt + V;
+    A.cnt_part = A.cnt + V;
+    A.splits = 1;
     q += sz_cnt;
     A.cand = reinterpret_cast<uint64_t*>(q);
     q += sz_cand;
