@@ -3131,6 +3131,7 @@ __global__ __launch_bounds__(256) void vpet_bank_aops_kernel(BankArgs P) {
     // the error bound assumes w >= 0: otherwise a_v = -inf makes every row a
     // candidate (the selection is then exact or falls back)
     P.aval[row] = wneg ? -__builtin_inf() : a;
+    P.cnt[row] = 0;  // valid (the scan counts in cnt_part)
 }
 
 // Error of the split contraction.  With A = A_hi + A_lo + e_A (|A_lo| and
