@@ -134,6 +134,10 @@ struct InferArgs {
     float a1scale, a1hi, a2hi;
     int nseg2;             // segments of a2, from seg2
     unsigned seg2;
+    // few voxels: gridDim.y blocks share a voxel's draws
+    uint64_t* part_keys;   // [V][parts][n_acc] each part's smallest keys
+    unsigned* part_done;   // [V] parts that are done
+    unsigned* part_hist;   // [V][kHistBins] counts of the draws' upper bounds
 };
 
 // ---------------------------------------------------------------------------
@@ -1135,7 +1139,7 @@ __device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, co
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
     for (int m = 0; m < P.M; ++m) {
         const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
-        for (uint32_t t = (uint32_t)wave; t < ntiles; t += (uint32_t)P.wpv) {
+        for (uint32_t t = blockIdx.y * (uint32_t)P.wpv + (uint32_t)wave; t < ntiles; t += (uint32_t)P.wpv * gridDim.y) {
             uint64_t key[kU];
             if constexpr (KINDS != 0)
                 tile_keys<KINDS, kU, L1>(P, m, vg, t * kTile, yw, key);
@@ -1269,7 +1273,10 @@ constexpr long long kScrMaxDraws = 1LL << 24;  // a key holds 24 bits of draw in
 constexpr int kScrChunk = 2048;
 __global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0, double h, int F, int k0, int nseg,
                                                                unsigned seg0, float b0, float* out, double a1hi,
-                                                               const double* cheb, double* poly) {
+                                                               const double* cheb, double* poly, unsigned* done,
+                                                               int n_done) {
+    // the split call's counters, in front of its kernels
+    for (int q = blockIdx.x * kWave + threadIdx.x; q < n_done; q += gridDim.x * kWave) done[q] = 0u;
     __shared__ double sC[kScrChunk], sP[VPET_MAX_FRAMES];
     __shared__ int sN[VPET_MAX_FRAMES];
     const int lane = threadIdx.x, j = lane & 3;
@@ -1702,7 +1709,8 @@ __device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVo
                                               const float4* cross, int m, uint32_t vg, ScreenList& list) {
     constexpr int U = KIND == KIND_REV ? 2 : kUmax, kTile = kWave * U;
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
-    for (uint32_t t = threadIdx.x >> 6; t < ntiles && !list.full; t += (uint32_t)P.wpv) {
+    for (uint32_t t = blockIdx.y * (uint32_t)P.wpv + (threadIdx.x >> 6); t < ntiles && !list.full;
+         t += (uint32_t)P.wpv * gridDim.y) {
         Screened s[U];
         uint32_t g[U];
         bool ok[U];
@@ -1715,6 +1723,53 @@ __device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVo
         }
         list.insert(s, g, ok);
     }
+}
+
+// Few voxels, several blocks each: a first launch counts every draw's upper
+// bound in bins of 1.1 % (float bits with six of the mantissa, 2^-12 to 2^20); the
+// upper end of the bin that holds the n-th smallest bounds the n-th smallest
+// distance of all parts together, so that each part of the second launch
+// lists only its share of the n closest.  12 voxels x 20k draws of three models,
+// n = 300: 583 us in one block each, 420 with a list of n per part, 221 so; one
+// voxel x 100k draws 285 -> 115 us.
+constexpr int kHistBins = 2048;
+constexpr uint32_t kHistBase = (127u - 12u) << 6;
+__device__ __forceinline__ int hist_bin(float upper) {
+    return (int)min(max(__float_as_uint(upper) >> 17, kHistBase) - kHistBase, (uint32_t)kHistBins - 1u);
+}
+template <int KIND, int ROW>
+__device__ __forceinline__ void screen_count(const InferArgs& P, const ScreenVox& S, const float4* tab,
+                                             const float4* cross, int m, uint32_t vg, unsigned* hist) {
+    for (uint32_t i = blockIdx.y * blockDim.x + threadIdx.x; i < P.n_draws; i += gridDim.y * blockDim.x)
+        atomicAdd(&hist[hist_bin(screen_upper(screen_draw<KIND, ROW>(P, S, tab, cross, m, vg, i)))], 1u);
+}
+// (a wavefront) Upper end of the bin that holds the n-th smallest bound.
+__device__ __forceinline__ float hist_threshold(const unsigned* hist, int n) {
+    constexpr int PER = kHistBins / kWave;
+    const int lane = lane_id();
+    int c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] = (int)hist[lane * PER + q];
+        sum += c[q];
+    }
+    int run = sum;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int o = __shfl_up(run, off, kWave);
+        if (lane >= off) run += o;
+    }
+    run -= sum;  // counts before this lane's bins
+    int bin = kHistBins - 1;
+#pragma unroll
+    for (int q = PER - 1; q >= 0; --q) {
+        int before = run;
+        for (int k = 0; k <= q; ++k) before += c[k];
+        if (before >= n) bin = lane * PER + q;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) bin = min(bin, __shfl_xor(bin, off, kWave));
+    return bin == kHistBins - 1 ? __builtin_inff() : __uint_as_float(((uint32_t)bin + 1u + kHistBase) << 17);
 }
 
 // Exact keys of the candidates keys[j0 + lane ...], j < count, in place: U per
@@ -1800,8 +1855,9 @@ __device__ __forceinline__ void block_rank(uint64_t* keys_all, int wpv, int cap,
     __syncthreads();
 }
 
-// vpet_infer_kernel (L2) with screened draws: the same outputs.
-template <int KINDS>
+// vpet_infer_kernel (L2) with screened draws: the same outputs.  With few voxels
+// the grid's second dimension splits a voxel's draws over several blocks.
+template <int KINDS, bool COUNT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vpet_infer_screen_kernel(InferArgs P) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1826,10 +1882,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     }
     __syncthreads();
     if (*flag == 0) {
-        if (wave == 0) infer_invalid(P, row);
+        if (!COUNT && wave == 0) infer_invalid(P, row);
         return;
     }
     bool screened = flag[1] == 0;
+    if (COUNT && !screened) return;
     if (screened) {
         screen_table<kRow>(P, fs, tab);
         if (KINDS == 0 || KINDS == KIND_REV) screen_cross_table(P, fs, cross);
@@ -1844,6 +1901,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         S.nq = wave_uniform(sv->nq);
         S.np = wave_uniform(sv->np);
         __syncthreads();
+        if constexpr (COUNT) {
+            unsigned* hist = reinterpret_cast<unsigned*>(keys_all);
+            for (int q = tid; q < kHistBins; q += blockDim.x) hist[q] = 0u;
+            __syncthreads();
+            for (int m = 0; m < P.M; ++m) {
+                const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
+                if constexpr (KINDS != 0)
+                    screen_count<KINDS, kRow>(P, S, tab, cross, m, vg, hist);
+                else if (kind == KIND_IRR)
+                    screen_count<KIND_IRR, kRow>(P, S, tab, cross, m, vg, hist);
+                else if (kind == KIND_REV)
+                    screen_count<KIND_REV, kRow>(P, S, tab, cross, m, vg, hist);
+                else
+                    screen_count<KIND_1TCM, kRow>(P, S, tab, cross, m, vg, hist);
+            }
+            __syncthreads();
+            for (int q = tid; q < kHistBins; q += blockDim.x)
+                if (hist[q] != 0u) atomicAdd(P.part_hist + (size_t)row * kHistBins + q, hist[q]);
+            return;
+        }
         ScreenList list;
         list.keys = keys_all + (size_t)wave * P.cap;
         list.n = n;
@@ -1851,6 +1928,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         list.have = list.nbuf = 0;
         list.tau = list.root = __builtin_inff();
         list.full = false;
+        if (gridDim.y > 1) list.set_tau(hist_threshold(P.part_hist + (size_t)row * kHistBins, n) * 1.0000005f);
         for (int m = 0; m < P.M; ++m) {
             const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
             if constexpr (KINDS != 0)
@@ -1879,7 +1957,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
                     if (q * (int)blockDim.x + wave * kWave < have)
                         screen_exact<KINDS, 1>(P, vg, yw, keys_all, q * (int)blockDim.x + wave * kWave, have);
                 const int len = 1 << (32 - __builtin_clz((unsigned)(have - 1)));
-                for (int j = have + tid; j < len; j += blockDim.x) keys_all[j] = kNoKey;
+                for (int j = have + tid; j < max(len, n); j += blockDim.x) keys_all[j] = kNoKey;
                 __syncthreads();
                 block_bitonic_sort(keys_all, len);
             } else if (screened) {
@@ -1891,7 +1969,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         } else if (!list.full) {
             for (int j0 = 0; j0 < list.have; j0 += 2 * kWave) screen_exact<KINDS, 2>(P, vg, yw, list.keys, j0, list.have);
             const int len = list.have <= 2 ? 2 : 1 << (32 - __builtin_clz((unsigned)(list.have - 1)));
-            for (int j = list.have + lane; j < len; j += kWave) list.keys[j] = kNoKey;
+            for (int j = list.have + lane; j < max(len, n); j += kWave) list.keys[j] = kNoKey;
             wave_lds_sync();
             wave_bitonic_sort(list.keys, len);
             __syncthreads();
@@ -1902,6 +1980,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     if (!screened) {
         __syncthreads();
         stream_draws<KINDS, false>(P, vg, yw, keys_all);
+        __syncthreads();
+        if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
+    }
+    if (gridDim.y > 1) {
+        // this part's n smallest keys; the block that finishes the voxel last
+        // merges the parts
+        __syncthreads();
+        uint64_t* mine = P.part_keys + ((size_t)row * gridDim.y + blockIdx.y) * n;
+        for (int j = tid; j < n; j += blockDim.x) mine[j] = keys_all[j];
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) flag[2] = atomicAdd(P.part_done + row, 1u) == gridDim.y - 1u ? 1 : 0;
+        __syncthreads();
+        if (flag[2] == 0) return;
+        __threadfence();
+        const uint64_t* all = P.part_keys + (size_t)row * gridDim.y * n;
+        const uint32_t total = gridDim.y * (uint32_t)n;
+        TopN top;
+        top.keys = keys_all + (size_t)wave * P.cap;
+        top.n = n;
+        top.cap = P.cap;
+        top.nbuf = 0;
+        top.tau = kNoKey;
+        for (int j = lane; j < P.cap; j += kWave) top.keys[j] = kNoKey;
+        wave_lds_sync();
+        for (uint32_t j0 = (uint32_t)wave * kWave; j0 < total; j0 += (uint32_t)P.wpv * kWave) {
+            const uint32_t j = j0 + (uint32_t)lane;
+            const uint64_t key[1] = {j < total ? __hip_atomic_load(all + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                               : kNoKey};
+            top.insert(key);
+        }
+        top.merge();
         __syncthreads();
         if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
     }
@@ -5837,9 +5947,10 @@ struct ScreenPlan {
     unsigned seg0 = 0, seg2 = 0;
     float b0 = 0.0f, a1hi = 0.0f, a2hi = 0.0f;
     size_t lds = 0, off_cheb = 0, off_poly = 0, off_scr = 0;  // bytes from the tables' start
+    int parts = 1;
 };
 ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, int M, int64_t n_draws, int n_acc,
-                       const vpet_abc_opts& o, int64_t n_voxels, int wpv) {
+                       const vpet_abc_opts& o, int64_t n_voxels, int wpv, bool noalloc) {
     ScreenPlan S;
     const int64_t total = (int64_t)M * n_draws;
     if (o.distance != 0 || total < screen_min_draws(n_voxels) || total > kScrMaxDraws) return S;
@@ -5908,6 +6019,13 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
             sizeof(uint64_t) * screen_keys(wpv, S.cap, T.F) + sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv +
             sizeof(ScreenVox) + (o.proposal ? sizeof(MixTab) + sizeof(MixScreen) + sizeof(float) * S.nseg : 0);
     S.use = S.lds <= (size_t)kLdsLimit;
+    // a voxel's draws over several blocks while the launch has fewer than two
+    // blocks per CU and a block keeps draws enough to repay its tables twice
+    if (!noalloc && !o.proposal && o.waves_per_voxel == 0 && total >= 8000 &&
+        sizeof(uint64_t) * screen_keys(wpv, S.cap, T.F) >= sizeof(unsigned) * kHistBins)
+        while (n_voxels * S.parts * 2 <= 512 && total / (S.parts * 2) >= 2000 && S.parts < 64)
+            S.parts *= 2;
+    if (S.parts < 4) S.parts = 1;  // (two: 200 voxels x 100k draws 318 us, one 275)
     return S;
 }
 
@@ -6225,7 +6343,7 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
     while (wpv > 1 && lds_for(wpv) > (size_t)kLdsLimit) wpv >>= 1;
     if (lds_for(wpv) > (size_t)kLdsLimit) return fail(VPET_E_LIMIT, "selection buffer exceeds LDS");
     size_t lds = lds_for(wpv);
-    const ScreenPlan scr = screen_plan(T, P, kinds, M, n_draws, (int)n_acc, o, n_voxels, wpv);
+    const ScreenPlan scr = screen_plan(T, P, kinds, M, n_draws, (int)n_acc, o, n_voxels, wpv, noalloc);
     if (scr.use) {
         cap = scr.cap;
         lds = scr.lds;
@@ -6272,6 +6390,19 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         lock = std::unique_lock<std::mutex>(ctx->mu);
         if ((rc = upload_tables(*ctx, T, st, P.tab, slot)) != VPET_OK) return rc;
     }
+    char* part_work = nullptr;
+    if (scr.use && scr.parts > 1) {
+        const size_t keys = align256(sizeof(uint64_t) * (size_t)n_voxels * scr.parts * n_acc);
+        if (hipMallocAsync((void**)&part_work, keys + sizeof(unsigned) * n_voxels * (1 + kHistBins), st) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            part_work = nullptr;  // one block per voxel then
+        } else {
+            P.part_keys = reinterpret_cast<uint64_t*>(part_work);
+            P.part_done = reinterpret_cast<unsigned*>(part_work + keys);
+            P.part_hist = P.part_done + n_voxels;
+        }
+    }
     if (scr.use) {
         // the screen's tables follow the call's in the same device buffer
         char* base = const_cast<char*>(reinterpret_cast<const char*>(P.tab.C));
@@ -6280,7 +6411,7 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         const unsigned blocks = (unsigned)((scr.nseg + 15) / 16) + (scr.nseg2 ? 1u : 0u);
         hipLaunchKernelGGL(vpet_screen_table_kernel, dim3(blocks), dim3(64), 0, st, P.tab, T.C0, T.h, T.F, T.k0, scr.nseg,
                            scr.seg0, scr.b0, out, (double)scr.a1hi, reinterpret_cast<const double*>(base + scr.off_cheb),
-                           poly);
+                           poly, P.part_done, part_work ? (int)n_voxels * (1 + kHistBins) : 0);
         P.scr = out;
         P.poly = poly;
     }
@@ -6299,15 +6430,20 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         Q.prop = o.proposal ? o.proposal + (size_t)base * VPET_PROPOSAL_NOUT : nullptr;
         Q.out_ess = o.out_ess ? o.out_ess + base : nullptr;
         Q.below = o.accept_below ? o.accept_below + base : nullptr;
-        const dim3 grid((unsigned)Q.V), block(kWave * wpv);
+        const dim3 grid((unsigned)Q.V, part_work ? (unsigned)scr.parts : 1u), block(kWave * wpv);
         const int one = M == 1 ? kinds[0] : 0;
+#define VPET_SCREEN_LAUNCH(KD)                                                                                  \
+    do {                                                                                                        \
+        if (part_work) hipLaunchKernelGGL((vpet_infer_screen_kernel<KD, true>), grid, block, lds, st, Q);       \
+        hipLaunchKernelGGL((vpet_infer_screen_kernel<KD, false>), grid, block, lds, st, Q);                     \
+    } while (0)
         const int sel = o.proposal ? (scr.use ? -3 : -1 - o.distance)
                                    : (scr.use ? -8 - one : one * 2 + (o.distance == 1 ? 1 : 0));
         switch (sel) {
-            case -8 - KIND_IRR: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_IRR>), grid, block, lds, st, Q); break;
-            case -8 - KIND_REV: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_REV>), grid, block, lds, st, Q); break;
-            case -8 - KIND_1TCM: hipLaunchKernelGGL((vpet_infer_screen_kernel<KIND_1TCM>), grid, block, lds, st, Q); break;
-            case -8: hipLaunchKernelGGL((vpet_infer_screen_kernel<0>), grid, block, lds, st, Q); break;
+            case -8 - KIND_IRR: VPET_SCREEN_LAUNCH(KIND_IRR); break;
+            case -8 - KIND_REV: VPET_SCREEN_LAUNCH(KIND_REV); break;
+            case -8 - KIND_1TCM: VPET_SCREEN_LAUNCH(KIND_1TCM); break;
+            case -8: VPET_SCREEN_LAUNCH(0); break;
             case -1: hipLaunchKernelGGL((vpet_infer_is_kernel<false>), grid, block, lds, st, Q); break;
             case -2: hipLaunchKernelGGL((vpet_infer_is_kernel<true>), grid, block, lds, st, Q); break;
             case -3: hipLaunchKernelGGL(vpet_infer_is_screen_kernel, grid, block, lds, st, Q); break;
@@ -6320,8 +6456,16 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
             case 1: hipLaunchKernelGGL((vpet_infer_kernel<0, true>), grid, block, lds, st, Q); break;
             default: hipLaunchKernelGGL((vpet_infer_kernel<0, false>), grid, block, lds, st, Q); break;
         }
+#undef VPET_SCREEN_LAUNCH
         hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "infer launch");
+        if (e != hipSuccess) {
+            if (part_work) (void)hipFreeAsync(part_work, st);
+            return hip_fail(e, "infer launch");
+        }
+    }
+    if (part_work) {
+        const hipError_t e = hipFreeAsync(part_work, st);
+        if (e != hipSuccess) return hip_fail(e, "hipFreeAsync");
     }
     if (ctx) {
         hipError_t e = hipEventRecord(ctx->ev[slot], st);

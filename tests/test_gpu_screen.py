@@ -81,6 +81,22 @@ def test_inputs(case):
     _check_infer(ora, y, ft, cp, [model], boxes, n_draws, p, 3, weights=weights)
 
 
+@pytest.mark.parametrize("models,n_draws,n,voxels,ties", [
+    ((IRR,), 8000, 1, 1, False), ((IRR,), 8001, 100, 3, False), ((T1, IRR, REV), 9001, 300, 2, False),
+    ((REV,), 16_000, 64, 1, False), ((T1,), 50_001, 65, 128, False), ((IRR,), 20_000, 2000, 2, False),
+    ((IRR,), 9000, 50, 2, True)])
+def test_few_voxels(models, n_draws, n, voxels, ties):
+    """A voxel's draws over several blocks (a count of upper bounds, then the
+    parts' candidates); ties leave every part to the unscreened path."""
+    import oracle as ora
+    ft, cp, y = _inputs(n_vox=voxels, model=models[-1], sched=W.SCHED_30x50)
+    boxes = W.box_array(list(models))
+    if ties:
+        for s, v in ((0, 0.3), (1, 0.3), (2, 0.1), (4, 0.05)):
+            boxes[0, s] = (v, v)
+    _check_infer(ora, y, ft, cp, list(models), boxes, n_draws, (n + 0.5) / (n_draws * len(models)), 13, voxel_offset=2)
+
+
 @pytest.mark.parametrize("n_draws,n,share,scale,spread,sd", [
     (2599, 20, 0.1, 1.0, 0.2, 0.3), (2600, 64, 0.0, 1.0, 0.2, 0.3), (2601, 65, 0.1, 1.5, 0.2, 0.3),
     (5003, 300, 0.5, 1.0, 0.2, 0.3), (4000, 1000, 0.1, 1.0, 0.2, 0.3),
