@@ -3832,24 +3832,15 @@ constexpr size_t kOffW1 = 0, kOffB1 = kOffW1 + (size_t)kNetIn * kNetH, kOffW2 = 
                  kOffB3 = kOffW3 + (size_t)kNetH * kNetOut, kNetParams = kOffB3 + kNetOut;
 static_assert(kNetParams == VPET_PROPOSAL_NPARAM, "parameter blob layout");
 
-// C = epilogue(op(A) op(B)): a(m, k) = A[m sam + k sak], b(k, n) = B[k sbk +
-// n sbn], FP32 in memory, bf16 on the matrix cores, FP32 accumulation.
-// Epilogue: + bias[n]; then ReLU (relu), or multiplication by (mask[m][n] > 0)
-// (the ReLU derivative of the forward activation); accumulate adds to C.
+// C = A^T B, A [K][M], B [K][N], C [M][N], FP32 in memory: a weight gradient, K
+// the rows of the batch.
 struct GemmArgs {
-    const float* A;
-    long long sam, sak;
-    const float* B;
-    long long sbk, sbn;
+    const float *A, *B;
     float* C;
-    long long ldc;
-    const float* bias;
-    const float* mask;
-    long long ldm;
-    int M, N, K, relu, accumulate;
+    int M, N, K;
     // split K: block z sums k in [z kchunk, (z+1) kchunk) and, with part set,
-    // stores its raw partial tile at part + z pstride ([M][N]); a second
-    // kernel adds the partials in order and applies the epilogue
+    // stores its partial tile at part + z pstride; a second kernel adds the
+    // partials in order
     int kchunk;
     float* part;
     long long pstride;
@@ -3867,63 +3858,45 @@ __device__ __forceinline__ void split_bf16x8(const float (&x)[8], uint4& hi, uin
     lo = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
 }
 
-// C = act(A B + bias) (or masked) with fp32 operands on BF16 matrix cores:
-// each operand is split into bf16 hi + lo and the product is hi*hi + hi*lo +
-// lo*hi (three MFMAs, FP32 accumulation), relative error about 3 * 2^-16 per
-// term instead of 2^-7 for a plain bf16 product.
+// C = A^T B with fp32 operands on BF16 matrix cores: each operand is split into
+// bf16 hi + lo and the product is hi*hi + hi*lo + lo*hi (three MFMAs, FP32
+// accumulation), relative error about 3 * 2^-16 per term instead of 2^-7 for a
+// plain bf16 product.
 // Block = 4 wavefronts = a 64 x 64 tile of C (a 32 x 32 tile per wavefront).
-// K advances in chunks of 32: the block stages the chunk's 64 x 32 slices of A
-// and B into LDS, split into bf16 hi and lo once, with loads in which
-// consecutive lanes read consecutive addresses along whichever of the
-// operand's two strides is 1 (the transposed operands of the backward pass
-// included); the wavefronts then read their MFMA fragments from LDS.  Two
-// buffers: the loads of chunk c+1 are issued before chunk c is multiplied.
-// The products and their order per 16-wide k step are those of one MFMA
-// chain per output tile, so the result does not depend on the staging.
+// K advances in chunks of 32: the block stages the chunk's 32 x 64 slices of A
+// and B into LDS, transposed and split into bf16 hi and lo once (consecutive
+// lanes read consecutive addresses); the wavefronts then read their MFMA
+// fragments from LDS.  Two buffers: the loads of chunk c+1 are issued before
+// chunk c is multiplied.  The products and their order per 16-wide k step are
+// those of one MFMA chain per output tile, so the result does not depend on
+// the staging.
 constexpr int kGemmKC = 32;                  // k per staged chunk
 constexpr int kGemmRS = kGemmKC + 8;         // LDS row stride (bf16), padded against bank conflicts
-__global__ __launch_bounds__(256) void vpet_gemm_bf16x3_kernel(GemmArgs G) {
+__device__ __forceinline__ void gemm_bf16x3(const GemmArgs& G, int bx, int by, int bz) {
     __shared__ __align__(16) uint16_t sm[2][4][64 * kGemmRS];  // [buffer][A hi, A lo, B hi, B lo][row][k]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bm0 = blockIdx.y * 64, bn0 = blockIdx.x * 64;
+    const int bm0 = by * 64, bn0 = bx * 64;
     const int m0 = bm0 + (wave >> 1) * 32, n0 = bn0 + (wave & 1) * 32;
-    const int kbeg = blockIdx.z * G.kchunk, kend = min(G.K, kbeg + G.kchunk);
-    // staging map: element e = tid + 256 q (q < 8) of a 64 x 32 slice, the
-    // fast index along the operand's unit stride
-    const bool a_kfast = G.sak == 1, b_kfast = G.sbk == 1;
+    const int kbeg = bz * G.kchunk, kend = min(G.K, kbeg + G.kchunk);
+    // staging map: element e = tid + 256 q (q < 8) of a 32 x 64 slice
     float av[8], bv[8];
     auto load = [&](int k0) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int e = tid + 256 * q;
-            {
-                const int r = a_kfast ? (e >> 5) : (e & 63), k = a_kfast ? (e & 31) : (e >> 6);
-                const int m = bm0 + r, kk = k0 + k;
-                av[q] = (m < G.M && kk < kend) ? G.A[(long long)m * G.sam + (long long)kk * G.sak] : 0.0f;
-            }
-            {
-                const int r = b_kfast ? (e >> 5) : (e & 63), k = b_kfast ? (e & 31) : (e >> 6);
-                const int n = bn0 + r, kk = k0 + k;
-                bv[q] = (n < G.N && kk < kend) ? G.B[(long long)kk * G.sbk + (long long)n * G.sbn] : 0.0f;
-            }
+            const int e = tid + 256 * q, kk = k0 + (e >> 6), m = bm0 + (e & 63), n = bn0 + (e & 63);
+            av[q] = (m < G.M && kk < kend) ? G.A[(long long)kk * G.M + m] : 0.0f;
+            bv[q] = (n < G.N && kk < kend) ? G.B[(long long)kk * G.N + n] : 0.0f;
         }
     };
     auto stash = [&](int buf) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int e = tid + 256 * q;
-            {
-                const int r = a_kfast ? (e >> 5) : (e & 63), k = a_kfast ? (e & 31) : (e >> 6);
-                const uint32_t h = bf16_rn(av[q]);
-                sm[buf][0][r * kGemmRS + k] = (uint16_t)h;
-                sm[buf][1][r * kGemmRS + k] = (uint16_t)bf16_rn(av[q] - __uint_as_float(h << 16));
-            }
-            {
-                const int r = b_kfast ? (e >> 5) : (e & 63), k = b_kfast ? (e & 31) : (e >> 6);
-                const uint32_t h = bf16_rn(bv[q]);
-                sm[buf][2][r * kGemmRS + k] = (uint16_t)h;
-                sm[buf][3][r * kGemmRS + k] = (uint16_t)bf16_rn(bv[q] - __uint_as_float(h << 16));
-            }
+            const int e = tid + 256 * q, o = (e & 63) * kGemmRS + (e >> 6);
+            const uint32_t ha = bf16_rn(av[q]), hb = bf16_rn(bv[q]);
+            sm[buf][0][o] = (uint16_t)ha;
+            sm[buf][1][o] = (uint16_t)bf16_rn(av[q] - __uint_as_float(ha << 16));
+            sm[buf][2][o] = (uint16_t)hb;
+            sm[buf][3][o] = (uint16_t)bf16_rn(bv[q] - __uint_as_float(hb << 16));
         }
     };
     f32x16_t acc = {};
@@ -3957,105 +3930,54 @@ __global__ __launch_bounds__(256) void vpet_gemm_bf16x3_kernel(GemmArgs G) {
     for (int r = 0; r < 16; ++r) {
         const int m = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n = n0 + (lane & 31);
         if (m >= G.M || n >= G.N) continue;
-        float v = acc[r];
-        if (G.part) {
-            G.part[blockIdx.z * G.pstride + (long long)m * G.N + n] = v;
-            continue;
-        }
-        if (G.bias) v += G.bias[n];
-        if (G.relu) v = fmaxf(v, 0.0f);
-        if (G.mask && !(G.mask[(long long)m * G.ldm + n] > 0.0f)) v = 0.0f;
-        float* cptr = G.C + (long long)m * G.ldc + n;
-        *cptr = G.accumulate ? *cptr + v : v;
+        const long long e = (long long)m * G.N + n;
+        if (G.part)
+            G.part[bz * G.pstride + e] = acc[r];
+        else
+            G.C[e] = acc[r];
     }
 }
 
-// C = epilogue(sum over the S split-K partials, in order): bias, relu, mask.
-__global__ __launch_bounds__(256) void vpet_gemm_reduce_kernel(GemmArgs G, int S) {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long long)G.M * G.N) return;
-    const int m = (int)(e / G.N), n = (int)(e - (long long)m * G.N);
-    float v = 0.0f;
-    for (int z = 0; z < S; ++z) v += G.part[z * G.pstride + e];
-    if (G.bias) v += G.bias[n];
-    if (G.relu) v = fmaxf(v, 0.0f);
-    if (G.mask && !(G.mask[(long long)m * G.ldm + n] > 0.0f)) v = 0.0f;
-    float* c = G.C + (long long)m * G.ldc + n;
-    *c = G.accumulate ? *c + v : v;
+// The weight gradients of one step (three products over the batch rows), one
+// launch: block first[q] .. first[q + 1] - 1 is a tile and a split of product q.
+constexpr int kGradProducts = 3;
+struct GradGroup {
+    GemmArgs g[kGradProducts];
+    int nx[kGradProducts], ny[kGradProducts], S[kGradProducts], first[kGradProducts + 1];
+    const float* dY[kGradProducts];  // bias gradients: column sums of dY [rows][cols]
+    float* db[kGradProducts];
+    int cols[kGradProducts], rows;
+    int red[kGradProducts + 1];      // blocks of 256 elements of the split products
+};
+__global__ __launch_bounds__(256) void vpet_grad_gemm_kernel(GradGroup Q) {
+    const int b = blockIdx.x, q = b < Q.first[1] ? 0 : (b < Q.first[2] ? 1 : 2);
+    const int t = b - Q.first[q], nx = Q.nx[q], ny = Q.ny[q];
+    gemm_bf16x3(Q.g[q], t % nx, t / nx % ny, t / (nx * ny));
 }
 
-// db[n] = sum_m dY[m][n] (one block per column).
-__global__ __launch_bounds__(256) void vpet_colsum_kernel(const float* dY, long long ld, int M, float* out) {
-    const int n = blockIdx.x;
-    double s = 0.0;
-    for (int m = threadIdx.x; m < M; m += blockDim.x) s += (double)dY[(long long)m * ld + n];
-    __shared__ double part[4];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) out[n] = (float)(part[0] + part[1] + part[2] + part[3]);
-}
-
-// Mean negative log density of z[b][D] under the mixture of O[b][96] (a head
-// over D parameters) and its gradient dO (already divided by the batch size);
-// loss_acc += mean.
-template <int D>
-__global__ __launch_bounds__(256) void vpet_mix_loss_kernel(const float* O, const float* Z, int Bn, float* dO,
-                                                            float* loss_acc) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    double nll = 0.0;
-    if (b < Bn) {
-        const float* o = O + (size_t)b * kNetOut;
-        float* d = dO + (size_t)b * kNetOut;
-        double lg[kMixC], comp[kMixC], mx = -1e300;
-#pragma unroll
-        for (int c = 0; c < kMixC; ++c) mx = fmax(mx, (double)o[c]);
-        double se = 0.0;
-#pragma unroll
-        for (int c = 0; c < kMixC; ++c) se += exp((double)o[c] - mx);
-        const double lse_l = mx + log(se);
-        double cmx = -1e300;
-#pragma unroll
-        for (int c = 0; c < kMixC; ++c) {
-            lg[c] = (double)o[c] - lse_l;  // log pi_c
-            double q = lg[c];
-#pragma unroll
-            for (int j = 0; j < D; ++j) {
-                const double sg = 1.0 / (1.0 + exp(-(double)o[kMixC + kMixC * D + c * D + j]));
-                const double lsd = kLS0 + (kLS1 - kLS0) * sg;
-                const double t = ((double)Z[b * D + j] - (double)o[kMixC + c * D + j]) * exp(-lsd);
-                q += -0.5 * t * t - lsd - 0.9189385332046727;  // 0.5 log(2 pi)
-            }
-            comp[c] = q;
-            cmx = fmax(cmx, q);
-        }
-        double sc = 0.0;
-#pragma unroll
-        for (int c = 0; c < kMixC; ++c) sc += exp(comp[c] - cmx);
-        const double lse = cmx + log(sc);
-        nll = -lse;
-        const double rB = 1.0 / (double)Bn;
-#pragma unroll
-        for (int c = 0; c < kMixC; ++c) {
-            const double r = exp(comp[c] - lse);
-            d[c] = (float)((exp(lg[c]) - r) * rB);
-#pragma unroll
-            for (int j = 0; j < D; ++j) {
-                const double sg = 1.0 / (1.0 + exp(-(double)o[kMixC + kMixC * D + c * D + j]));
-                const double lsd = kLS0 + (kLS1 - kLS0) * sg;
-                const double isd = exp(-lsd);
-                const double t = ((double)Z[b * D + j] - (double)o[kMixC + c * D + j]) * isd;
-                d[kMixC + c * D + j] = (float)(-r * t * isd * rB);
-                d[kMixC + kMixC * D + c * D + j] = (float)(r * (1.0 - t * t) * (kLS1 - kLS0) * sg * (1.0 - sg) * rB);
-            }
-        }
-        for (int q = net_out_used(D); q < kNetOut; ++q) d[q] = 0.0f;
+// The split products' partials added in order, and the bias gradients (a block
+// per column, FP64 sums).
+__global__ __launch_bounds__(256) void vpet_grad_reduce_kernel(GradGroup Q) {
+    const int b = blockIdx.x;
+    if (b < Q.red[kGradProducts]) {
+        const int q = b < Q.red[1] ? 0 : (b < Q.red[2] ? 1 : 2);
+        const GemmArgs& G = Q.g[q];
+        const int e = (b - Q.red[q]) * 256 + (int)threadIdx.x;
+        if (e >= G.M * G.N) return;
+        float v = 0.0f;
+        for (int z = 0; z < Q.S[q]; ++z) v += G.part[z * G.pstride + e];
+        G.C[e] = v;
+        return;
     }
+    int n = b - Q.red[kGradProducts], q = 0;
+    while (q < kGradProducts - 1 && n >= Q.cols[q]) n -= Q.cols[q++];
+    double t = 0.0;
+    for (int m = threadIdx.x; m < Q.rows; m += blockDim.x) t += (double)Q.dY[q][(long long)m * Q.cols[q] + n];
     __shared__ double part[4];
-    double s = wave_sum(nll);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    t = wave_sum(t);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(loss_acc, (float)((part[0] + part[1] + part[2] + part[3]) / (double)Bn));
+    if (threadIdx.x == 0) Q.db[q][n] = (float)(part[0] + part[1] + part[2] + part[3]);
 }
 
 // Adam (Kingma and Ba) on the FP32 master weights; c1, c2 are the bias
@@ -4084,14 +4006,6 @@ __global__ __launch_bounds__(256) void vpet_net_init_kernel(float* p, uint32_t k
     philox10((uint32_t)i, 0u, 5u, 0u, key0, key1, w);
     const double ua = ((double)(w[0] >> 8) + 1.0) * 0x1p-24, ub = (double)(w[1] >> 8) * 0x1p-24;
     p[i] = (float)(sd * sqrt(-2.0 * log(ua)) * cos(2.0 * M_PI * ub));
-}
-
-// Network inputs X[b][32] = log1p(max(y, 0)) (zero padding) of observed TACs.
-__global__ __launch_bounds__(256) void vpet_net_features_kernel(const float* tacs, long long n, int F, float* X) {
-    const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    for (int f = 0; f < kNetIn; ++f)
-        X[b * kNetIn + f] = f < F ? (float)log1p(fmax((double)tacs[b * F + f], 0.0)) : 0.0f;
 }
 
 // Training batch: bank row of sample j of epoch e is (j * mul + add) mod n_bank
@@ -4202,14 +4116,31 @@ constexpr int kFwdRows = 64;
 constexpr int kFwdBlocks = 256;  // a block per CU (146 KB of LDS each)
 constexpr int kFwdXS = kNetIn + 8, kFwdHS = kNetH + 8;  // LDS row strides (bf16), padded against bank conflicts
 constexpr int kFragW1 = 0, kFragW2 = kFragW1 + 8 * (kNetIn / 16), kFragW3 = kFragW2 + 8 * (kNetH / 16),
-              kFrags = kFragW3 + (kNetOut / 32) * (kNetH / 16);
+              kFrags = kFragW3 + (kNetOut / 32) * (kNetH / 16),
+              // the backward pass's W3^T (256 columns, 96 rows) and W2^T
+              kFragW3T = kFrags, kFragW2T = kFragW3T + 8 * (kNetOut / 16), kFragsTrain = kFragW2T + 8 * (kNetH / 16);
 
 // Weights as MFMA operands: fragment (layer, 32-column tile, 16-row k step) is
 // 64 lanes x 16 bytes of bf16 hi, then of lo; lane l holds column l % 32, rows
 // 8 (l / 32) .. + 7.
-__global__ __launch_bounds__(256) void vpet_net_frags_kernel(const float* p, uint4* frag) {
+__global__ __launch_bounds__(256) void vpet_net_frags_kernel(const float* p, uint4* frag, int count, float* loss) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x, fr = t >> 6, lane = t & 63;
-    if (fr >= kFrags) return;
+    if (loss && t == 0) *loss = 0.0f;  // (in front of the kernel that adds to it)
+    if (fr >= count) return;
+    if (fr >= kFragW3T) {
+        const bool third = fr < kFragW2T;
+        const int q = fr - (third ? kFragW3T : kFragW2T), nks = third ? kNetOut / 16 : kNetH / 16;
+        const int k = 16 * (q % nks) + 8 * (lane >> 5), c = 32 * (q / nks) + (lane & 31);
+        const float* row = third ? p + kOffW3 + (size_t)c * kNetOut + k : p + kOffW2 + (size_t)c * kNetH + k;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = row[e];
+        uint4 hi, lo;
+        split_bf16x8(x, hi, lo);
+        frag[(size_t)(2 * fr) * kWave + lane] = hi;
+        frag[(size_t)(2 * fr + 1) * kWave + lane] = lo;
+        return;
+    }
     const float* W = p + kOffW1;
     int N = kNetH, tile, ks;
     if (fr < kFragW2) {
@@ -4283,7 +4214,7 @@ struct FwdLds {
 // Features of rows [row0, row0 + 64) by `nthr` threads (thread t).
 template <int PER>
 __device__ __forceinline__ void fwd_features(const float* tacs, long long n, int F, long long row0, int t, int nthr,
-                                             FwdLds& S) {
+                                             FwdLds& S, float* X = nullptr) {
     float y[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -4298,6 +4229,7 @@ __device__ __forceinline__ void fwd_features(const float* tacs, long long n, int
         const uint32_t h = bf16x2_rn(x, 0.0f);
         S.X[0][o] = (uint16_t)h;
         S.X[1][o] = (uint16_t)bf16x2_rn(x - __uint_as_float(h << 16), 0.0f);
+        if (X && row0 + e / kNetIn < n) X[row0 * kNetIn + e] = x;
     }
 }
 
@@ -4414,6 +4346,207 @@ __global__ __launch_bounds__(512) void vpet_net_forward_kernel(const float* __re
             fwd_features<16>(tacs, n, F, (t + gridDim.x) * kFwdRows, tid - 384, 128, S);
         }
         __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// One training step's passes over the rows, 64 rows per block: features and
+// targets (or a given batch), the forward pass as above, the mean negative log
+// density of z[D] under the row's mixture and its gradient dO (divided by the
+// batch size), and the backward products dH2 = dO W3^T and dH1 = dH2 W2^T with
+// the ReLU masks kept in registers (a wavefront forms the same columns of H and
+// dH).  X, H1, H2, dO, dH2, dH1 go to memory for the weight gradients; loss +=
+// the mean.  The same arithmetic and order as the separate products.  Bound by
+// latency at the usual batch (32 blocks): 2048 rows, with the weight gradients
+// grouped into two launches, 204 -> 86 us (18 launches of 4 to 36 us before);
+// 64 rows 132 -> 65 us, 65536 rows 1500 -> 708 us.
+// ---------------------------------------------------------------------------
+struct StepArgs {
+    const float* p;
+    const uint4* frag;
+    const float *tacs, *theta;  // observed curves [n][F] and parameters [n][8], or nullptr:
+    float *X, *Z;               // the batch [n][32], [n][D] (written when tacs is given)
+    float *H1, *H2, *dO, *dH2, *dH1, *loss;
+    long long n;
+    int F;
+};
+
+__device__ __forceinline__ double shfl8_f64(double v, int src) {  // lane src of this group of 8
+    const int l = (lane_id() & ~7) | src;
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)u, l, kWave), hi = (uint32_t)__shfl((int)(uint32_t)(u >> 32), l, kWave);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+template <int D>
+__global__ __launch_bounds__(512) void vpet_net_step_kernel(StepArgs A) {
+    __shared__ __align__(16) FwdLds S;
+    // after layer 2 the first layer's activations make room for the outputs
+    // (fp32) and the split output gradients
+    constexpr int OS = kNetOut + 1, GS = kNetOut + 8;
+    float* O = reinterpret_cast<float*>(&S.H1[0][0]);
+    uint16_t* G0 = reinterpret_cast<uint16_t*>(O + kFwdRows * OS);
+    uint16_t* G1 = G0 + kFwdRows * GS;
+    static_assert(4 * kFwdRows * OS + 4 * kFwdRows * GS <= (int)sizeof(S.H1), "outputs fit");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    for (int c = tid; c < kNetH; c += 512) {
+        S.b1[c] = A.p[kOffB1 + c];
+        S.b2[c] = A.p[kOffB2 + c];
+        if (c < kNetOut) S.b3[c] = A.p[kOffB3 + c];
+    }
+    auto fragment = [&](int fr, int part) { return as_bf16x8(A.frag[(size_t)(2 * fr + part) * kWave + lane]); };
+    const long long ntiles = (A.n + kFwdRows - 1) / kFwdRows;
+    double nll = 0.0;
+    for (long long t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const long long row0 = t * kFwdRows;
+        if (A.tacs) {
+            fwd_features<4>(A.tacs, A.n, A.F, row0, tid, 512, S, A.X);
+        } else {
+            for (int e = tid; e < kFwdRows * kNetIn; e += 512) {
+                const float x = row0 + e / kNetIn < A.n ? A.X[row0 * kNetIn + e] : 0.0f;
+                const int o = (e / kNetIn) * kFwdXS + e % kNetIn;
+                const uint32_t h = bf16x2_rn(x, 0.0f);
+                S.X[0][o] = (uint16_t)h;
+                S.X[1][o] = (uint16_t)bf16x2_rn(x - __uint_as_float(h << 16), 0.0f);
+            }
+        }
+        __syncthreads();
+        // this wavefront's 32 columns of a 256-column product of both 32-row
+        // halves: columns 32 wave + 8 q + 4 half + e of row 32 m + lane % 32
+        f32x16_t a[2];
+        auto product = [&](auto nks, int fr, const uint16_t* hi, const uint16_t* lo, int stride) {
+            constexpr int NKS = decltype(nks)::value;
+            a[0] = a[1] = f32x16_t{};
+#pragma unroll 4
+            for (int ks = 0; ks < NKS; ++ks) {
+                const bf16x8_t wh = fragment(fr + NKS * wave + ks, 0), wl = fragment(fr + NKS * wave + ks, 1);
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int o = (32 * m + (lane & 31)) * stride + 16 * ks + 8 * half;
+                    a[m] = mfma_x3(wh, wl, as_bf16x8(*reinterpret_cast<const uint4*>(hi + o)),
+                                   as_bf16x8(*reinterpret_cast<const uint4*>(lo + o)), a[m]);
+                }
+            }
+        };
+        // fin(column, value, bit) finishes each value; memory (fp32) and LDS
+        auto store = [&](auto fin, float* out, uint16_t* hi, uint16_t* lo) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 32 * wave + 8 * q + 4 * half, r = 32 * m + (lane & 31);
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fin(c + e, a[m][4 * q + e], 1u << (16 * m + 4 * q + e));
+                    if (row0 + r < A.n)
+                        *reinterpret_cast<float4*>(out + (row0 + r) * kNetH + c) = make_float4(v[0], v[1], v[2], v[3]);
+                    if (hi) store_split4(hi + r * kFwdHS + c, lo + r * kFwdHS + c, v);
+                }
+        };
+        uint32_t on1 = 0u, on2 = 0u;  // positive activations of this lane's columns
+        product(std::integral_constant<int, kNetIn / 16>{}, kFragW1, S.X[0], S.X[1], kFwdXS);
+        store([&](int c, float v, uint32_t bit) {
+            v = fmaxf(v + S.b1[c], 0.0f);
+            on1 |= v > 0.0f ? bit : 0u;
+            return v;
+        }, A.H1, S.H1[0], S.H1[1]);
+        __syncthreads();
+        product(std::integral_constant<int, kNetH / 16>{}, kFragW2, S.H1[0], S.H1[1], kFwdHS);
+        store([&](int c, float v, uint32_t bit) {
+            v = fmaxf(v + S.b2[c], 0.0f);
+            on2 |= v > 0.0f ? bit : 0u;
+            return v;
+        }, A.H2, S.H2[0], S.H2[1]);
+        __syncthreads();
+        if (wave < 6) {  // the outputs, into the first layer's place
+            const int m = wave & 1, ct = wave >> 1;
+            f32x16_t o = {};
+#pragma unroll 4
+            for (int ks = 0; ks < kNetH / 16; ++ks) {
+                const int l = (32 * m + (lane & 31)) * kFwdHS + 16 * ks + 8 * half;
+                o = mfma_x3(fragment(kFragW3 + 16 * ct + ks, 0), fragment(kFragW3 + 16 * ct + ks, 1),
+                            as_bf16x8(*reinterpret_cast<const uint4*>(&S.H2[0][l])),
+                            as_bf16x8(*reinterpret_cast<const uint4*>(&S.H2[1][l])), o);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int c = 32 * ct + 8 * (r >> 2) + 4 * half + (r & 3);
+                O[(32 * m + (lane & 31)) * OS + c] = o[r] + S.b3[c];
+            }
+        }
+        __syncthreads();
+        {  // a thread per row and component
+            const int r = tid >> 3, c = tid & 7;
+            const long long row = row0 + r;
+            const bool live = row < A.n;
+            const float* o = O + r * OS;
+            float z[D];
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                if (A.tacs)
+                    z[j] = live ? (float)log(fmax((double)A.theta[row * VPET_PSTRIDE + head_slot<D>(j)], 1e-6)) : 0.0f;
+                else
+                    z[j] = live ? A.Z[row * D + j] : 0.0f;
+            }
+            double mx = -1e300;
+#pragma unroll
+            for (int k = 0; k < kMixC; ++k) mx = fmax(mx, (double)o[k]);
+            const double ex = exp((double)o[c] - mx);
+            double se = 0.0;
+#pragma unroll
+            for (int k = 0; k < kMixC; ++k) se += shfl8_f64(ex, k);
+            const double lg = (double)o[c] - (mx + log(se));  // log pi_c
+            double q = lg, sg[D], isd[D], tt[D];
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                sg[j] = 1.0 / (1.0 + exp(-(double)o[kMixC + kMixC * D + c * D + j]));
+                const double lsd = kLS0 + (kLS1 - kLS0) * sg[j];
+                isd[j] = exp(-lsd);
+                tt[j] = ((double)z[j] - (double)o[kMixC + c * D + j]) * isd[j];
+                q += -0.5 * tt[j] * tt[j] - lsd - 0.9189385332046727;  // 0.5 log(2 pi)
+            }
+            double cmx = -1e300;
+#pragma unroll
+            for (int k = 0; k < kMixC; ++k) cmx = fmax(cmx, shfl8_f64(q, k));
+            const double ec = exp(q - cmx);
+            double sc = 0.0;
+#pragma unroll
+            for (int k = 0; k < kMixC; ++k) sc += shfl8_f64(ec, k);
+            const double lse = cmx + log(sc);
+            if (live && c == 0) nll -= lse;
+            const double rB = 1.0 / (double)A.n, rr = exp(q - lse);
+            auto put = [&](int col, float v) {
+                if (!live) v = 0.0f;
+                const uint32_t h = bf16x2_rn(v, 0.0f);
+                G0[r * GS + col] = (uint16_t)h;
+                G1[r * GS + col] = (uint16_t)bf16x2_rn(v - __uint_as_float(h << 16), 0.0f);
+                if (live) A.dO[row * kNetOut + col] = v;
+            };
+            put(c, (float)((exp(lg) - rr) * rB));
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                put(kMixC + c * D + j, (float)(-rr * tt[j] * isd[j] * rB));
+                put(kMixC + kMixC * D + c * D + j,
+                    (float)(rr * (1.0 - tt[j] * tt[j]) * (kLS1 - kLS0) * sg[j] * (1.0 - sg[j]) * rB));
+            }
+            for (int k = net_out_used(D) + c; k < kNetOut; k += kMixC) put(k, 0.0f);
+        }
+        __syncthreads();
+        product(std::integral_constant<int, kNetOut / 16>{}, kFragW3T, G0, G1, GS);
+        store([&](int, float v, uint32_t bit) { return (on2 & bit) != 0u ? v : 0.0f; }, A.dH2, S.H2[0], S.H2[1]);
+        __syncthreads();
+        product(std::integral_constant<int, kNetH / 16>{}, kFragW2T, S.H2[0], S.H2[1], kFwdHS);
+        store([&](int, float v, uint32_t bit) { return (on1 & bit) != 0u ? v : 0.0f; }, A.dH1, nullptr, nullptr);
+        __syncthreads();
+    }
+    nll = wave_sum(nll);
+    double* red = reinterpret_cast<double*>(&S.X[0][0]);
+    if (lane == 0) red[wave] = nll;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+        for (int w = 0; w < 8; ++w) t += red[w];
+        atomicAdd(A.loss, (float)(t / (double)A.n));
     }
 }
 
@@ -7607,25 +7740,20 @@ __global__ __launch_bounds__(256) void vpet_fill_kernel(float* p, long long n, f
     if (i < n) p[i] = v;
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void vpet_net_targets_kernel(const float* theta, long long n, float* Z) {
-    const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    for (int j = 0; j < D; ++j) Z[b * D + j] = (float)log(fmax((double)theta[b * VPET_PSTRIDE + head_slot<D>(j)], 1e-6));
-}
-
-// Activations of one batch of up to `rows` samples.
+// One batch's activations and gradients for up to `rows` samples.
 struct NetWork {
-    float *X, *H1, *H2, *O, *dO, *dH1, *dH2, *Z;
-    float* part;  // split-K partials: kSplitMax tiles of at most kNetH x kNetH
+    float *X, *H1, *H2, *dO, *dH1, *dH2, *Z;
+    float* part;  // split-K partials of the three weight gradients
+    uint4* frag;  // split weights
     long long rows;
 };
 
 constexpr int kSplitMax = 16;
+constexpr size_t kPartFloats = (size_t)kSplitMax * (kNetH * kNetOut + kNetH * kNetH + kNetIn * kNetH);
+constexpr size_t kFragFloats = sizeof(uint4) / sizeof(float) * 2 * kWave * (size_t)kFragsTrain;
 
 size_t net_work_bytes(long long rows) {
-    return sizeof(float) * ((size_t)rows * (kNetIn + 4 * kNetH + 2 * kNetOut + kMixDMax) +
-                            (size_t)kSplitMax * kNetH * kNetH) + 9 * 256;
+    return sizeof(float) * ((size_t)rows * (kNetIn + 4 * kNetH + kNetOut + kMixDMax) + kPartFloats + kFragFloats) + 9 * 256;
 }
 
 void net_work_carve(char* base, long long rows, NetWork& w) {
@@ -7640,55 +7768,65 @@ void net_work_carve(char* base, long long rows, NetWork& w) {
     w.H2 = take((size_t)rows * kNetH);
     w.dH1 = take((size_t)rows * kNetH);
     w.dH2 = take((size_t)rows * kNetH);
-    w.O = take((size_t)rows * kNetOut);
     w.dO = take((size_t)rows * kNetOut);
     w.Z = take((size_t)rows * kMixDMax);
-    w.part = take((size_t)kSplitMax * kNetH * kNetH);
+    w.part = take(kPartFloats);
+    w.frag = reinterpret_cast<uint4*>(take(kFragFloats));
 }
 
-// A product with few output tiles and a long K (the weight gradients: K =
-// batch rows) is split along K over up to kSplitMax blocks per tile, so that
-// the launch fills the chip; the partials are added in a fixed order, which
-// keeps the result deterministic.
-void gemm(hipStream_t st, const float* A, long long sam, long long sak, const float* B, long long sbk, long long sbn,
-          float* C, long long ldc, int M, int N, int K, const float* bias, int relu, const float* mask, long long ldm,
-          float* part) {
-    GemmArgs G{A, sam, sak, B, sbk, sbn, C, ldc, bias, mask, ldm, M, N, K, relu, 0, K, nullptr, 0};
-    const int tiles = ((N + 63) / 64) * ((M + 63) / 64);
-    int S = 1;
-    if (part && tiles < 128 && K >= 512 && (long long)M * N <= (long long)kNetH * kNetH) {
-        S = std::min(std::min(kSplitMax, (256 + tiles - 1) / tiles), K / 256);
-        G.kchunk = ((K + S - 1) / S + 15) & ~15;
-        S = (K + G.kchunk - 1) / G.kchunk;
-    }
-    if (S > 1) {
-        G.part = part;
-        G.pstride = (long long)M * N;
-    }
-    hipLaunchKernelGGL(vpet_gemm_bf16x3_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)S),
-                       dim3(256), 0, st, G);
-    if (S > 1)
-        hipLaunchKernelGGL(vpet_gemm_reduce_kernel, dim3((unsigned)(((long long)M * N + 255) / 256)), dim3(256), 0, st,
-                           G, S);
-}
-
-// H1 = relu(X W1 + b1), H2 = relu(H1 W2 + b2), O = H2 W3 + b3 for n rows of X.
-void net_forward(hipStream_t st, const float* p, const NetWork& w, int n) {
-    gemm(st, w.X, kNetIn, 1, p + kOffW1, kNetH, 1, w.H1, kNetH, n, kNetH, kNetIn, p + kOffB1, 1, nullptr, 0, w.part);
-    gemm(st, w.H1, kNetH, 1, p + kOffW2, kNetH, 1, w.H2, kNetH, n, kNetH, kNetH, p + kOffB2, 1, nullptr, 0, w.part);
-    gemm(st, w.H2, kNetH, 1, p + kOffW3, kNetOut, 1, w.O, kNetOut, n, kNetOut, kNetH, p + kOffB3, 0, nullptr, 0, w.part);
-}
-
-// Gradients of the mean negative log density into g (overwritten), given dO.
-void net_backward(hipStream_t st, const float* p, const NetWork& w, int n, float* g) {
-    gemm(st, w.H2, 1, kNetH, w.dO, kNetOut, 1, g + kOffW3, kNetOut, kNetH, kNetOut, n, nullptr, 0, nullptr, 0, w.part);
-    hipLaunchKernelGGL(vpet_colsum_kernel, dim3(kNetOut), dim3(256), 0, st, w.dO, (long long)kNetOut, n, g + kOffB3);
-    gemm(st, w.dO, kNetOut, 1, p + kOffW3, 1, kNetOut, w.dH2, kNetH, n, kNetH, kNetOut, nullptr, 0, w.H2, kNetH, w.part);
-    gemm(st, w.H1, 1, kNetH, w.dH2, kNetH, 1, g + kOffW2, kNetH, kNetH, kNetH, n, nullptr, 0, nullptr, 0, w.part);
-    hipLaunchKernelGGL(vpet_colsum_kernel, dim3(kNetH), dim3(256), 0, st, w.dH2, (long long)kNetH, n, g + kOffB2);
-    gemm(st, w.dH2, kNetH, 1, p + kOffW2, 1, kNetH, w.dH1, kNetH, n, kNetH, kNetH, nullptr, 0, w.H1, kNetH, w.part);
-    gemm(st, w.X, 1, kNetIn, w.dH1, kNetH, 1, g + kOffW1, kNetH, kNetIn, kNetH, n, nullptr, 0, nullptr, 0, w.part);
-    hipLaunchKernelGGL(vpet_colsum_kernel, dim3(kNetH), dim3(256), 0, st, w.dH1, (long long)kNetH, n, g + kOffB1);
+// Loss (overwritten) and gradients (into g, overwritten) of n rows: of observed
+// curves and parameters, or of the batch in w.X and w.Z (tacs = nullptr).
+// The weight gradients are products over the rows with few output tiles, split
+// along the rows over up to kSplitMax blocks per tile so that the launch fills
+// the chip; the partials are added in a fixed order (deterministic).
+void net_step(hipStream_t st, const float* p, const NetWork& w, const float* tacs, const float* theta, int F, int dims,
+              int n, float* g, float* loss) {
+    hipLaunchKernelGGL(vpet_net_frags_kernel, dim3((kFragsTrain * kWave + 255) / 256), dim3(256), 0, st, p, w.frag,
+                       kFragsTrain, loss);
+    const StepArgs A{p, w.frag, tacs, theta, w.X, w.Z, w.H1, w.H2, w.dO, w.dH2, w.dH1, loss, (long long)n, F};
+    const dim3 blocks((unsigned)std::min((n + kFwdRows - 1) / kFwdRows, kFwdBlocks));
+    if (dims == 4)
+        hipLaunchKernelGGL(vpet_net_step_kernel<4>, blocks, dim3(512), 0, st, A);
+    else
+        hipLaunchKernelGGL(vpet_net_step_kernel<5>, blocks, dim3(512), 0, st, A);
+    GradGroup Q{};
+    float* part = w.part;
+    int nb = 0, nr = 0, nc = 0;
+    auto add = [&](int q, const float* act, int M, const float* dY, int N, float* dW, float* db) {  // dW = act^T dY
+        GemmArgs G{act, dY, dW, M, N, n, n, nullptr, 0};
+        const int nx = (N + 63) / 64, ny = (M + 63) / 64, tiles = nx * ny;
+        int S = 1;
+        if (n >= 512) {
+            S = std::min(std::min(kSplitMax, (256 + tiles - 1) / tiles), n / 256);
+            G.kchunk = ((n + S - 1) / S + 15) & ~15;
+            S = (n + G.kchunk - 1) / G.kchunk;
+        }
+        if (S > 1) {
+            G.part = part;
+            G.pstride = (long long)M * N;
+            part += (size_t)S * M * N;
+        }
+        Q.g[q] = G;
+        Q.nx[q] = nx;
+        Q.ny[q] = ny;
+        Q.S[q] = S;
+        Q.first[q] = nb;
+        nb += tiles * S;
+        Q.red[q] = nr;
+        nr += S > 1 ? (M * N + 255) / 256 : 0;
+        Q.dY[q] = dY;
+        Q.db[q] = db;
+        Q.cols[q] = N;
+        nc += N;
+    };
+    add(0, w.H2, kNetH, w.dO, kNetOut, g + kOffW3, g + kOffB3);
+    add(1, w.H1, kNetH, w.dH2, kNetH, g + kOffW2, g + kOffB2);
+    add(2, w.X, kNetIn, w.dH1, kNetH, g + kOffW1, g + kOffB1);
+    Q.first[kGradProducts] = nb;
+    Q.red[kGradProducts] = nr;
+    Q.rows = n;
+    hipLaunchKernelGGL(vpet_grad_gemm_kernel, dim3((unsigned)nb), dim3(256), 0, st, Q);
+    hipLaunchKernelGGL(vpet_grad_reduce_kernel, dim3((unsigned)(nr + nc)), dim3(256), 0, st, Q);
 }
 
 int check_frames(int32_t n_frames) {
@@ -7730,7 +7868,8 @@ int vpet_proposal_forward(const float* params, const float* tacs, int64_t n, int
     uint4* frag = nullptr;
     hipError_t e = hipMallocAsync((void**)&frag, sizeof(uint4) * 2 * kWave * kFrags, st);
     if (e != hipSuccess) return fail(VPET_E_NOMEM, "proposal work: %s", hipGetErrorString(e));
-    hipLaunchKernelGGL(vpet_net_frags_kernel, dim3((kFrags * kWave + 255) / 256), dim3(256), 0, st, params, frag);
+    hipLaunchKernelGGL(vpet_net_frags_kernel, dim3((kFrags * kWave + 255) / 256), dim3(256), 0, st, params, frag, kFrags,
+                       (float*)nullptr);
     const long long tiles = (n + kFwdRows - 1) / kFwdRows;
     hipLaunchKernelGGL(vpet_net_forward_kernel, dim3((unsigned)std::min<long long>(tiles, kFwdBlocks)), dim3(512), 0, st,
                        params, frag, tacs, (long long)n, n_frames, out);
@@ -7755,19 +7894,7 @@ int vpet_proposal_loss_grad(const float* params, const float* tacs, const float*
     if (e != hipSuccess) return fail(VPET_E_NOMEM, "proposal work: %s", hipGetErrorString(e));
     NetWork w;
     net_work_carve(work, n, w);
-    const unsigned blk = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(vpet_net_features_kernel, dim3(blk), dim3(256), 0, st, tacs, (long long)n, n_frames, w.X);
-    if (dims == 4)
-        hipLaunchKernelGGL(vpet_net_targets_kernel<4>, dim3(blk), dim3(256), 0, st, theta, (long long)n, w.Z);
-    else
-        hipLaunchKernelGGL(vpet_net_targets_kernel<5>, dim3(blk), dim3(256), 0, st, theta, (long long)n, w.Z);
-    hipLaunchKernelGGL(vpet_fill_kernel, dim3(1), dim3(256), 0, st, loss, 1LL, 0.0f);
-    net_forward(st, params, w, (int)n);
-    if (dims == 4)
-        hipLaunchKernelGGL(vpet_mix_loss_kernel<4>, dim3(blk), dim3(256), 0, st, w.O, w.Z, (int)n, w.dO, loss);
-    else
-        hipLaunchKernelGGL(vpet_mix_loss_kernel<5>, dim3(blk), dim3(256), 0, st, w.O, w.Z, (int)n, w.dO, loss);
-    net_backward(st, params, w, (int)n, grad);
+    net_step(st, params, w, tacs, theta, n_frames, dims, (int)n, grad, loss);
     e = hipGetLastError();
     const hipError_t e2 = hipFreeAsync(work, st);
     if (e != hipSuccess) return hip_fail(e, "proposal loss/gradient");
@@ -7854,14 +7981,7 @@ int vpet_proposal_train(float* params, const float* bank_theta, const double* ba
             hipLaunchKernelGGL(vpet_net_batch_kernel<5>, dim3(blk), dim3(256), 0, st, bank_theta, bank_x, ld,
                                (long long)n_bank, F, static_cast<const double*>(dfac), j % N, mul, add, (uint32_t)epoch,
                                (int)batch, k0, k1, w.X, w.Z);
-        net_forward(st, params, w, batch);
-        if (dims == 4)
-            hipLaunchKernelGGL(vpet_mix_loss_kernel<4>, dim3(blk), dim3(256), 0, st, w.O, w.Z, (int)batch, w.dO,
-                               losses + t);
-        else
-            hipLaunchKernelGGL(vpet_mix_loss_kernel<5>, dim3(blk), dim3(256), 0, st, w.O, w.Z, (int)batch, w.dO,
-                               losses + t);
-        net_backward(st, params, w, batch, g);
+        net_step(st, params, w, nullptr, nullptr, F, dims, batch, g, losses + t);
         b1t *= 0.9;
         b2t *= 0.999;
         const double lr_t = learning_rate * 0.5 * (1.0 + std::cos(M_PI * (double)t / (double)steps));
