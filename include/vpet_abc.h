@@ -342,7 +342,9 @@ int vpet_abc_bank_build(uint32_t model_id, const double* prior_box, int64_t n_dr
  * by an exact pass over the whole bank.
  * Device scratch (a candidate list of 8 n keys, or 16 n bank rows for the
  * BF16 scan, per voxel, in voxel chunks of at most 4 GiB; the BF16 operands,
- * 8 M n_draws ld bytes) is allocated and freed in stream order.
+ * 8 M n_draws ld bytes; for many voxels and rows their order, about 12 bytes a
+ * row and 12 ld bytes per 64 rows; 16 KiB n for voxels that are redone) is
+ * allocated and freed in stream order.
  * Errors: VPET_E_ARG, VPET_E_MODEL, VPET_E_GRID, VPET_E_LIMIT, VPET_E_NOMEM,
  * VPET_E_HIP.
  */

@@ -1652,6 +1652,14 @@ struct ScreenList {
         full = full || have > cap - kWave;
     }
 
+    // A full list whose keys are now the exact ones, sorted (error class 0, the
+    // narrowest): the n smallest stay, with them an exact threshold.
+    __device__ void exact() {
+        have = n;
+        full = false;
+        if (keys[n - 1] != kNoKey) set_tau(prefix(keys, n, n, have));
+    }
+
     // First tile, n <= 64: the n-th smallest of the lanes' smallest upper bounds
     // is one of the n-th smallest distance, so that a short stream does not
     // sort a buffer full of draws that it can rule out.
@@ -3607,7 +3615,8 @@ __device__ __forceinline__ void bank_mfma_body(const BankArgs& P) {
 }
 
 // Up to 32 frames the kernel fits 128 VGPRs (4 wavefronts per SIMD, two
-// blocks per CU); 40 and 48 frames need more registers and run at 3.
+// blocks per CU), and so does the ordered scan at any length; the plain scan of
+// 40 and 48 frames needs more registers and runs at 3.
 template <int K, bool PILOT, bool ORDERED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void vpet_bank_mfma_kernel(BankArgs P) {
     bank_mfma_body<K, PILOT, ORDERED>(P);
@@ -4102,8 +4111,8 @@ __device__ __forceinline__ void mix_table(const float* o, MixTab& t, double shar
 // ---------------------------------------------------------------------------
 // Fused network evaluation: features, both hidden layers and the outputs of 64
 // rows per block and pass, activations in LDS (bf16 hi + lo), as products of
-// vpet_gemm_bf16x3_kernel's arithmetic and order (the outputs are the same
-// bits).  A block's eight wavefronts each keep 32 columns of W1 and W2 in
+// gemm_bf16x3's arithmetic and order (the training step's outputs are the
+// same bits).  A block's eight wavefronts each keep 32 columns of W1 and W2 in
 // registers for the whole launch (a persistent grid of one block per CU), so
 // only W3's 96 KB of split weights stream from L2 per 64 rows; six wavefronts
 // form the outputs' 2 x 3 tiles while the other two form the next pass's
@@ -4897,7 +4906,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // mixture draw itself in fp32 on the hardware's transcendental unit; the draws
 // it cannot rule out are drawn and scored as in vpet_infer_is_kernel.  About 200
 // instructions a draw instead of 1100: 16,384 voxels x 20k draws, n = 100, 10.1 ->
-// 2.45 ms, of which 0.6 ms do not depend on the number of draws.
+// 2.66 ms, of which 0.6 ms do not depend on the number of draws.
+//
+// A trained network's draws are alike, and many lie within their bounds of the
+// threshold: a list that fills up is scored exactly at once, keeps its n smallest
+// and goes on with their threshold (a second loop: one loop for both cost 7 %).
+// 65,536 voxels, trained for 5000 steps, 20k draws: half the lists fill up, 39 ->
+// 12 ms; 100k draws, 85 % of them, 184 -> 47 ms (leaving such voxels to the
+// unscreened draws: 30 and 187 ms).
 //
 // u0 and the component thresholds are compared as integers (u0 2^24 < ceil(cum
 // 2^24)), so the component is the exact one.  theta = e^mu 2^(sd log2(e) n): the
@@ -5009,7 +5025,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     MixTab* mix = reinterpret_cast<MixTab*>(red + kRedStride * P.wpv);
     MixScreen* ms = reinterpret_cast<MixScreen*>(mix + 1);
     ScreenVox* sv = reinterpret_cast<ScreenVox*>(ms + 1);
-    int* flag = reinterpret_cast<int*>(sv + 1);  // [0] valid, [1] unscreened, [4 + w] wave w's candidates
+    int* flag = reinterpret_cast<int*>(sv + 1);  // [0] valid, [1] unscreened
     float* slope = reinterpret_cast<float*>(flag + 4 + P.wpv);
     if (wave == 0) {
         voxel_curve(P, row, yw, flag);
@@ -5062,26 +5078,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         list.have = list.nbuf = 0;
         list.tau = list.root = __builtin_inff();
         list.full = false;
-        constexpr int U = 1, kTile = kWave * U;
-        const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
-        for (uint32_t t = (uint32_t)wave; t < ntiles && !list.full; t += (uint32_t)P.wpv) {
-            Screened s[U];
-            uint32_t g[U];
-            bool ok[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                g[u] = t * kTile + (uint32_t)(u * kWave + lane);
-                ok[u] = screen_proposal(P, S, C, mix, ms, tab, slope, vg, g[u], s[u]) && g[u] < P.n_draws;
-            }
+        const uint32_t ntiles = (P.n_draws + kWave - 1) / kWave;
+        auto tile = [&](uint32_t t) {
+            Screened s[1];
+            const uint32_t g[1] = {t * kWave + (uint32_t)lane};
+            const bool ok[1] = {screen_proposal(P, S, C, mix, ms, tab, slope, vg, g[0], s[0]) && g[0] < P.n_draws};
             list.insert(s, g, ok);
-        }
-        if (!list.full) list.merge();
-        if (lane == 0) {
-            if (list.full) flag[1] = 1;
-            flag[4 + wave] = list.have;
-        }
+        };
         // exact keys of this wavefront's candidates, then the n smallest
-        if (!list.full) {
+        auto exact = [&] {
             for (int j0 = 0; j0 < list.have; j0 += kWave) {
                 const int j = j0 + lane;
                 const uint32_t idx[1] = {j < list.have ? (uint32_t)list.keys[j] & 0xFFFFFFu : 0u};
@@ -5096,10 +5101,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
             for (int j = list.have + lane; j < P.cap; j += kWave) list.keys[j] = kNoKey;
             wave_lds_sync();
             wave_bitonic_sort(list.keys, min(len, P.cap));
+        };
+        uint32_t t = (uint32_t)wave;
+        for (; t < ntiles; t += (uint32_t)P.wpv) {
+            tile(t);
+            if (list.full) break;  // (this tile's draws are not in)
         }
-        __syncthreads();
-        screened = flag[1] == 0;
-        if (screened && P.wpv > 1) {
+        // a full list goes on from its exact keys
+        while (t < ntiles) {
+            exact();
+            list.exact();
+            for (; t < ntiles; t += (uint32_t)P.wpv) {
+                tile(t);
+                if (list.full) break;
+            }
+        }
+        list.merge();
+        exact();
+        if (P.wpv > 1) {
+            __syncthreads();
             block_topn_sort(keys_all, P.wpv, P.cap, n);
         }
     }
@@ -6189,8 +6209,9 @@ namespace {
 // Whether a bank call scans in order: the order costs about 0.3 ms per call and
 // 0.15 ms per voxel chunk, the scan of every tile 0.33 ms per 1e9 pairs, and a
 // block's voxels and a tile's rows are alike only when there are many of each.
+// (The order is held in 32-bit integers, hence the upper end.)
 bool order_pays(int64_t n_voxels, int64_t n_tot) {
-    return n_voxels >= 8192 && n_tot >= 16384 && (double)n_voxels * (double)n_tot >= 3e9;
+    return n_voxels >= 8192 && n_tot >= 16384 && n_tot <= (1LL << 30) && (double)n_voxels * (double)n_tot >= 3e9;
 }
 
 // Blocks per 256 voxels of an ordered scan: the needed tiles vary from block to
@@ -6524,7 +6545,9 @@ static int infer_entry(bool noalloc, const float* tacs, int64_t n_voxels, const 
         if ((rc = upload_tables(*ctx, T, st, P.tab, slot)) != VPET_OK) return rc;
     }
     char* part_work = nullptr;
-    if (scr.use && scr.parts > 1) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (scr.use && scr.parts > 1 && hipStreamIsCapturing(st, &capture) == hipSuccess &&
+        capture == hipStreamCaptureStatusNone) {  // (a capture gets no allocation)
         const size_t keys = align256(sizeof(uint64_t) * (size_t)n_voxels * scr.parts * n_acc);
         if (hipMallocAsync((void**)&part_work, keys + sizeof(unsigned) * n_voxels * (1 + kHistBins), st) !=
             hipSuccess) {
@@ -6785,7 +6808,7 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     const long long cv = std::min<long long>(n_voxels, chunk);
     const int KB = 2 * ld;  // contraction length: [x, x^2] per frame
     char* work = nullptr;
-    const bool ordered = use_mfma && order_pays(n_voxels, n_tot);
+    bool ordered = use_mfma && order_pays(n_voxels, n_tot);
     A.splits = ordered ? order_splits(cv) : 1;
     const size_t sz_tau = align256(sizeof(float) * cv), sz_cnt = align256(sizeof(int) * (1 + 2 * (size_t)A.splits) * cv);
     const size_t sz_fb = fallback_bytes(cv, (int)n_acc), sz_cand = align256(cand_bytes * (size_t)cap * cv);
@@ -6800,7 +6823,14 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     const size_t sz_vox = align256(sizeof(int) * cv), sz_p = align256(sizeof(uint16_t) * (size_t)KB * (size_t)pilot);
     const size_t sz_t = align256(sizeof(uint16_t) * (size_t)KB * n_tiles);
     const size_t sz_ord = ordered ? sz_tree + sz_key + sz_hist + sz_tot + sz_rows + sz_vox + 2 * sz_p + 3 * sz_t : 0;
-    hipError_t e = hipMallocAsync((void**)&work, sz_tau + sz_cnt + sz_fb + sz_cand + 2 * sz_b + 2 * sz_a + 3 * sz_c + sz_av + sz_ord, st);
+    const size_t sz_plain = sz_tau + sz_cnt + sz_fb + sz_cand + 2 * sz_b + 2 * sz_a + 3 * sz_c + sz_av;
+    hipError_t e = hipMallocAsync((void**)&work, sz_plain + sz_ord, st);
+    if (e != hipSuccess && ordered) {  // no room for the order: every tile is scanned
+        (void)hipGetLastError();
+        ordered = false;
+        A.splits = 1;
+        e = hipMallocAsync((void**)&work, sz_plain, st);
+    }
     if (e != hipSuccess) return fail(VPET_E_NOMEM, "bank work: %s", hipGetErrorString(e));
     char* q = work;
     A.tau = reinterpret_cast<float*>(q);

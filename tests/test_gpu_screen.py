@@ -113,3 +113,13 @@ def test_proposal_draws(n_draws, n, share, scale, spread, sd):
     y[4, 2] = np.nan
     keep = [v for v in range(10) if v not in (2, 3)]
     _check_is(y, ft, cp, o, n_draws, (n + 0.5) / n_draws, 5, share=share, scale=scale, sample=keep, v_off=3)
+
+
+@pytest.mark.parametrize("n_draws,n,share,sd", [(6000, 100, 0.1, 0.02), (20_000, 30, 0.0, 0.005), (5003, 300, 0.0, 0.003)])
+def test_proposal_full_lists(n_draws, n, share, sd):
+    """Proposals far narrower than the noise: more draws within their bounds of
+    the threshold than a candidate list holds."""
+    from test_gpu_proposal import _check_is, _synthetic_outputs, _tacs
+    ft, cp, th, y = _tacs(9, 14)
+    o = _synthetic_outputs(th, np.random.default_rng(32), spread=0.0, sd=sd)
+    _check_is(y, ft, cp, o, n_draws, (n + 0.5) / n_draws, 5, share=share, scale=1.0, sample=list(range(9)), v_off=3)
