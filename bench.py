@@ -29,17 +29,25 @@ sys.path.insert(0, ROOT)
 METRIC = "posterior voxels/s at fixed draws & error vs FP64 oracle; % of roofline"
 # MI355X: 256 CUs x 64 lanes x 2 flops (FMA) x 2.4 GHz = 78.6 TFLOP/s FP64 vector.
 PEAK_F64_VECTOR_TFLOPS = 78.6
+# FP32 vector peak with packed instructions; the library is built without them, so
+# half of it is the most that its FP32 code can reach.
+PEAK_F32_VECTOR_TFLOPS = 157.3
 PEAK_BF16_MFMA_TFLOPS = 2500.0  # dense BF16 matrix-core peak (no sparsity)
-KERNEL_NAME = "vpet_infer_kernel"
+KERNEL_NAME = "vpet_infer_screen_kernel"
+IS_KERNEL_NAME = "vpet_infer_is_screen_kernel"
 SRC = os.path.join(ROOT, "paper_2603_14859_amd", "csrc", "vpet_abc.hip")
 
 
-def flops_per_draw(n_steps: int, n_frames: int) -> int:
-    """Floating-point work of one irreversible-2TCM draw in the kernel's formulation:
-    one FMA per grid step (2 flops), 12 flops per frame (frame value from the
-    recursion identity: 8; weighted squared residual: 4), 40 flops of per-draw
-    set-up (theta map and coefficients, transcendental internals not counted)."""
-    return 2 * n_steps + 12 * n_frames + 40
+def flops_per_draw(proposal: bool = False) -> int:
+    """FP32 operations of one irreversible-2TCM draw in the kernels' formulation
+    (the interval of its distance; neither the Philox block, a third of the
+    instructions, nor conversions and table addressing are counted): 14 for the
+    parameters, beta and W / beta, 26 for four cubics of log2 beta, 38 for the
+    quadratic form, its error bounds and the test.  A proposal draw adds 28 for
+    the normals and the mixture's exponentials, 20 for the box and 9 for the
+    bound of its fp32 parameters.  The few draws that pass (about 1.05 n a
+    voxel) are simulated exactly in FP64, not counted either."""
+    return 14 + 26 + 38 + (28 + 20 + 9 if proposal else 0)
 
 
 def host_cpu() -> str:
@@ -198,11 +206,12 @@ def bank_form(cfg, ft, cp, y_host, y_dev, steps: int, warmup: int, cpu: bool, bu
     if scan == "bf16":
         # the contraction d - a = sum_k A_vk B_gk over K = 2F real terms: one
         # multiply-add per term and pair (the hi/lo split, the error-bound
-        # product and the padding of F to a multiple of 8 are not counted)
+        # product and the padding of F to a multiple of 8 are not counted).  All
+        # pairs count, also those that a tile's bound rules out without a product.
         fpp = 2 * 2 * F
         ld = int(V.lib.vpet_abc_bank_ld(F))
         peak, bound = PEAK_BF16_MFMA_TFLOPS, "mfma"
-        kname = f"vpet_bank_mfma{'' if ld <= 32 else '_wide'}_kernel<{2 * ld}, false> (BF16 contraction scan)"
+        kname = f"vpet_bank_mfma{'' if ld <= 32 else '_wide'}_kernel<{2 * ld}, false, true> (BF16 contraction scan, ordered)"
         pilot = min(n_tot, -(-11 * n_tot // (2 * n)))
     else:
         fpp = 4 * F  # per frame: subtract, weight, fused multiply-add
@@ -305,7 +314,6 @@ def main():
     ft, cp, y_host = make_inputs(cfg, dev)
     y = torch.from_numpy(y_host).to(dev)
     models, boxes = list(cfg.models), cfg.box_array()
-    n_steps = int(round(float(ft[-1] - ft[0]) / np.float32(cfg.dt)))
     F = ft.size - 1
 
     def step(out):
@@ -358,13 +366,14 @@ def main():
     e2e_s = time.perf_counter() - t0
     del y_e2e, y_pin, out_pin
 
-    fl = flops_per_draw(n_steps, F) * cfg.n_voxels * cfg.n_draws * len(models)
+    fl = flops_per_draw() * cfg.n_voxels * cfg.n_draws * len(models)
     achieved = fl / (kernel_ms * 1e-3) / 1e12
-    roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_F64_VECTOR_TFLOPS,
-                "unit": "TFLOP/s", "frac": round(achieved / PEAK_F64_VECTOR_TFLOPS, 4),
+    roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_F32_VECTOR_TFLOPS,
+                "unit": "TFLOP/s", "frac": round(achieved / PEAK_F32_VECTOR_TFLOPS, 4),
                 "traffic": traffic_from_profiles(cfg.name),
                 "kernel": KERNEL_NAME, "kernel_ms": round(kernel_ms, 3),
-                "flops_per_draw": flops_per_draw(n_steps, F)}
+                "flops_per_draw": flops_per_draw(),
+                "note": "fp32 bounds rule draws out; every kept draw's distance is FP64"}
 
     out = {"metric": METRIC, "value": cfg.n_voxels / (ms_per_step * 1e-3), "unit": "voxels/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3),
@@ -430,7 +439,6 @@ def learned_form(cfg, ft, cp, y_host, y, steps: int, warmup: int, cpu: bool, bud
     ki = th[:, 0].astype(np.float64) * th[:, 2] / (th[:, 1] + th[:, 2])
     box = cfg.box_array()
     F = ft.size - 1
-    n_steps = int(round(float(ft[-1] - ft[0]) / np.float32(cfg.dt)))
     n_is, n_acc, share, scale = 20_000, 100, 0.1, 1.5
     train = {"bank_draws": 1_000_000, "steps": 5000, "batch": 2048, "lr": 5e-4, "noise_level": 0.05}
     torch.cuda.synchronize()
@@ -536,18 +544,18 @@ def learned_form(cfg, ft, cp, y_host, y, steps: int, warmup: int, cpu: bool, bud
     def rmse(m, n=nv):
         return float(math.sqrt(np.nanmean((m[:n, 0] - ki[:n]) ** 2)))
 
-    fl = flops_per_draw(n_steps, F) * nv * n_is
+    fl = flops_per_draw(True) * nv * n_is
     achieved = fl / (kernel_ms * 1e-3) / 1e12
     out = {"value": nv / (ms_per_step * 1e-3), "unit": "voxels/s", "ms_per_step": round(ms_per_step, 3),
            "dtype": "f64 simulation, bf16x3 network (fp32 accumulation)",
            "config": {"voxels": nv, "proposal_draws_per_voxel": n_is, "n_accept": n_acc, "prior_share": share,
                       "sd_scale": scale, "models": ["2TCM-irreversible"]},
-           "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_F64_VECTOR_TFLOPS,
-                        "unit": "TFLOP/s", "frac": round(achieved / PEAK_F64_VECTOR_TFLOPS, 4),
+           "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_F32_VECTOR_TFLOPS,
+                        "unit": "TFLOP/s", "frac": round(achieved / PEAK_F32_VECTOR_TFLOPS, 4),
                         "traffic": traffic_from_profiles(cfg.name.replace("100kdraws", "learned20k"),
-                                                         "vpet_infer_is_kernel"),
-                        "kernel": "vpet_infer_is_kernel", "kernel_ms": round(kernel_ms, 3),
-                        "flops_per_draw": flops_per_draw(n_steps, F)},
+                                                         IS_KERNEL_NAME),
+                        "kernel": IS_KERNEL_NAME, "kernel_ms": round(kernel_ms, 3),
+                        "flops_per_draw": flops_per_draw(True)},
            "training": {**train, "samples": train["steps"] * train["batch"], "seconds": round(train_s, 2),
                         "loss_first_100": float(losses[:100].mean()), "loss_last_100": float(losses[-100:].mean())},
            "comparison": {
@@ -727,7 +735,7 @@ def learned_bank_form(cfg, ft, cp, y_host, y, steps: int, warmup: int, ctx, cpu:
                         "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_MFMA_TFLOPS, 4),
                         "traffic": traffic_from_profiles(cfg.name.replace("100kdraws", "learnedbank10k"),
                                                          "vpet_bank_mfma_kernel"),
-                        "kernel": f"vpet_bank_mfma_kernel<{2 * int(V.lib.vpet_abc_bank_ld(F))}, false> (BF16 scan)",
+                        "kernel": f"vpet_bank_mfma_kernel<{2 * int(V.lib.vpet_abc_bank_ld(F))}, false, false> (BF16 scan)",
                         "kernel_ms": round(kern_ms, 3), "flops_per_pair": fpp},
            "sweep": sweep, "plain": plain, "equal_error": equal, "judge_common_threshold": judge}
     if cpu:
