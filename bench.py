@@ -69,9 +69,9 @@ def source_sha() -> str:
         return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
-def traffic_from_profiles(workload_name: str, kernel: str = KERNEL_NAME):
-    """HBM bytes per launch from the committed counter summary, if it was taken
-    on the current kernel source; else None."""
+def traffic_from_profiles(workload_name: str, kernel: str = KERNEL_NAME, field: str = "hbm_bytes_per_launch"):
+    """HBM bytes per launch (or another field) from the committed counter
+    summary, if it was taken on the current kernel source; else None."""
     path = os.path.join(ROOT, "profiles", f"{kernel}_{workload_name}_traffic.json")
     if not os.path.exists(path):
         return None
@@ -79,7 +79,7 @@ def traffic_from_profiles(workload_name: str, kernel: str = KERNEL_NAME):
         rec = json.load(f)
     if rec.get("kernel_src_sha") != source_sha():
         return None
-    return rec.get("hbm_bytes_per_launch")
+    return rec.get(field)
 
 
 def make_inputs(cfg, dev):
@@ -219,13 +219,16 @@ def bank_form(cfg, ft, cp, y_host, y_dev, steps: int, warmup: int, cpu: bool, bu
         peak, bound, kname = PEAK_F64_VECTOR_TFLOPS, "alu", f"vpet_bank_scan_kernel<{ld}, false, false> (FP64 scan)"
         pilot = min(n_tot, -(-4 * n_tot // n))
     achieved = pairs * fpp / (kern_ms * 1e-3) / 1e12
+    # the products that the ordered scan does, of all pairs' (a counter's share)
+    share = traffic_from_profiles(cfg.name, "vpet_bank_mfma_kernel", "products_done_share") if scan == "bf16" else 1.0
     out = {"value": cfg.n_voxels / (ms * 1e-3), "unit": "voxels/s", "ms_per_step": round(ms, 3),
            "call_ms_hip_events": round(call_ms, 3), "bank_build_ms": round(build_ms, 3), "ki_rmse": ki_rmse,
            "dtype": "bf16x3 contraction + f64 re-rank" if scan == "bf16" else "f64",
            "config": {"bank_draws": n_tot, "draws": "one Philox4x32-10 bank (stream 1) for all voxels",
                       "n_accept": n, "pilot_rows": pilot, "scan": scan},
            "roofline": {"bound": bound, "achieved": round(achieved, 3), "peak": peak,
-                        "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
+                        "unit": "TFLOP/s", "frac": round(achieved * share / peak, 4) if share else None,
+                        "products_done_share": share,
                         "traffic": traffic_from_profiles(cfg.name, "vpet_bank_mfma_kernel") if scan == "bf16" else None,
                         "kernel": kname, "kernel_ms": round(kern_ms, 3), "flops_per_pair": fpp}}
     if cpu:
