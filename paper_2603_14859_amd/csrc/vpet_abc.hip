@@ -1001,6 +1001,7 @@ __device__ __forceinline__ void infer_invalid(const InferArgs& P, long long row)
 }
 
 // Outputs of one voxel from its n accepted keys (ascending, in LDS).
+template <bool KEEP>
 __device__ __forceinline__ void infer_outputs(const InferArgs& P, long long row, uint32_t vg, const uint64_t* acc,
                                               double* red) {
     const int tid = threadIdx.x, n = (int)P.n_acc;
@@ -1011,8 +1012,10 @@ __device__ __forceinline__ void infer_outputs(const InferArgs& P, long long row,
     if (P.out_thr && tid == 0) P.out_thr[row] = __uint_as_float((uint32_t)(acc[n - 1] >> 32));
 
     // Survivor reduction per model: count, mean, variance (two passes, FP64).
-    // A thread's first key keeps its values between the passes.
-    const uint32_t g0 = tid < n ? (uint32_t)acc[tid] : 0u;
+    // KEEP: a thread's first key keeps its values between the passes (the larger
+    // code costs the unscreened kernel 1 us a call).
+    const uint32_t g0 = KEEP && tid < n ? (uint32_t)acc[tid] : 0u;
+    const int j1 = KEEP ? tid + (int)blockDim.x : tid;
     for (int m = 0; m < P.M; ++m) {
         const ModelDev& md = P.md[m];
         auto values = [&](uint32_t g, double (&val)[6]) {
@@ -1023,14 +1026,14 @@ __device__ __forceinline__ void infer_outputs(const InferArgs& P, long long row,
         double s1[7], v0[6];
 #pragma unroll
         for (int q = 0; q < 7; ++q) s1[q] = 0.0;
-        const bool mine0 = tid < n && g0 / P.n_draws == (uint32_t)m;
+        const bool mine0 = KEEP && tid < n && g0 / P.n_draws == (uint32_t)m;
         if (mine0) {
             values(g0, v0);
 #pragma unroll
             for (int q = 0; q < 6; ++q) s1[q] += v0[q];
             s1[6] += 1.0;
         }
-        for (int j = tid + blockDim.x; j < n; j += blockDim.x) {
+        for (int j = j1; j < n; j += blockDim.x) {
             const uint32_t g = (uint32_t)acc[j];
             if (g / P.n_draws != (uint32_t)m) continue;
             double val[6];
@@ -1054,7 +1057,7 @@ __device__ __forceinline__ void infer_outputs(const InferArgs& P, long long row,
                 s2[q] = fma(dv, dv, s2[q]);
             }
         }
-        for (int j = tid + blockDim.x; j < n; j += blockDim.x) {
+        for (int j = j1; j < n; j += blockDim.x) {
             const uint32_t g = (uint32_t)acc[j];
             if (g / P.n_draws != (uint32_t)m) continue;
             double val[6];
@@ -1122,8 +1125,9 @@ __device__ __forceinline__ void voxel_curve(const InferArgs& P, long long row, d
 }
 
 // Every draw of every model through this wavefront's running top-n: the wave's
-// n smallest keys end sorted at keys_all[wave cap ..].
-template <int KINDS, bool L1>
+// n smallest keys end sorted at keys_all[wave cap ..].  PARTS: of the draws of
+// block y's part (the grid's y extent kept in the loop costs the others 0.5 %).
+template <int KINDS, bool L1, bool PARTS>
 __device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, const double2* yw, uint64_t* keys_all) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     TopN top;
@@ -1139,7 +1143,8 @@ __device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, co
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
     for (int m = 0; m < P.M; ++m) {
         const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
-        for (uint32_t t = blockIdx.y * (uint32_t)P.wpv + (uint32_t)wave; t < ntiles; t += (uint32_t)P.wpv * gridDim.y) {
+        for (uint32_t t = (PARTS ? blockIdx.y * (uint32_t)P.wpv : 0u) + (uint32_t)wave; t < ntiles;
+             t += (uint32_t)P.wpv * (PARTS ? gridDim.y : 1u)) {
             uint64_t key[kU];
             if constexpr (KINDS != 0)
                 tile_keys<KINDS, kU, L1>(P, m, vg, t * kTile, yw, key);
@@ -1179,12 +1184,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         return;
     }
 
-    stream_draws<KINDS, L1>(P, vg, yw, keys_all);
+    stream_draws<KINDS, L1, false>(P, vg, yw, keys_all);
     __syncthreads();
     if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
     const uint64_t* acc = keys_all;  // the n accepted keys, ascending
 
-    infer_outputs(P, row, vg, acc, red);
+    infer_outputs<false>(P, row, vg, acc, red);
 }
 
 // ===========================================================================
@@ -1987,7 +1992,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     }
     if (!screened) {
         __syncthreads();
-        stream_draws<KINDS, false>(P, vg, yw, keys_all);
+        stream_draws<KINDS, false, true>(P, vg, yw, keys_all);
         __syncthreads();
         if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
     }
@@ -2023,7 +2028,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         __syncthreads();
         if (P.wpv > 1) block_topn_sort(keys_all, P.wpv, P.cap, n);
     }
-    infer_outputs(P, row, vg, keys_all, red);
+    infer_outputs<true>(P, row, vg, keys_all, red);
 }
 
 template <int KIND>
