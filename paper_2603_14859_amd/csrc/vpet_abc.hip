@@ -1965,6 +1965,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
                 block_merge_runs(keys_all, P.cap, P.wpv * P.cap);
                 int have;
                 ScreenList::prefix(keys_all, P.wpv * P.cap, n, have);
+                __syncthreads();  // (screen_exact writes the keys that every wavefront has just read)
                 const int rounds = (have + (int)blockDim.x - 1) / (int)blockDim.x;
                 for (int q = 0; q < rounds; ++q)
                     if (q * (int)blockDim.x + wave * kWave < have)

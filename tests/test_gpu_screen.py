@@ -123,3 +123,16 @@ def test_proposal_full_lists(n_draws, n, share, sd):
     ft, cp, th, y = _tacs(9, 14)
     o = _synthetic_outputs(th, np.random.default_rng(32), spread=0.0, sd=sd)
     _check_is(y, ft, cp, o, n_draws, (n + 0.5) / n_draws, 5, share=share, scale=1.0, sample=list(range(9)), v_off=3)
+
+
+@pytest.mark.parametrize("models,n_draws,n,wpv,durations", [
+    ((IRR,), 3000, 65, 4, W.SCHED_30x50), ((IRR,), 6000, 400, 4, [0.2] * 8), ((T1, REV), 4000, 400, 4, [0.2] * 8),
+    ((IRR,), 6000, 700, 2, [0.4] * 3), ((REV,), 5000, 300, 4, [0.2] * 4)])
+def test_one_list_for_the_block(models, n_draws, n, wpv, durations):
+    """Several wavefronts, n > 64: the block's merged list is read by every
+    wavefront before any of them scores its part of it (short grids make the
+    exact pass short beside the reading of a long list)."""
+    import oracle as ora
+    ft, cp, y = _inputs(n_vox=9, model=models[-1], sched=durations)
+    total = n_draws * len(models)
+    _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, (n + 0.5) / total, 23, wpv=wpv)
