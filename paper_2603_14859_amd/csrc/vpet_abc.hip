@@ -71,6 +71,8 @@ constexpr int kWave = 64;
 constexpr int kUmax = VPET_DRAWS_PER_LANE;
 template <int KINDS>
 constexpr int draws_per_lane() { return (KINDS == 1 || KINDS == 2) ? kUmax : 2; }
+// The same for screened draws, by the draw's own model also in a call of several models.
+__host__ __device__ constexpr int screen_draws_per_lane(int kind) { return kind == 4 ? 2 : kUmax; }
 constexpr double kCmin = 1e-5;        // 1 - z below which frame sums are accumulated
 constexpr int kMaxModels = 3;
 constexpr int kMaxWpv = 4;
@@ -1143,8 +1145,7 @@ __device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, co
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
     for (int m = 0; m < P.M; ++m) {
         const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
-        for (uint32_t t = (PARTS ? blockIdx.y * (uint32_t)P.wpv : 0u) + (uint32_t)wave; t < ntiles;
-             t += (uint32_t)P.wpv * (PARTS ? gridDim.y : 1u)) {
+        auto tile = [&](uint32_t t) {
             uint64_t key[kU];
             if constexpr (KINDS != 0)
                 tile_keys<KINDS, kU, L1>(P, m, vg, t * kTile, yw, key);
@@ -1155,6 +1156,15 @@ __device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, co
             else
                 tile_keys<KIND_1TCM, kU, L1>(P, m, vg, t * kTile, yw, key);
             top.insert(key);
+        };
+        if constexpr (PARTS) {
+            // the draws of screen_stream's tiles: other blocks of the voxel may be screened
+            const uint32_t per = (uint32_t)(screen_draws_per_lane(kind) / kU);
+            for (uint32_t t = blockIdx.y * (uint32_t)P.wpv + (uint32_t)wave; t * per < ntiles;
+                 t += (uint32_t)P.wpv * gridDim.y)
+                for (uint32_t q = t * per; q < min((t + 1u) * per, ntiles); ++q) tile(q);
+        } else {
+            for (uint32_t t = (uint32_t)wave; t < ntiles; t += (uint32_t)P.wpv) tile(t);
         }
     }
     top.merge();
@@ -1720,7 +1730,7 @@ struct ScreenList {
 template <int KIND, int ROW>
 __device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVox& S, const float4* tab,
                                               const float4* cross, int m, uint32_t vg, ScreenList& list) {
-    constexpr int U = KIND == KIND_REV ? 2 : kUmax, kTile = kWave * U;
+    constexpr int U = screen_draws_per_lane(KIND), kTile = kWave * U;
     const uint32_t ntiles = (P.n_draws + kTile - 1) / kTile;
     for (uint32_t t = blockIdx.y * (uint32_t)P.wpv + (threadIdx.x >> 6); t < ntiles && !list.full;
          t += (uint32_t)P.wpv * gridDim.y) {

@@ -136,3 +136,26 @@ def test_one_list_for_the_block(models, n_draws, n, wpv, durations):
     ft, cp, y = _inputs(n_vox=9, model=models[-1], sched=durations)
     total = n_draws * len(models)
     _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, (n + 0.5) / total, 23, wpv=wpv)
+
+
+def test_few_voxels_some_parts_full():
+    """A voxel's draws over four blocks of which only some have more candidates
+    than their lists hold (3072 nearly equal draws of the second model fill the
+    lists of the first three and leave the fourth none): the blocks that go on
+    without the screen take the same draws as their screened lists did."""
+    import oracle as ora
+    models = [T1, IRR, REV]
+    boxes = W.box_array(models)
+    boxes[0, 0] = boxes[2, 0] = (0.9, 1.0)  # far from the observed curves
+    boxes[0, 1] = boxes[2, 1] = (0.01, 0.05)
+    boxes[2, 2] = (0.001, 0.05)
+    boxes[2, 3] = (0.0, 0.01)
+    for s, lo, hi in ((0, 0.3, 0.30006), (1, 0.3, 0.3), (2, 0.1, 0.1), (4, 0.05, 0.05)):
+        boxes[1, s] = (lo, hi)
+    ft = W.frame_times(W.SCHED_30x50)
+    _, cp = W.grid(0.2, 50.0)
+    rng = np.random.default_rng(41)
+    th = W.true_params(rng, 2, IRR, boxes[1])
+    clean = ora.simulate(IRR, th, cp, 0.2, ft)
+    y = W.add_noise(clean, ft, rng.standard_normal(clean.shape))
+    _check_infer(ora, y, ft, cp, models, boxes, 3072, 50.5 / 9216, 17, voxel_offset=4)
