@@ -1607,8 +1607,12 @@ __device__ __forceinline__ Screened screen_draw(const InferArgs& P, const Screen
 // Candidates of one wavefront: keys (lower bound, error class, draw), the
 // first `have` of them sorted and certified at or below tau, an upper bound of
 // the wave's n-th smallest distance.  The error class is the width of the
-// draw's interval rounded up to the next float with two mantissa bits.
-constexpr uint32_t kErrBase = (127u - 40u) << 2;
+// draw's interval rounded up to the next float with one mantissa bit, 2^-80 to 1.5
+// 2^47, so that every width has one: screen_voxel admits curves with yy > 1e-10,
+// where err alone exceeds 2^-51, and with m^2 < 1e12, which bounds d and T, and rho
+// is at most 0.18 m (a proposal's kap < 0.025), so that a width is below 2^41.  (Two
+// mantissa bits from 2^-40 ended at 1.5e7, below the widths of curves with m^2 > 3e11.)
+constexpr uint32_t kErrBase = (127u - 80u) << 1;
 __device__ __forceinline__ float screen_upper(const Screened& s) {
     const float q = __builtin_amdgcn_sqrtf(fmaxf(s.d + s.err, 0.0f)) * 1.0000003f + s.rho;
     return q * q * 1.0000005f;
@@ -1616,13 +1620,13 @@ __device__ __forceinline__ float screen_upper(const Screened& s) {
 __device__ __forceinline__ uint64_t screen_key(const Screened& s, uint32_t g) {
     const float q = fmaxf(__builtin_amdgcn_sqrtf(fmaxf(s.d - s.err, 0.0f)) * 0.9999997f - s.rho, 0.0f);
     const float lower = q * q * 0.9999995f, width = screen_upper(s) - lower;
-    const uint32_t cls = min(max((__float_as_uint(width) >> 21) + 1u, kErrBase) - kErrBase, 255u);
+    const uint32_t cls = min(max((__float_as_uint(width) >> 22) + 1u, kErrBase) - kErrBase, 255u);
     return ((uint64_t)__float_as_uint(lower) << 32) | (cls << 24) | g;
 }
 // The draw's upper bound, a little up so that fp32 ties at it stay candidates.
 __device__ __forceinline__ float screen_upper(uint64_t key) {
     const float l = __uint_as_float((uint32_t)(key >> 32));
-    const float e = __uint_as_float((((uint32_t)key >> 24) + kErrBase) << 21);
+    const float e = __uint_as_float((((uint32_t)key >> 24) + kErrBase) << 22);
     return (l + e) * 1.0000005f;
 }
 

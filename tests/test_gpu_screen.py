@@ -159,3 +159,57 @@ def test_few_voxels_some_parts_full():
     clean = ora.simulate(IRR, th, cp, 0.2, ft)
     y = W.add_noise(clean, ft, rng.standard_normal(clean.shape))
     _check_infer(ora, y, ft, cp, models, boxes, 3072, 50.5 / 9216, 17, voxel_offset=4)
+
+
+def _voxel_scale(y, ft, cp, k1, vb):
+    """Largest norm of an observed curve's and a model curve's sum under unit weights."""
+    import oracle as ora
+    th = np.zeros((2, 8), np.float32)
+    th[0, 0] = 1.0           # the input's running integral
+    th[1, [0, 1, 4]] = 1.0   # the input itself
+    q, p = ora.simulate(T1, th, cp, 0.2, ft).astype(np.float64)
+    return np.linalg.norm(y.astype(np.float64), axis=1) + k1 * np.linalg.norm(q) + vb * np.linalg.norm(p)
+
+
+@pytest.mark.parametrize("models,square,wpv", [((REV,), 1e10, 1), ((REV,), 9.9e11, 1), ((REV,), 9.9e11, 4),
+                                               ((T1, REV), 3e11, 1), ((T1, REV), 9.9e11, 2), ((IRR,), 9.9e11, 1),
+                                               ((IRR,), 1e-6, 1), ((REV,), 1e-9, 1)])
+def test_scale(models, square, wpv):
+    """Weights that put the largest squared norm at either end of what the screen takes."""
+    import oracle as ora
+    ft, cp, y = _inputs(n_vox=9, model=models[-1], sched=W.SCHED_30x50)
+    weights = np.repeat(square / _voxel_scale(y, ft, cp, 1.0, 0.1)[:, None] ** 2, y.shape[1], axis=1).astype(np.float32)
+    _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), 4000, (60 + 0.5) / (4000 * len(models)), 19,
+                 weights=weights, wpv=wpv)
+
+
+def test_wide_proposal_intervals():
+    """Wide mixtures and large weights: intervals of 4e8 on distances of 9e11, whose
+    widths differ from draw to draw by more than 2^24.  Sets are equal up to draws
+    whose fp32 distances may round together (2^-24 relative on either side)."""
+    import oracle as ora
+    import oracle.proposal as prop
+    import paper_2603_14859_amd as V
+    nv, n_draws, n, share, scale = 60, 5000, 50, 0.99, 90.0
+    ft = W.frame_times(W.SCHED_30x50)
+    _, cp = W.grid(0.2, 50.0)
+    box = W.box_array([IRR])[0]
+    box[0], box[1], box[2], box[4] = (0.98, 1.0), (1e-7, 1e-6), (1e-7, 1e-6), (0.0, 1e-6)
+    th = np.zeros((1, 8), np.float32)
+    th[0, 0] = 1.0
+    q = ora.simulate(T1, th, cp, 0.2, ft)[0].astype(np.float64)
+    rng = np.random.default_rng(31)
+    y = (0.01 * q * (1.0 + 0.1 * rng.standard_normal((nv, 30)))).astype(np.float32)
+    weights = np.repeat(0.95e12 / _voxel_scale(y, ft, cp, 1.0, 0.0)[:, None] ** 2, 30, axis=1).astype(np.float32)
+    o = np.zeros((nv, 96), np.float32)
+    dev = torch.device("cuda:0")
+    g = V.infer(torch.from_numpy(y).to(dev), ft, cp, 0.2, [IRR], box[None], n_draws, (n + 0.5) / n_draws, 5, debug=True,
+                proposal=torch.from_numpy(o).to(dev), prior_share=share, sd_scale=scale, waves_per_voxel=1,
+                weights=torch.from_numpy(weights).to(dev))
+    got = g["accept_idx"].cpu().numpy()
+    for v in range(nv):
+        order, _, _, d = prop.infer_is(y[v], ft, cp, 0.2, box, o[v].astype(np.float64), n_draws, (n + 0.5) / n_draws, 5, v,
+                                       prior_share=share, sd_scale=scale, weights_v=weights[v])
+        h = d[order[n - 1]]
+        for k in set(got[v].tolist()) ^ set(order.tolist()):
+            assert abs(d[k] - h) <= 2.0 ** -22 * h, f"voxel {v}: draw {k}, {abs(d[k] - h) / h:.1e} from the threshold"
