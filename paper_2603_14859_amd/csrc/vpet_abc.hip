@@ -1984,7 +1984,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
                 for (int q = 0; q < rounds; ++q)
                     if (q * (int)blockDim.x + wave * kWave < have)
                         screen_exact<KINDS, 1>(P, vg, yw, keys_all, q * (int)blockDim.x + wave * kWave, have);
-                const int len = 1 << (32 - __builtin_clz((unsigned)(have - 1)));
+                const int len = have <= 2 ? 2 : 1 << (32 - __builtin_clz((unsigned)(have - 1)));
                 for (int j = have + tid; j < max(len, n); j += blockDim.x) keys_all[j] = kNoKey;
                 __syncthreads();
                 block_bitonic_sort(keys_all, len);

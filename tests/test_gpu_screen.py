@@ -213,3 +213,13 @@ def test_wide_proposal_intervals():
         h = d[order[n - 1]]
         for k in set(got[v].tolist()) ^ set(order.tolist()):
             assert abs(d[k] - h) <= 2.0 ** -22 * h, f"voxel {v}: draw {k}, {abs(d[k] - h) / h:.1e} from the threshold"
+
+
+@pytest.mark.parametrize("models,n_draws,n,voxels", [((IRR,), 130_000, 65, 1), ((T1,), 40_000, 70, 2),
+                                                     ((IRR, REV), 60_000, 66, 1)])
+def test_few_voxels_nearly_empty_parts(models, n_draws, n, voxels):
+    """n a little above 64, over up to 64 blocks: many of them have no candidate
+    or one."""
+    import oracle as ora
+    ft, cp, y = _inputs(n_vox=voxels, model=models[-1], sched=W.SCHED_30x50)
+    _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, (n + 0.5) / (n_draws * len(models)), 29)
