@@ -642,8 +642,8 @@ __device__ void simulate_lpnt(const float* th, const Tab& T, int F, int k0, doub
         if (tm > tD) {
             const double sv = (tm - tD) * rspan;
             const double kap = k2a + gam * exp_series(alpha * (log_pos<true>(sv) + 1.0 - sv));
-            const StepW w = __ballot(!(kap * h >= 0.0 && kap * h <= 0.3)) == 0ull ? step_weights_small(kap, h)
-                                                                                  : step_weights(kap, h);
+            // (by the lane's own step, so that a row does not depend on its neighbours)
+            const StepW w = kap * h >= 0.0 && kap * h <= 0.3 ? step_weights_small(kap, h) : step_weights(kap, h);
             z = fma(w.e, z, (k2 - R1 * kap) * fma(w.a, c_prev, w.b * c_next));
         } else {
             z = fma(w0.e, z, src0 * fma(w0.a, c_prev, w0.b * c_next));

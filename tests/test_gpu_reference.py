@@ -196,3 +196,16 @@ def test_reference_full_size_sampled():
     print(f"[reference full size] {len(sample)} sampled voxels, {swaps} with threshold swaps; "
           f"P(lp-ntPET) > 1/2 for {sens:.3f} of activated and {fpr:.3f} of null voxels")
     assert sens > 0.5 and fpr < 0.1
+
+
+@pytest.mark.parametrize("n", [1, 3, 65, 200])
+def test_lpnt_rows_do_not_depend_on_their_neighbours(n):
+    """A bank row is a function of its own draw: the same FP64 bits in a bank of
+    n rows as in one of 1000, also where some steps' exponents exceed the series'
+    range (kappa h up to 0.8) and others' do not."""
+    cfg = W.CFG_LPNT_SMALL
+    box = W.box_array([W.M_LPNTPET])
+    box[0, 2] = (0.01, 1.0)
+    box[0, 3] = (0.0, 3.0)
+    few, many = (V.bank_build([W.M_LPNTPET], box, k, 7, cfg.input_fn(), cfg.frame_times, cfg.dt)[1] for k in (n, 1000))
+    assert torch.equal(few, many[:n])
