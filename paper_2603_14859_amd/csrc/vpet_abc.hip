@@ -6105,15 +6105,43 @@ int select_key_buffer(int cap, int n, bool weighted) {
 }
 
 // Whether a call screens its draws (vpet_infer_screen_kernel), and its shapes:
-// an L2 call with a one-exponential model whose draws per voxel repay the
-// voxel's table and the segment table's launch, whose draw indices fit a key,
-// and whose segments and candidates fit the table buffer and the LDS.
-// Measured (n = 20, 30 frames / 50 min, unscreened -> screened): 16,384 voxels
-// x 1024 draws 423 -> 262 us, x 6000 draws 2090 -> 518 us; 1024 voxels x 1024
-// draws 61 -> 68 us, x 2000 draws 83 -> 72 us; 64 voxels x 2000 draws 64.4 ->
-// 64.6 us, x 6000 draws 113 -> 77 us; one voxel x 2000 draws 57 -> 60 us, x
-// 6000 draws 106 -> 72 us.
+// an L2 call whose draws per voxel repay the screen (below), whose draw indices fit
+// a key, and whose segments and candidates fit the table buffer and the LDS.
+// The fewest draws (n = 20, 30 frames / 50 min, unscreened -> screened): 16,384
+// voxels x 1024 draws 423 -> 262 us, x 6000 draws 2090 -> 518 us; 1024 voxels x 1024
+// draws 61 -> 68 us, x 2000 draws 83 -> 72 us; 64 voxels x 2000 draws 64.4 -> 64.6
+// us, x 6000 draws 113 -> 77 us; one voxel x 2000 draws 57 -> 60 us, x 6000 draws 106
+// -> 72 us.
 int64_t screen_min_draws(int64_t n_voxels) { return n_voxels >= 2048 ? 1024 : (n_voxels >= 512 ? 2000 : 2600); }
+
+// What the screen costs beside its draws is the tables of a voxel (base) and the
+// exact pass over its candidates: about 1.1 n recursions, each of them once per
+// listed model (per_n), in lists whose size `cap` sets the sorts and, through the
+// LDS, the resident wavefronts (per_cap, above the smallest list).  A call is screened
+// from base + per_n n + per_cap (cap - 256) draws on, counted in the draws that the
+// unscreened kernel does in that time.  Fitted to the faster of both kernels over 1600
+// calls (30 frames / 50 min; 16 to 30,000 voxels, 1024 to 60,000 draws, n from 1/400 to
+// 1/3 of them), from which the choice differs by 1.2 % in the mean (from the draws
+// alone: 10 %).  Unscreened -> screened, of 9000 voxels: 1TCM + both 2TCMs, 2000
+// draws, n = 80, 773 -> 1273 us, and 8000 draws, n = 20, 2204 -> 1239 us; reversible
+// 2TCM, 1024 draws, n = 10, 395 -> 488 us, and 2000 draws, n = 20, 735 -> 570 us;
+// irreversible 2TCM, 2000 draws, n = 666, 1127 -> 1299 us, and n = 20, 441 -> 221 us.
+struct ScreenCost {
+    int base, per_n, per_cap;
+};
+bool screen_pays(bool rev, int M, bool proposal, int64_t n_voxels, int64_t draws, int n_acc, int cap) {
+    static const ScreenCost costs[5][4] = {
+        // voxels: below 512, 2048, 8192 (one wavefront each from there on), more
+        {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {880, 1, 1}},                // one model of one exponential
+        {{0, 0, 0}, {1900, 30, 16}, {900, 15, 3}, {600, 8, 3}},        // two of them
+        {{0, 0, 0}, {1300, 1, 3}, {1200, 2, 1}, {900, 15, 4}},         // the reversible 2TCM
+        {{2700, 0, 0}, {1900, 30, 8}, {1600, 8, 20}, {1900, 30, 8}},   // it and another; 400 more for all three
+        {{1400, 0, 1}, {400, 0, 10}, {400, 2, 3}, {400, 2, 1}}};       // proposal draws
+    if (draws < screen_min_draws(n_voxels)) return false;
+    const ScreenCost& c = costs[proposal ? 4 : (rev ? 2 : 0) + (M > 1 ? 1 : 0)]
+                               [n_voxels < 512 ? 0 : (n_voxels < 2048 ? 1 : (n_voxels < 8192 ? 2 : 3))];
+    return draws >= c.base + (M > 2 ? 400 : 0) + (int64_t)c.per_n * n_acc + (int64_t)c.per_cap * (cap - 256);
+}
 struct ScreenPlan {
     bool use = false;
     int nseg = 0, nseg2 = 0, cap = 0, wpv = 1;
@@ -6191,7 +6219,6 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
     S.lds = 16 * ((size_t)T.F + (size_t)row * S.nseg + (size_t)kScrCross * S.nseg2) +
             sizeof(uint64_t) * screen_keys(wpv, S.cap, T.F) + sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv +
             sizeof(ScreenVox) + (o.proposal ? sizeof(MixTab) + sizeof(MixScreen) + sizeof(float) * S.nseg : 0);
-    S.use = S.lds <= (size_t)kLdsLimit;
     // a voxel's draws over several blocks while the launch has fewer than two
     // blocks per CU and a block keeps draws enough to repay its tables twice
     if (!noalloc && !o.proposal && o.waves_per_voxel == 0 && total >= 8000 &&
@@ -6199,6 +6226,9 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
         while (n_voxels * S.parts * 2 <= 512 && total / (S.parts * 2) >= 2000 && S.parts < 64)
             S.parts *= 2;
     if (S.parts < 4) S.parts = 1;  // (two: 200 voxels x 100k draws 318 us, one 275)
+    // (the parts share the candidates: 16 voxels x 2 x 4000 draws, n = 80, 222 -> 146 us)
+    S.use = S.lds <= (size_t)kLdsLimit &&
+            (S.parts > 1 || screen_pays(rev, M, o.proposal != nullptr, n_voxels, total, n_acc, S.cap));
     return S;
 }
 

@@ -223,3 +223,25 @@ def test_few_voxels_nearly_empty_parts(models, n_draws, n, voxels):
     import oracle as ora
     ft, cp, y = _inputs(n_vox=voxels, model=models[-1], sched=W.SCHED_30x50)
     _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, (n + 0.5) / (n_draws * len(models)), 29)
+
+
+@pytest.mark.parametrize("models,n_draws,n,voxels", [((T1, IRR, REV), 667, 80, 9000), ((REV,), 1024, 85, 30_000),
+                                                     ((T1, IRR), 4000, 320, 1000), ((IRR, REV), 4000, 320, 9000)])
+def test_screened_where_it_pays(models, n_draws, n, voxels):
+    """A call with too many accepted draws for its draws (or too few draws) is not
+    slower than the same call under L1, which runs the unscreened kernel and costs
+    as much there; screened, these took 1.4 to 1.8 times that."""
+    ft, cp, y = _inputs(n_vox=200, model=models[-1], sched=W.SCHED_30x50)
+    y = torch.from_numpy(np.tile(y, (voxels // 200, 1))).to("cuda:0")
+    import paper_2603_14859_amd as V
+    times = {}
+    for k in ("l1", "l2"):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+        for i in range(6):
+            V.infer(y, ft, cp, 0.2, list(models), W.box_array(list(models)), n_draws,
+                    (n + 0.5) / (n_draws * len(models)), 3, distance=k)
+            ev[i].record()
+        torch.cuda.synchronize()
+        times[k] = min(a.elapsed_time(b) for a, b in zip(ev[1:], ev[2:]))
+    print(times)
+    assert times["l2"] <= 1.2 * times["l1"]
