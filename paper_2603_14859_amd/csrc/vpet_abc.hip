@@ -6215,10 +6215,17 @@ ScreenPlan screen_plan(const HostTab& T, const InferArgs& P, const int* kinds, i
     // the large table of a voxel's two-exponential screen is shared by four wavefronts
     if (rev && o.waves_per_voxel == 0) wpv = std::max(wpv, 4);
     const int row = M == 1 && !rev ? kScrRow1 : kScrRow2;
+    auto lds_for = [&](int w) {
+        return 16 * ((size_t)T.F + (size_t)row * S.nseg + (size_t)kScrCross * S.nseg2) +
+               sizeof(uint64_t) * screen_keys(w, S.cap, T.F) + sizeof(double) * kRedStride * w + 16 + sizeof(int) * w +
+               sizeof(ScreenVox) + (o.proposal ? sizeof(MixTab) + sizeof(MixScreen) + sizeof(float) * S.nseg : 0);
+    };
+    // fewer wavefronts where their lists leave the LDS: one voxel x 20k draws, n = 896,
+    // 1380 us unscreened, 364 us with two; 1000 x 60k reversible draws, n = 1500, 4.63 and
+    // 3.83 ms (proposal draws are the faster unscreened: 1000 x 20k, n = 720, 1.44 and 1.83 ms)
+    while (o.waves_per_voxel == 0 && !o.proposal && wpv > 1 && lds_for(wpv) > (size_t)kLdsLimit) wpv >>= 1;
     S.wpv = wpv;
-    S.lds = 16 * ((size_t)T.F + (size_t)row * S.nseg + (size_t)kScrCross * S.nseg2) +
-            sizeof(uint64_t) * screen_keys(wpv, S.cap, T.F) + sizeof(double) * kRedStride * wpv + 16 + sizeof(int) * wpv +
-            sizeof(ScreenVox) + (o.proposal ? sizeof(MixTab) + sizeof(MixScreen) + sizeof(float) * S.nseg : 0);
+    S.lds = lds_for(wpv);
     // a voxel's draws over several blocks while the launch has fewer than two
     // blocks per CU and a block keeps draws enough to repay its tables twice
     if (!noalloc && !o.proposal && o.waves_per_voxel == 0 && total >= 8000 &&

@@ -245,3 +245,23 @@ def test_screened_where_it_pays(models, n_draws, n, voxels):
         times[k] = min(a.elapsed_time(b) for a, b in zip(ev[1:], ev[2:]))
     print(times)
     assert times["l2"] <= 1.2 * times["l1"]
+
+
+@pytest.mark.parametrize("models,n_draws,n,voxels", [
+    ((REV,), 30_000, 716, 3), ((REV,), 30_000, 718, 3), ((REV,), 20_000, 1500, 600), ((IRR,), 9000, 896, 2),
+    ((IRR,), 5000, 720, 600), ((T1, IRR, REV), 20_000, 1000, 2), ((REV,), 20_000, 3000, 3)])
+def test_lists_of_fewer_wavefronts(models, n_draws, n, voxels):
+    """On both sides of where four wavefronts' lists fill the LDS (n = 717)."""
+    import oracle as ora
+    ft, cp, y = _inputs(n_vox=min(voxels, 9), model=models[-1], sched=W.SCHED_30x50)
+    total = n_draws * len(models)
+    p = (n + 0.5) / total
+    if voxels <= 9:
+        _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, p, 31)
+        return
+    # (many voxels: the first ones against the same call of them alone)
+    from test_gpu_parity import _gpu_infer
+    big = _gpu_infer(np.tile(y, (voxels // 9 + 1, 1))[:voxels], ft, cp, list(models), W.box_array(list(models)), n_draws, p, 31)
+    g, _ = _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, p, 31)
+    assert np.array_equal(big["accept_idx"][:9], g["accept_idx"])
+    assert np.array_equal(big["moments"][:9], g["moments"], equal_nan=True)
