@@ -1753,25 +1753,29 @@ __device__ __forceinline__ void screen_stream(const InferArgs& P, const ScreenVo
 }
 
 // Few voxels, several blocks each: a first launch counts every draw's upper
-// bound in bins of 1.1 % (float bits with six of the mantissa, 2^-12 to 2^20); the
-// upper end of the bin that holds the n-th smallest bounds the n-th smallest
-// distance of all parts together, so that each part of the second launch
-// lists only its share of the n closest.  12 voxels x 20k draws of three models,
-// n = 300: 583 us in one block each, 420 with a list of n per part, 221 so; one
-// voxel x 100k draws 285 -> 115 us.
+// bound in bins of 1.1 % (float bits with six of the mantissa; 32 octaves, from 2^-26 to
+// 2^6 of the curve's own squared norm yy, so that its unit and the weights' scale do
+// not matter: with fixed bins up to 2^20 the split below took 439 us instead of 232
+// under weights of 3e5); the upper end of the bin that holds the n-th smallest bounds
+// the n-th smallest distance of all parts together, so that each part of the second
+// launch lists only its share of the n closest.  12 voxels x 20k draws of three
+// models, n = 300: 583 us in one block each, 420 with a list of n per part, 221 so;
+// one voxel x 100k draws 285 -> 115 us.
 constexpr int kHistBins = 2048;
-constexpr uint32_t kHistBase = (127u - 12u) << 6;
-__device__ __forceinline__ int hist_bin(float upper) {
-    return (int)min(max(__float_as_uint(upper) >> 17, kHistBase) - kHistBase, (uint32_t)kHistBins - 1u);
+__device__ __forceinline__ uint32_t hist_base(const ScreenVox& S) {
+    return (max(__float_as_uint(S.yy) >> 23, 27u) - 26u) << 6;
+}
+__device__ __forceinline__ int hist_bin(float upper, uint32_t hist0) {
+    return (int)min(max(__float_as_uint(upper) >> 17, hist0) - hist0, (uint32_t)kHistBins - 1u);
 }
 template <int KIND, int ROW>
 __device__ __forceinline__ void screen_count(const InferArgs& P, const ScreenVox& S, const float4* tab,
                                              const float4* cross, int m, uint32_t vg, unsigned* hist) {
     for (uint32_t i = blockIdx.y * blockDim.x + threadIdx.x; i < P.n_draws; i += gridDim.y * blockDim.x)
-        atomicAdd(&hist[hist_bin(screen_upper(screen_draw<KIND, ROW>(P, S, tab, cross, m, vg, i)))], 1u);
+        atomicAdd(&hist[hist_bin(screen_upper(screen_draw<KIND, ROW>(P, S, tab, cross, m, vg, i)), hist_base(S))], 1u);
 }
 // (a wavefront) Upper end of the bin that holds the n-th smallest bound.
-__device__ __forceinline__ float hist_threshold(const unsigned* hist, int n) {
+__device__ __forceinline__ float hist_threshold(const unsigned* hist, int n, uint32_t hist0) {
     constexpr int PER = kHistBins / kWave;
     const int lane = lane_id();
     int c[PER], sum = 0;
@@ -1796,7 +1800,7 @@ __device__ __forceinline__ float hist_threshold(const unsigned* hist, int n) {
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) bin = min(bin, __shfl_xor(bin, off, kWave));
-    return bin == kHistBins - 1 ? __builtin_inff() : __uint_as_float(((uint32_t)bin + 1u + kHistBase) << 17);
+    return bin == kHistBins - 1 ? __builtin_inff() : __uint_as_float(((uint32_t)bin + 1u + hist0) << 17);
 }
 
 // Exact keys of the candidates keys[j0 + lane ...], j < count, in place: U per
@@ -1955,7 +1959,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         list.have = list.nbuf = 0;
         list.tau = list.root = __builtin_inff();
         list.full = false;
-        if (gridDim.y > 1) list.set_tau(hist_threshold(P.part_hist + (size_t)row * kHistBins, n) * 1.0000005f);
+        if (gridDim.y > 1) list.set_tau(hist_threshold(P.part_hist + (size_t)row * kHistBins, n, hist_base(S)) * 1.0000005f);
         for (int m = 0; m < P.M; ++m) {
             const int kind = KINDS != 0 ? KINDS : P.md[m].kind;
             if constexpr (KINDS != 0)

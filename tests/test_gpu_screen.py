@@ -265,3 +265,29 @@ def test_lists_of_fewer_wavefronts(models, n_draws, n, voxels):
     g, _ = _check_infer(ora, y, ft, cp, list(models), W.box_array(list(models)), n_draws, p, 31)
     assert np.array_equal(big["accept_idx"][:9], g["accept_idx"])
     assert np.array_equal(big["moments"][:9], g["moments"], equal_nan=True)
+
+
+@pytest.mark.parametrize("scale", [1e-6, 3e5])
+def test_few_voxels_scale(scale):
+    """Few voxels' draws over several blocks with small and large caller weights:
+    the sets, and (the threshold of the whole voxel being found at any scale) about
+    the time of unit weights (1.9 times that under the large ones without it)."""
+    import oracle as ora
+    import paper_2603_14859_amd as V
+    models = [T1, IRR, REV]
+    ft, cp, y = _inputs(n_vox=3, model=IRR, sched=W.SCHED_30x50)
+    boxes, p = W.box_array(models), 300.5 / 60_000
+    one = np.ones(y.shape, np.float32)
+    _check_infer(ora, y, ft, cp, models, boxes, 20_000, p, 37, weights=one * np.float32(scale))
+    t = {}
+    yd = torch.from_numpy(np.tile(y, (4, 1))).to("cuda:0")
+    for w in (1.0, scale):
+        wd = torch.full_like(yd, w)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(12)]
+        for e in ev:
+            V.infer(yd, ft, cp, 0.2, models, boxes, 20_000, p, 37, weights=wd)
+            e.record()
+        torch.cuda.synchronize()
+        t[w] = min(a.elapsed_time(b) for a, b in zip(ev[1:], ev[2:]))
+    print(t)
+    assert t[scale] <= 1.4 * t[1.0]
