@@ -69,3 +69,10 @@ def test_same_sets_as_every_row(models, frames, voxels, draws, n, case):
         assert torch.equal(torch.nan_to_num(a[k].double(), nan=-7.0), torch.nan_to_num(b[k].double(), nan=-7.0)), k
     if case == "plain":
         assert a["fallback_voxels"] <= voxels // 50
+
+
+@pytest.mark.parametrize("models,frames,voxels,draws,n", [
+    ((W.M_1TCM,), 22, 524_301, 16_384, 30),               # one block per 256 voxels
+    ((W.M_MRTM, W.M_LPNTPET), 37, 131_900, 20_003, 400)])  # a second, smaller voxel chunk in the first one's buffers
+def test_one_block_and_two_chunks(models, frames, voxels, draws, n):
+    test_same_sets_as_every_row(models, frames, voxels, draws, n, "plain")
