@@ -6825,9 +6825,14 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     if (!tacs || !out_moments || !out_model_prob || !bank_theta || !bank_x)
         return fail(VPET_E_ARG, "tacs, bank and output pointers must not be NULL");
     const int64_t n_tot = (int64_t)M * n_draws;
+    bool ordered = use_mfma && order_pays(n_voxels, n_tot);
     // candidate buffer per voxel: the contraction's error margin admits rows
-    // somewhat above the threshold, so it gets twice the room (up to 4096)
-    const int cap = use_mfma ? std::max(512, std::min(4096, pow2_at_least(16 * (int)n_acc)))
+    // somewhat above the threshold, so it gets twice the room (up to 4096), and at
+    // least 256 entries for each piece of the list (with fewer, narrow posteriors, whose
+    // rows lie in few tiles, overflowed: 40,000 voxels x 80k 1TCM rows, n = 30, redid 1902
+    // voxels, 5.8 ms instead of 1.1)
+    const int cap = use_mfma ? std::max(512 * (ordered ? order_splits(n_voxels) : 1),
+                                        std::min(4096, pow2_at_least(16 * (int)n_acc)))
                              : std::max(256, pow2_at_least(8 * (int)n_acc));
     const size_t cand_bytes = sizeof(uint64_t);  // (fp32 distance or computed S, bank row)
     // default pilot: about 4 n bank rows below the threshold (FP64 scan: the
@@ -6869,7 +6874,6 @@ int vpet_abc_infer_bank(const float* tacs, int64_t n_voxels, const float* frame_
     const long long cv = std::min<long long>(n_voxels, chunk);
     const int KB = 2 * ld;  // contraction length: [x, x^2] per frame
     char* work = nullptr;
-    bool ordered = use_mfma && order_pays(n_voxels, n_tot);
     A.splits = ordered ? order_splits(cv) : 1;
     const size_t sz_tau = align256(sizeof(float) * cv), sz_cnt = align256(sizeof(int) * (1 + 2 * (size_t)A.splits) * cv);
     const size_t sz_fb = fallback_bytes(cv, (int)n_acc), sz_cand = align256(cand_bytes * (size_t)cap * cv);

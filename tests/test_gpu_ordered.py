@@ -76,3 +76,11 @@ def test_same_sets_as_every_row(models, frames, voxels, draws, n, case):
     ((W.M_MRTM, W.M_LPNTPET), 37, 131_900, 20_003, 400)])  # a second, smaller voxel chunk in the first one's buffers
 def test_one_block_and_two_chunks(models, frames, voxels, draws, n):
     test_same_sets_as_every_row(models, frames, voxels, draws, n, "plain")
+
+
+@pytest.mark.parametrize("models,voxels,draws,n", [((W.M_1TCM,), 40_000, 80_000, 30), ((W.M_2TCM_IRR,), 20_000, 150_000, 30),
+                                                   ((W.M_1TCM,), 270_000, 20_000, 16)])
+def test_narrow_posteriors_fit_their_lists(models, voxels, draws, n):
+    """Few accepted rows of a large bank: a voxel's candidates lie in few tiles, and
+    every piece of its list holds as many as half an undivided one."""
+    test_same_sets_as_every_row(models, 30, voxels, draws, n, "plain")
