@@ -2954,16 +2954,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void vp
                 }
             }
         };
+        // four; with 48 frames they and the pieces' ends leave the 128 VGPRs, so two
+        // (190,000 voxels x 16,384 rows, n = 400: 11.6 -> 10.7 ms; two with 32 frames,
+        // n = 512, 19.9 -> 21.1 ms)
+        constexpr int kLoads = LD > 40 ? 2 : 4;
         for (int pass = 0; pass < 2; ++pass) {
-            for (int j0 = 0; j0 < c; j0 += 4 * kWave) {
-                uint64_t e[4];  // four list entries per lane, loaded together
+            for (int j0 = 0; j0 < c; j0 += kLoads * kWave) {
+                uint64_t e[kLoads];  // list entries of a lane, loaded together
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kLoads; ++u) {
                     const int j = j0 + u * kWave + lane;
                     e[u] = j < c ? src[list.slot(j)] : 0ull;
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kLoads; ++u) {
                     const bool take = j0 + u * kWave + lane < c &&
                                       (__uint_as_float((uint32_t)(e[u] >> 32)) <= cthr1) == (pass == 0);
                     const uint64_t b = __ballot(take);
