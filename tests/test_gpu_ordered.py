@@ -84,3 +84,21 @@ def test_narrow_posteriors_fit_their_lists(models, voxels, draws, n):
     """Few accepted rows of a large bank: a voxel's candidates lie in few tiles, and
     every piece of its list holds as many as half an undivided one."""
     test_same_sets_as_every_row(models, 30, voxels, draws, n, "plain")
+
+
+@pytest.mark.parametrize("frames,voxels,draws,n", [(48, 301, 20_003, 40), (41, 301, 20_003, 400), (48, 20_001, 150_001, 100),
+                                                   (43, 20_001, 150_001, 512)])
+def test_most_frames(frames, voxels, draws, n):
+    """41 to 48 frames, unordered and ordered: the sets of the FP64 scan."""
+    ft = W.frame_times([0.2] * 10 + [1.0] * (frames - 10))
+    nodes, cp = W.grid(0.2, float(ft[-1]))
+    th_b, x_b = V.bank_build([W.M_2TCM_IRR], W.box_array([W.M_2TCM_IRR]), draws, 7, cp, ft, 0.2)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    clean = x_b[torch.randint(0, draws, (voxels,), generator=g, device=DEV), :frames]
+    dt = torch.from_numpy(np.diff(ft.astype(np.float64))).to(DEV)
+    y = (clean + torch.sqrt(0.05 * clean.abs() / dt)
+         * torch.randn(clean.shape, generator=g, device=DEV, dtype=torch.float64)).float().contiguous()
+    a, b = (V.infer_bank(y, ft, 0.2, nodes, [W.M_2TCM_IRR], draws, (n + 0.5) / draws, th_b, x_b, bank_scan=s, debug=True)
+            for s in ("bf16", "f64"))
+    for k in ("accept_idx", "accept_dist", "threshold", "moments", "model_prob"):
+        assert torch.equal(torch.nan_to_num(a[k].double(), nan=-7.0), torch.nan_to_num(b[k].double(), nan=-7.0)), k
