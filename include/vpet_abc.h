@@ -262,6 +262,10 @@ int vpet_abc_simulate(uint32_t model_id, const float* theta, int64_t n, const fl
  * moments and probabilities (debug outputs: index -1, distance NaN).
  * The accepted set is the n smallest keys (fp32(d), g): ties in fp32 distance
  * go to the lower global draw index.
+ * Device scratch: a call of up to 128 voxels with at least 8000 draws (L2, no
+ * proposal, waves_per_voxel 0) shares each voxel's draws between blocks through at
+ * most about 4 KiB n + 1 MiB, allocated and freed in stream order; under stream capture, or
+ * where that fails, it runs one block per voxel with the same results.
  * Errors: VPET_E_ARG, VPET_E_MODEL, VPET_E_GRID, VPET_E_LIMIT (see above),
  * VPET_E_NOMEM, VPET_E_HIP.  n_voxels = 0 returns VPET_OK with no launch.
  */
@@ -277,9 +281,9 @@ int vpet_abc_infer(const float* tacs, int64_t n_voxels, const float* frame_times
  * the same arguments, kernels and results, and no hipMalloc, hipFree or other
  * allocating routine.  The call's draw-independent tables (input nodes,
  * per-frame sums and lengths) are written in stream order into one 256 KB
- * device array that the library holds on every GPU it runs on until the
- * process ends; the largest grid (VPET_MAX_NODES nodes, VPET_MAX_FRAMES
- * frames) needs about 165 KB, and a request beyond 256 KB returns
+ * device array (what they leave of it holds the tables of screened draws) that the
+ * library holds on every GPU it runs on until the process ends; the largest grid (VPET_MAX_NODES nodes, VPET_MAX_FRAMES
+ * frames) needs about 172 KiB, and a request beyond 256 KB returns
  * VPET_E_LIMIT.  Every call on a GPU shares that array, which keeps the last
  * call's tables: calls on one stream are ordered, but calls that overlap on
  * one GPU (other streams, other host threads) race -- the caller orders them.
@@ -340,8 +344,9 @@ int vpet_abc_bank_build(uint32_t model_id, const double* prior_box, int64_t n_dr
  * not apply.  Whatever the scan, the accepted set is the exact one: a voxel
  * whose candidate list cannot prove it holds the n smallest keys is redone
  * by an exact pass over the whole bank.
- * Device scratch (a candidate list of 8 n keys, or 16 n bank rows for the
- * BF16 scan, per voxel, in voxel chunks of at most 4 GiB; the BF16 operands,
+ * Device scratch (a candidate list of 8 n keys, or for the BF16 scan of 16 n bank
+ * rows, 512 at least and 4096 at most, up to 2048 at least where rows and voxels are
+ * ordered, per voxel, in voxel chunks of at most 4 GiB; the BF16 operands,
  * 8 M n_draws ld bytes; for many voxels and rows their order, about 12 bytes a
  * row and 12 ld bytes per 64 rows; 16 KiB n for voxels that are redone) is
  * allocated and freed in stream order.

@@ -1214,8 +1214,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // with ee = sum w e^2, ye = -2 sum w y e, eq = 2 sum w q e, ep = 2 sum w p e:
 // four functions of the one variable beta and six constants per voxel.  The
 // functions are tabulated per voxel as cubics on the segments of u = beta + b0
-// (16 per octave), after which a draw costs about 100 fp32 instructions
-// instead of the 600 of its FP64 recursion over every grid step.
+// (16 per octave), after which a draw costs about 120 vector instructions
+// instead of the 613 of its FP64 recursion over every grid step.
 //
 // The reversible 2TCM has two exponentials, x = A1 e(a1) + A2 e(a2) + v p with
 // A1 + A2 = (1 - vB) K1 and rates a1 <= min(k2, k4) <= max(k2, k3 + k4) <= a2.
@@ -1233,8 +1233,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // the accepted set, its keys and the outputs are that kernel's.  A voxel whose
 // candidates do not fit (ties everywhere, a curve outside the fp32 range)
 // takes that kernel's path.  Bound by the vector ALU's issue rate, as that
-// kernel is (111 vector instructions a one-exponential draw, 235 a two-exponential
-// one, whose 19 LDS reads a draw weigh as much): 16,384 voxels x 100k draws (30
+// kernel is (121 vector instructions a one-exponential draw, 252 a two-exponential
+// one, whose 20 LDS reads a draw weigh as much; with a voxel's tables and survivors
+// 132 and 278 at 100k draws, n = 100): 16,384 voxels x 100k draws (30
 // frames, 250 steps) 31.0 -> 4.6 ms, 1024 voxels x 2000 draws 83 -> 72 us, 5003
 // voxels x 20k draws of each 2TCM 6.55 -> 1.99 ms.
 //
@@ -1246,13 +1247,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // segment has half-width <= u/32 and its cubic interpolates at the Chebyshev
 // nodes: error <= (1/32)^4/192 = 5.0e-9 times that, 3.9e-8 qa_f and 6.4e-8
 // qa_f^2, which moves d' by at most 7.7e-8 A |Qa| m (A = W for two
-// exponentials).  The polynomial in a1 has error <= 7.5e-8 qa_f (4 times the tail of
-// the Bessel series I_k(3) e^-3, k >= 12, for (a1's range) T <= 6): at most 3.8e-8
-// W^2 |Qa|^2 since 2 A1 A2 <= W^2 / 2, and its fp32 evaluation 20 eps 2 A1 |Qa| A2
-// |E2| <= 1.2e-7 A1^2 |Qa|^2 + 1.2e-5 A2^2 ee.
+// exponentials).  The polynomial in a1 has error <= 1.53e-7 qa_f (4 times the tail of
+// the Bessel series I_k(3.25) e^-3.25, k >= 12, for (a1's range) T <= kScrMaxA1T = 6.5):
+// at most 7.7e-8 W^2 |Qa|^2 since 2 A1 A2 <= W^2 / 2, and its fp32 evaluation 20 eps
+// 2 A1 |Qa| A2 |E2| <= 1.2e-7 A1^2 |Qa|^2 + 1.2e-5 A2^2 ee.
 // Roundings: the terms of d~ sum to at most 4 T, T = yy + sum A^2 ee + v^2 pp (+
 // B^2 qq); 16 roundings of a term, 3.8e-6 T.
-// So err = kScrEta W |Qa| m + kScrEps T, with A for W and a one-exponential eta.
+// So err = kScrEta W |Qa| m + kScrEps T, with A for W and a one-exponential eta; for
+// two exponentials eta = 7.7e-8 + 7.7e-8 + 1.2e-7 = 2.74e-7 (W |Qa| <= m) and eps = 3.8e-6
+// + 1.2e-5 = 1.58e-5.
 // Coefficients: u = beta + b0 in fp32 moves e_f by at most 2 eps e^-1 e^0.5 qa_f
 // per rounding of relative size eps, A and B have relative errors of 5 eps and
 // the reciprocal's: rho = 10 eps W |Qa|.  Two exponentials: a2 = (sum + r)/2 >=
@@ -4932,8 +4935,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // ---------------------------------------------------------------------------
 // Screened proposal draws (L2): the screen of vpet_infer_screen_kernel with the
 // mixture draw itself in fp32 on the hardware's transcendental unit; the draws
-// it cannot rule out are drawn and scored as in vpet_infer_is_kernel.  About 200
-// instructions a draw instead of 1100: 16,384 voxels x 20k draws, n = 100, 10.1 ->
+// it cannot rule out are drawn and scored as in vpet_infer_is_kernel.  About 220
+// instructions a draw instead of 1117 (over the whole kernel 287 at 20k draws, 320 with
+// a trained network, whose lists fill up): 16,384 voxels x 20k draws, n = 100, 10.1 ->
 // 2.66 ms, of which 0.6 ms do not depend on the number of draws.
 //
 // A trained network's draws are alike, and many lie within their bounds of the
