@@ -1157,14 +1157,17 @@ __device__ __forceinline__ void stream_draws(const InferArgs& P, uint32_t vg, co
                 tile_keys<KIND_1TCM, kU, L1>(P, m, vg, t * kTile, yw, key);
             top.insert(key);
         };
-        if constexpr (PARTS) {
+        if constexpr (PARTS && KINDS == 0) {
             // the draws of screen_stream's tiles: other blocks of the voxel may be screened
             const uint32_t per = (uint32_t)(screen_draws_per_lane(kind) / kU);
             for (uint32_t t = blockIdx.y * (uint32_t)P.wpv + (uint32_t)wave; t * per < ntiles;
                  t += (uint32_t)P.wpv * gridDim.y)
                 for (uint32_t q = t * per; q < min((t + 1u) * per, ntiles); ++q) tile(q);
         } else {
-            for (uint32_t t = (uint32_t)wave; t < ntiles; t += (uint32_t)P.wpv) tile(t);
+            static_assert(KINDS == 0 || kU == screen_draws_per_lane(KINDS), "the screened tiles");
+            for (uint32_t t = (PARTS ? blockIdx.y * (uint32_t)P.wpv : 0u) + (uint32_t)wave; t < ntiles;
+                 t += (uint32_t)P.wpv * (PARTS ? gridDim.y : 1u))
+                tile(t);
         }
     }
     top.merge();
