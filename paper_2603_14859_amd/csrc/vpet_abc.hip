@@ -1382,6 +1382,16 @@ __global__ __launch_bounds__(64) void vpet_screen_table_kernel(Tab T, double C0,
     }
 }
 
+// The widest interval that a key's error class holds (255, see ScreenList), and the
+// largest m^2 that the screen takes, of which no interval is wider.  The width is at
+// most 2 err + 4 rho (sqrt d + a rounding) and the bounds' own roundings, 2.5e-6 d; T, d
+// and A |Qa| m are at most m^2: of one exponential (2 (9e-8 + 5e-6) + 4 6e-7 + 2.5e-6)
+// m^2 = 1.51e-5 m^2, of two (2 (2.8e-7 + 1.8e-5) + 4 2.4e-6 + 2.5e-6) m^2 = 4.87e-5 m^2,
+// and a proposal draw's rho adds at most 8 kap m to the first.
+constexpr double kMaxWidth = 1.75 * (1 << 27), kMaxSquare = 1e12;
+static_assert(4.88e-5 * kMaxSquare < kMaxWidth, "every width has a class");
+__device__ __forceinline__ double max_square(double kap) { return fmin(kMaxSquare, kMaxWidth / (1.54e-5 + 33.0 * kap)); }
+
 // A voxel's constants of the screen.
 struct ScreenVox {
     float yy, yq, yp, qq, qp, pp, ny, nq, np;
@@ -1392,8 +1402,10 @@ __device__ __forceinline__ float wave_uniform(float x) {
 }
 
 // Screen constants of a voxel (wave 0, after voxel_curve): fs[f] = (w, -2 w y,
-// 2 w q, 2 w p) for the table, the sums, and whether fp32 can hold them.
-__device__ __forceinline__ bool screen_voxel(const InferArgs& P, const double2* yw, double4* fs, ScreenVox* sv) {
+// 2 w q, 2 w p) for the table, the sums, and whether fp32 can hold them and the
+// error classes the widths of the intervals, m^2 below `most`.
+__device__ __forceinline__ bool screen_voxel(const InferArgs& P, const double2* yw, double4* fs, ScreenVox* sv,
+                                             double most = kMaxSquare) {
     const int lane = lane_id();
     const cdp FR = (cdp)P.tab.fr;
     const cip NF = (cip)P.tab.nf;
@@ -1435,7 +1447,7 @@ __device__ __forceinline__ bool screen_voxel(const InferArgs& P, const double2* 
         sv->nq = (float)(nq * 1.000001);
         sv->np = (float)(np * 1.000001);
     }
-    return mm * mm < 1e12 && aa < 1e12 && yy > 1e-10;
+    return mm * mm < most && aa < 1e12 && yy > 1e-10;
 }
 
 // The voxel's table: per segment the cubics of ee, ye, eq and ep (FP64 sums),
@@ -1613,12 +1625,11 @@ __device__ __forceinline__ Screened screen_draw(const InferArgs& P, const Screen
 // Candidates of one wavefront: keys (lower bound, error class, draw), the
 // first `have` of them sorted and certified at or below tau, an upper bound of
 // the wave's n-th smallest distance.  The error class is the width of the
-// draw's interval rounded up to the next float with one mantissa bit, 2^-80 to 1.5
-// 2^47, so that every width has one: screen_voxel admits curves with yy > 1e-10,
-// where err alone exceeds 2^-51, and with m^2 < 1e12, which bounds d and T, and rho
-// is at most 0.18 m (a proposal's kap < 0.025), so that a width is below 2^41.  (Two
-// mantissa bits from 2^-40 ended at 1.5e7, below the widths of curves with m^2 > 3e11.)
-constexpr uint32_t kErrBase = (127u - 80u) << 1;
+// draw's interval rounded up to the next float with two mantissa bits, up to kMaxWidth;
+// screen_voxel admits no curve whose intervals could be wider.  (With one mantissa bit
+// and more range the lists of 16,384 voxels x 10^6 draws filled up more often, 97.0 ->
+// 102.4 ms; classes counted from the curve's own scale cost every draw 1.5 %.)
+constexpr uint32_t kErrBase = (127u - 36u) << 2;
 __device__ __forceinline__ float screen_upper(const Screened& s) {
     const float q = __builtin_amdgcn_sqrtf(fmaxf(s.d + s.err, 0.0f)) * 1.0000003f + s.rho;
     return q * q * 1.0000005f;
@@ -1626,13 +1637,13 @@ __device__ __forceinline__ float screen_upper(const Screened& s) {
 __device__ __forceinline__ uint64_t screen_key(const Screened& s, uint32_t g) {
     const float q = fmaxf(__builtin_amdgcn_sqrtf(fmaxf(s.d - s.err, 0.0f)) * 0.9999997f - s.rho, 0.0f);
     const float lower = q * q * 0.9999995f, width = screen_upper(s) - lower;
-    const uint32_t cls = min(max((__float_as_uint(width) >> 22) + 1u, kErrBase) - kErrBase, 255u);
+    const uint32_t cls = min(max((__float_as_uint(width) >> 21) + 1u, kErrBase) - kErrBase, 255u);
     return ((uint64_t)__float_as_uint(lower) << 32) | (cls << 24) | g;
 }
 // The draw's upper bound, a little up so that fp32 ties at it stay candidates.
 __device__ __forceinline__ float screen_upper(uint64_t key) {
     const float l = __uint_as_float((uint32_t)(key >> 32));
-    const float e = __uint_as_float((((uint32_t)key >> 24) + kErrBase) << 22);
+    const float e = __uint_as_float((((uint32_t)key >> 24) + kErrBase) << 21);
     return (l + e) * 1.0000005f;
 }
 
@@ -5067,7 +5078,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         mix_table(P.prop + (size_t)row * kNetOut, *mix, P.prop_share, P.prop_logscale, P.prop_logvol, P.plo, P.phi);
         wave_lds_sync();
         mix_screen(*mix, *ms);
-        const bool fits = screen_voxel(P, yw, fs, sv);
+        wave_lds_sync();
+        const bool fits = screen_voxel(P, yw, fs, sv, max_square((double)ms->kap));
         wave_lds_sync();
         if (lane == 0) flag[1] = fits && ms->bad == 0 ? 0 : 1;
     }
