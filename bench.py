@@ -211,16 +211,20 @@ def bank_form(cfg, ft, cp, y_host, y_dev, steps: int, warmup: int, cpu: bool, bu
         fpp = 2 * 2 * F
         ld = int(V.lib.vpet_abc_bank_ld(F))
         peak, bound = PEAK_BF16_MFMA_TFLOPS, "mfma"
-        kname = f"vpet_bank_mfma{'' if ld <= 32 else '_wide'}_kernel<{2 * ld}, false, true> (BF16 contraction scan, ordered)"
+        # the library scans in order from these sizes on
+        ordered = cfg.n_voxels >= 8192 and n_tot >= 16384 and pairs >= 3e9
+        kname = (f"vpet_bank_mfma{'' if ld <= 32 else '_wide'}_kernel<{2 * ld}, false, {'true' if ordered else 'false'}> "
+                 f"(BF16 contraction scan{', ordered' if ordered else ''})")
         pilot = min(n_tot, -(-11 * n_tot // (2 * n)))
     else:
         fpp = 4 * F  # per frame: subtract, weight, fused multiply-add
         ld = int(V.lib.vpet_abc_bank_ld(F))
+        ordered = False
         peak, bound, kname = PEAK_F64_VECTOR_TFLOPS, "alu", f"vpet_bank_scan_kernel<{ld}, false, false> (FP64 scan)"
         pilot = min(n_tot, -(-4 * n_tot // n))
     achieved = pairs * fpp / (kern_ms * 1e-3) / 1e12
     # the products that the ordered scan does, of all pairs' (a counter's share)
-    share = traffic_from_profiles(cfg.name, "vpet_bank_mfma_kernel", "products_done_share") if scan == "bf16" else 1.0
+    share = traffic_from_profiles(cfg.name, "vpet_bank_mfma_kernel", "products_done_share") if ordered else 1.0
     out = {"value": cfg.n_voxels / (ms * 1e-3), "unit": "voxels/s", "ms_per_step": round(ms, 3),
            "call_ms_hip_events": round(call_ms, 3), "bank_build_ms": round(build_ms, 3), "ki_rmse": ki_rmse,
            "dtype": "bf16x3 contraction + f64 re-rank" if scan == "bf16" else "f64",
@@ -380,7 +384,7 @@ def main():
 
     out = {"metric": METRIC, "value": cfg.n_voxels / (ms_per_step * 1e-3), "unit": "voxels/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3),
-           "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f64",
+           "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32 screen + f64",
            "data": "synthetic (seeded Feng input, uniform prior truths, Gaussian frame noise)",
            "config": {"workload": cfg.name, "voxels": cfg.n_voxels, "frames": F, "minutes": float(ft[-1]),
                       "grid_dt_min": cfg.dt, "draws_per_voxel": cfg.n_draws, "accept_frac": cfg.accept_frac,
@@ -550,7 +554,7 @@ def learned_form(cfg, ft, cp, y_host, y, steps: int, warmup: int, cpu: bool, bud
     fl = flops_per_draw(True) * nv * n_is
     achieved = fl / (kernel_ms * 1e-3) / 1e12
     out = {"value": nv / (ms_per_step * 1e-3), "unit": "voxels/s", "ms_per_step": round(ms_per_step, 3),
-           "dtype": "f64 simulation, bf16x3 network (fp32 accumulation)",
+           "dtype": "f32 screen + f64, bf16x3 network (fp32 accumulation)",
            "config": {"voxels": nv, "proposal_draws_per_voxel": n_is, "n_accept": n_acc, "prior_share": share,
                       "sd_scale": scale, "models": ["2TCM-irreversible"]},
            "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_F32_VECTOR_TFLOPS,
