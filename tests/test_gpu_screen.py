@@ -215,6 +215,40 @@ def test_wide_proposal_intervals():
             assert abs(d[k] - h) <= 2.0 ** -22 * h, f"voxel {v}: draw {k}, {abs(d[k] - h) / h:.1e} from the threshold"
 
 
+@pytest.mark.parametrize("part,voxels", [(0.98, 60), (1.02, 5)])
+def test_wide_proposal_gate(part, voxels):
+    """The same mixtures (standard deviations of 12) on either side of the largest
+    norm whose intervals an error class holds, 2.35e8 / (1.54e-5 + 33 kappa)."""
+    import oracle as ora
+    import oracle.proposal as prop
+    import paper_2603_14859_amd as V
+    n_draws, n, share, scale = 5000, 50, 0.99, 90.0
+    ft = W.frame_times(W.SCHED_30x50)
+    _, cp = W.grid(0.2, 50.0)
+    box = W.box_array([IRR])[0]
+    box[0], box[1], box[2], box[4] = (0.98, 1.0), (1e-7, 1e-6), (1e-7, 1e-6), (0.0, 1e-6)
+    th = np.zeros((1, 8), np.float32)
+    th[0, 0] = 1.0
+    q = ora.simulate(T1, th, cp, 0.2, ft)[0].astype(np.float64)
+    rng = np.random.default_rng(37)
+    y = (0.01 * q * (1.0 + 0.1 * rng.standard_normal((voxels, 30)))).astype(np.float32)
+    o = np.zeros((voxels, 96), np.float32)
+    sd = float(np.exp(np.max(prop.mixture(o[:1].astype(np.float64), scale)[2])))
+    square = part * 1.75 * 2.0 ** 27 / (1.54e-5 + 33.0 * (2.3e-6 * sd + 2.1e-7))
+    weights = np.repeat(square / _voxel_scale(y, ft, cp, 1.0, 0.0)[:, None] ** 2, 30, axis=1).astype(np.float32)
+    dev = torch.device("cuda:0")
+    g = V.infer(torch.from_numpy(y).to(dev), ft, cp, 0.2, [IRR], box[None], n_draws, (n + 0.5) / n_draws, 5, debug=True,
+                proposal=torch.from_numpy(o).to(dev), prior_share=share, sd_scale=scale, waves_per_voxel=1,
+                weights=torch.from_numpy(weights).to(dev))
+    got = g["accept_idx"].cpu().numpy()
+    for v in range(voxels):
+        order, _, _, d = prop.infer_is(y[v], ft, cp, 0.2, box, o[v].astype(np.float64), n_draws, (n + 0.5) / n_draws, 5, v,
+                                       prior_share=share, sd_scale=scale, weights_v=weights[v])
+        h = d[order[n - 1]]
+        for k in set(got[v].tolist()) ^ set(order.tolist()):
+            assert abs(d[k] - h) <= 2.0 ** -22 * h, f"voxel {v}: draw {k}, {abs(d[k] - h) / h:.1e} from the threshold"
+
+
 @pytest.mark.parametrize("models,n_draws,n,voxels", [((IRR,), 130_000, 65, 1), ((T1,), 40_000, 70, 2),
                                                      ((IRR, REV), 60_000, 66, 1)])
 def test_few_voxels_nearly_empty_parts(models, n_draws, n, voxels):
